@@ -13,20 +13,21 @@
 // MFMA 16x16x16 operand layout (lane l, r = l % 16, g = l / 16, j = 0..3):
 //   A[r][4g + j],  B[4g + j][r],  D[4g + j][r].
 //
-//  k_cnn_pack     fp32 master parameters -> bf16 weight layouts for the kernels
+//  k_cnn_set      loads fp32 master parameters: clears the AdamW moments and
+//                 writes the bf16 weight layouts for the kernels
 //  k_cnn_input    tile pairs -> network input: the tiles' 2x2 sums and the
 //                 64 x 64 windows' 4x4 sums (bf16), for listed tiles
-//  k_cnn_fwd      four samples per workgroup at a time, four waves per sample
-//                 (each a quarter of every layer's output tiles), weights
-//                 shared in LDS;
+//  k_cnn_fwd      one or four samples per workgroup at a time, four waves per
+//                 sample (each a quarter of every layer's output tiles),
+//                 weights shared in LDS;
 //                 inference writes the proposal (window centre, fallback
 //                 flag), training writes the activations and outputs
-//  k_cnn_loss     loss and output gradient per sample
-//  k_cnn_bwd      per-sample back-propagation through the ReLUs and the
-//                 transposed convolutions (activation gradients)
-//  k_cnn_wgrad    weight and bias gradients of one layer, per block of samples
-//  k_cnn_head_grad  head gradients
-//  k_cnn_adamw    sums the per-block gradients and applies AdamW (fp32)
+//  k_cnn_bwd      loss, output gradient and back-propagation through the ReLUs
+//                 and the transposed convolutions (activation gradients), one
+//                 sample per workgroup at a time
+//  k_cnn_wgrad    weight and bias gradients of every layer, per block of samples
+//  k_cnn_adamw    sums the per-block gradients, applies AdamW (fp32) and
+//                 refreshes the bf16 layouts
 #include "lnr_internal.h"
 
 namespace lnr {
@@ -37,8 +38,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CH = 32;
 constexpr int kWave = 64;
-constexpr int kFwdWaves = 16;     // forward workgroup: 4 samples at a time,
-constexpr int kFwdGroupWaves = 4;  // four waves per sample
+constexpr int kFwdGroupWaves = 4;  // forward: waves per sample
+// the forward workgroup holds four samples at a time; one where the samples
+// would leave CUs without a workgroup (training forward of 256 samples: 16 us
+// on 256 workgroups, with 16-byte activation stores; 48 us on 64, 2-byte)
+constexpr int kFwdMany = 4;
 
 constexpr int C1 = 4;              // input channels
 constexpr int kIn = C1 * 256;       // input values per sample
@@ -76,28 +80,39 @@ __device__ inline f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
 }
 __device__ inline bf16x4 ld4(const uint16_t* p) { return *reinterpret_cast<const bf16x4*>(p); }
 
-__global__ __launch_bounds__(256) void k_cnn_pack(const float* __restrict__ P,
-                                                  uint16_t* __restrict__ pk) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < kW1p) {
-    const int co = i / kK1, k = i % kK1;
-    float v = 0.f;
-    if (k < 9 * C1) {
-      const int tap = k / C1, ci = k % C1;
-      v = P[kOffW[0] + (co * C1 + ci) * 9 + tap];
-    }
-    pk[i] = f2bf(v);
+// Parameter i's place(s) in the packed layouts (none for biases and the head).
+__device__ inline void pack_param(int i, float v, uint16_t* __restrict__ pk) {
+  if (i < kOffB[0]) {
+    const int co = i / (9 * C1), ci = i / 9 % C1, tap = i % 9;
+    pk[co * kK1 + tap * C1 + ci] = f2bf(v);
     return;
   }
-  int j = i - kW1p;
-  if (j >= 6 * kWp) return;
-  const bool tr = j >= 3 * kWp;
-  if (tr) j -= 3 * kWp;
-  const int l = 1 + j / kWp, e = j % kWp;
-  int co, tap, ci;
-  if (!tr) { co = e / (9 * CH); tap = (e / CH) % 9; ci = e % CH; }
-  else { ci = e / (9 * CH); tap = (e / CH) % 9; co = e % CH; }
-  pk[i] = f2bf(P[kOffW[l] + (co * CH + ci) * 9 + tap]);
+#pragma unroll
+  for (int l = 1; l < 4; ++l) {
+    const int e = i - kOffW[l];
+    if (e >= 0 && i < kOffB[l]) {
+      const int co = e / (9 * CH), ci = e / 9 % CH, tap = e % 9;
+      const uint16_t h = f2bf(v);
+      uint16_t* w = pk + kW1p + (l - 1) * kWp;
+      w[(co * 9 + tap) * CH + ci] = h;
+      w[3 * kWp + (ci * 9 + tap) * CH + co] = h;
+    }
+  }
+}
+
+// Master parameters P[0, kNParam) from src (null: P already holds them), the
+// moments after them cleared with `fresh`, and the packed layouts.
+__global__ __launch_bounds__(256) void k_cnn_set(const float* __restrict__ src,
+                                                 float* __restrict__ P, int fresh,
+                                                 uint16_t* __restrict__ pk) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < CH * (kK1 - 9 * C1))  // W1's zero columns
+    pk[i / (kK1 - 9 * C1) * kK1 + 9 * C1 + i % (kK1 - 9 * C1)] = 0;
+  if (i >= kNParam) return;
+  const float v = src ? src[i] : P[i];
+  if (src) P[i] = v;
+  if (fresh) P[kNParam + i] = P[2 * kNParam + i] = 0.f;
+  pack_param(i, v, pk);
 }
 
 // Network inputs: sample i is tile tiles[i] (tile i without a list), i below
@@ -170,6 +185,26 @@ __global__ __launch_bounds__(256) void k_cnn_input(const uint8_t* __restrict__ r
 // and weight reads 4-way).
 constexpr int kPS = 40;
 constexpr int kWS = 9 * CH + 8;
+
+// `rows` rows of N elements into rows of STRIDE elements in LDS, 16 bytes per
+// thread, all of a thread's loads (up to eight) in flight before its stores
+template <int N, int STRIDE>
+__device__ inline void load_rows(const uint16_t* __restrict__ src, uint16_t* dst, int rows,
+                                 int tid, int nt) {
+  static_assert(N % 8 == 0 && STRIDE % 8 == 0, "16-byte rows");
+  const int total = rows * (N / 8);
+  for (int i0 = tid; i0 < total; i0 += 8 * nt) {
+    uint4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      v[u] = reinterpret_cast<const uint4*>(src)[min(i0 + u * nt, total - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * nt;
+      if (i < total) *reinterpret_cast<uint4*>(dst + i / (N / 8) * STRIDE + i % (N / 8) * 8) = v[u];
+    }
+  }
+}
 
 __device__ void conv1_fwd_part(const uint16_t* in, const uint16_t* W1p, const float* bias,
                                uint16_t* out, int lane, int part) {
@@ -255,18 +290,26 @@ struct ProposalOut {
 };
 
 // LDS: packed weights (W1p, then W2..W4 with padded rows) and biases, shared
-// by the workgroup's 16 waves; then per sample in flight a 256-position and a
+// by the workgroup's waves; then per sample in flight a 256-position and a
 // 64-position activation buffer (x -> a1 -> a2 -> a3 -> a4 ping-pong). The
 // head's weights are read from global memory.
 constexpr int kFwdLdsWeights = (kW1p + 3 * CH * kWS) * 2 + 4 * CH * 4;
 constexpr int kFwdBufA = 256 * kPS, kFwdBufB = 64 * kPS;  // elements
 constexpr int kFwdLdsSample = (kFwdBufA + kFwdBufB) * 2;
-constexpr int kFwdSamples = kFwdWaves / kFwdGroupWaves;
-constexpr int kFwdLds = kFwdLdsWeights + kFwdSamples * kFwdLdsSample;
-static_assert(kFwdLds <= 160 * 1024, "forward workgroup LDS");
+constexpr int fwd_lds(int spb) { return kFwdLdsWeights + spb * kFwdLdsSample; }
+static_assert(fwd_lds(kFwdMany) <= 160 * 1024, "forward workgroup LDS");
 
-template <bool TRAIN>
-__global__ __launch_bounds__(kFwdWaves * kWave) void k_cnn_fwd(
+// a1 .. a4 as stored for training: position * 32 + channel, 8 channels (one
+// 16-byte access) at a time
+__device__ inline void store_acts(const uint16_t* buf, uint16_t* __restrict__ out, int npos,
+                                  int gt, int nt) {
+  for (int i = gt; i < npos * 4; i += nt)
+    reinterpret_cast<uint4*>(out)[i] =
+        *reinterpret_cast<const uint4*>(buf + (i >> 2) * kPS + (i & 3) * 8);
+}
+
+template <bool TRAIN, int SPB>
+__global__ __launch_bounds__(SPB * kFwdGroupWaves * kWave) void k_cnn_fwd(
     const uint16_t* __restrict__ pk, const float* __restrict__ P, const uint16_t* __restrict__ x,
     int n, float* __restrict__ out, uint16_t* __restrict__ acts, ProposalOut po) {
   extern __shared__ __align__(16) uint8_t sm[];
@@ -279,23 +322,15 @@ __global__ __launch_bounds__(kFwdWaves * kWave) void k_cnn_fwd(
   const int gt = part * kWave + lane;  // thread index within the sample's group
   constexpr int GT = kFwdGroupWaves * kWave;
   {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(pk);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(sm);
-    for (int i = tid; i < kW1p / 2; i += blockDim.x) dst[i] = src[i];
-    // W2..W4 rows (96 rows of 144 dwords) into the padded rows
-    uint32_t* dw = reinterpret_cast<uint32_t*>(sW);
-    const uint32_t* sw = src + kW1p / 2;
-    for (int i = tid; i < 3 * CH * (9 * CH / 2); i += blockDim.x) {
-      const int row = i / (9 * CH / 2), q = i % (9 * CH / 2);
-      dw[row * (kWS / 2) + q] = sw[i];
-    }
+    load_rows<kK1, kK1>(pk, sW1, CH, tid, SPB * GT);
+    load_rows<9 * CH, kWS>(pk + kW1p, sW, 3 * CH, tid, SPB * GT);
     for (int i = tid; i < 4 * CH; i += blockDim.x) sb[i] = P[kOffB[i / CH] + i % CH];
   }
   uint16_t* bufA = reinterpret_cast<uint16_t*>(sm + kFwdLdsWeights + grp * kFwdLdsSample);
   uint16_t* bufB = bufA + kFwdBufA;
   // every group runs the same number of rounds (the barriers are block-wide);
   // a group past the last sample idles through its round
-  for (int s0 = blockIdx.x * kFwdSamples; s0 < n; s0 += gridDim.x * kFwdSamples) {
+  for (int s0 = blockIdx.x * SPB; s0 < n; s0 += gridDim.x * SPB) {
     const int s = s0 + grp;
     const bool act = s < n;
     __syncthreads();  // weights loaded / previous round's buffers free
@@ -318,8 +353,8 @@ __global__ __launch_bounds__(kFwdWaves * kWave) void k_cnn_fwd(
     if (act) {
       if (TRAIN) {  // stored unpadded: position * 32 + channel
         uint16_t* a = acts + (size_t)s * kActN;
-        for (int i = gt; i < 8192; i += GT) a[kActA1 + i] = bufA[(i >> 5) * kPS + (i & 31)];
-        for (int i = gt; i < 2048; i += GT) a[kActA2 + i] = bufB[(i >> 5) * kPS + (i & 31)];
+        store_acts(bufA, a + kActA1, 256, gt, GT);
+        store_acts(bufB, a + kActA2, 64, gt, GT);
       }
     }
     __syncthreads();  // a1 copied out before a3 overwrites it
@@ -329,8 +364,8 @@ __global__ __launch_bounds__(kFwdWaves * kWave) void k_cnn_fwd(
     __syncthreads();
     if (act && TRAIN) {
       uint16_t* a = acts + (size_t)s * kActN;
-      for (int i = gt; i < 2048; i += GT) a[kActA3 + i] = bufA[(i >> 5) * kPS + (i & 31)];
-      for (int i = gt; i < 512; i += GT) a[kActA4 + i] = bufB[(i >> 5) * kPS + (i & 31)];
+      store_acts(bufA, a + kActA3, 64, gt, GT);
+      store_acts(bufB, a + kActA4, 16, gt, GT);
     }
     if (act && part == 0) {
       // head (fp32): f = p * 32 + c, eight features per lane
@@ -370,39 +405,26 @@ __global__ __launch_bounds__(kFwdWaves * kWave) void k_cnn_fwd(
   }
 }
 
-// loss and output gradient (the soft target is held constant)
-__global__ __launch_bounds__(256) void k_cnn_loss(const float* __restrict__ o,
-                                                  const int32_t* __restrict__ lab, int n,
-                                                  float* __restrict__ dO,
-                                                  float* __restrict__ loss) {
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s >= n) return;
-  const float ex = 8.f * o[3 * s] - (float)lab[2 * s];
-  const float ey = 8.f * o[3 * s + 1] - (float)lab[2 * s + 1];
-  const float z = o[3 * s + 2];
-  const float q = 1.f / (1.f + expf(-4.f * (2.5f - fmaxf(fabsf(ex), fabsf(ey)))));
-  const float inv = 1.f / (float)n;
-  dO[3 * s] = 8.f * fminf(fmaxf(ex, -1.f), 1.f) * inv;
-  dO[3 * s + 1] = 8.f * fminf(fmaxf(ey, -1.f), 1.f) * inv;
-  dO[3 * s + 2] = (1.f / (1.f + expf(-z)) - q) * inv;
-  if (loss) {
-    auto hub = [](float e) { return fabsf(e) <= 1.f ? 0.5f * e * e : fabsf(e) - 0.5f; };
-    loss[s] = hub(ex) + hub(ey) + fmaxf(z, 0.f) - q * z + log1pf(expf(-fabsf(z)));
-  }
-}
-
-// da_in = transposed conv of dz (NHWC [HOUT^2][32]) with W (WT [ci][tap][co]);
-// dz_in = bf16(da_in where a_in > 0), to LDS (NHWC) and global ([ci][q])
+// da_in = transposed conv of dz (LDS, [HOUT^2] rows of kPS) with W (WT, ci
+// rows of kWS: [tap][co]); dz_in = bf16(da_in where a_in > 0), to LDS (unless
+// null) and global ([ci][q]). The workgroup's waves take the (position tile,
+// channel half) units in turn; a unit's sums run in (tap, channel half) order.
 template <int HIN, int HOUT, int S>
 __device__ void conv_bwd_data(const uint16_t* dz, const uint16_t* WT,
                               const uint16_t* __restrict__ a_in /*global NHWC*/,
-                              uint16_t* dz_in, uint16_t* __restrict__ dz_in_g, int lane) {
+                              uint16_t* dz_in, uint16_t* __restrict__ dz_in_g, int lane,
+                              int wave, int nwaves) {
   const int r = lane & 15, g = lane >> 4;
   constexpr int MT = HIN * HIN / 16;
   const bf16x4 zero = {0, 0, 0, 0};
-  for (int mt = 0; mt < MT; ++mt) {
+  for (int unit = wave; unit < 2 * MT; unit += nwaves) {
+    const int mt = unit >> 1, ci = (unit & 1) * 16 + r;
     const int q = mt * 16 + r, qy = q / HIN, qx = q % HIN;
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+    const int p0 = mt * 16 + g * 4;
+    uint16_t av[4];  // in flight with the products
+#pragma unroll
+    for (int j = 0; j < 4; ++j) av[j] = a_in[(p0 + j) * CH + ci];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
       const int ty = qy + 1 - tap / 3, tx = qx + 1 - tap % 3;
@@ -411,163 +433,199 @@ __device__ void conv_bwd_data(const uint16_t* dz, const uint16_t* WT,
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         const int co = half * 16 + g * 4;
-        const bf16x4 a = ok ? ld4(dz + (oy * HOUT + ox) * CH + co) : zero;
-        const bf16x4 b0 = ld4(WT + (r * 9 + tap) * CH + co);
-        const bf16x4 b1 = ld4(WT + ((16 + r) * 9 + tap) * CH + co);
-        acc0 = mfma(a, b0, acc0);
-        acc1 = mfma(a, b1, acc1);
+        const bf16x4 a = ok ? ld4(dz + (oy * HOUT + ox) * kPS + co) : zero;
+        acc = mfma(a, ld4(WT + ci * kWS + tap * CH + co), acc);
       }
     }
+    bf16x4 v;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int p = mt * 16 + g * 4 + j;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int ci = h * 16 + r;
-        const float d = h ? acc1[j] : acc0[j];
-        const uint16_t v = a_in[p * CH + ci] != 0 && bf2f(a_in[p * CH + ci]) > 0.f ? f2bf(d) : 0;
-        dz_in[p * CH + ci] = v;
-        dz_in_g[ci * HIN * HIN + p] = v;
-      }
+      v[j] = av[j] != 0 && bf2f(av[j]) > 0.f ? (short)f2bf(acc[j]) : (short)0;
+      if (dz_in) dz_in[(p0 + j) * kPS + ci] = (uint16_t)v[j];
     }
+    *reinterpret_cast<bf16x4*>(dz_in_g + ci * HIN * HIN + p0) = v;
   }
 }
 
-constexpr int kBwdLdsWeights = 3 * kWp * 2 + 3 * 512 * 4;
-constexpr int kBwdLdsWave = (8192 + 2048 + 2048) * 2;
-constexpr int kBwdWaves = 4;
-constexpr int kBwdLds = kBwdLdsWeights + kBwdWaves * kBwdLdsWave;
+constexpr int kBwdWaves = 8;
+constexpr int kBwdLdsWeights = 3 * CH * kWS * 2 + 3 * 512 * 4;
+constexpr int kBwdLds = kBwdLdsWeights + 2 * 64 * kPS * 2;
+static_assert(2 * kBwdLds <= 160 * 1024, "two backward workgroups per CU");
 
+// Loss and output gradient (the soft target is held constant) of sample s,
+// then its activation gradients. One sample per workgroup at a time, its
+// position tiles spread over eight waves: the chain of four layers is bound
+// by latency, and a training batch of 256 gives every CU a sample (one wave
+// per sample on 64 workgroups: 82 us at 256 samples, this form 14 us).
 __global__ __launch_bounds__(kBwdWaves * kWave) void k_cnn_bwd(
     const uint16_t* __restrict__ pk, const float* __restrict__ P,
-    const uint16_t* __restrict__ acts, const float* __restrict__ dO, int n,
+    const uint16_t* __restrict__ acts, const float* __restrict__ o,
+    const int32_t* __restrict__ lab, int n, float* __restrict__ dO, float* __restrict__ loss,
     uint16_t* __restrict__ dzs) {
   extern __shared__ __align__(16) uint8_t sm[];
-  uint16_t* sWT = reinterpret_cast<uint16_t*>(sm);  // [3][32 ci][9][32 co]
-  float* sWh = reinterpret_cast<float*>(sWT + 3 * kWp);
+  uint16_t* sWT = reinterpret_cast<uint16_t*>(sm);  // [3][32 ci][kWS]: [9][32 co] + padding
+  float* sWh = reinterpret_cast<float*>(sWT + 3 * CH * kWS);
+  uint16_t* bufB = reinterpret_cast<uint16_t*>(sm + kBwdLdsWeights);
+  uint16_t* bufC = bufB + 64 * kPS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(pk + kW1p + 3 * kWp);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(sm);
-    for (int i = tid; i < 3 * kWp / 2; i += blockDim.x) dst[i] = src[i];
-    for (int i = tid; i < 3 * 512; i += blockDim.x) sWh[i] = P[kOffWh + i];
-  }
-  __syncthreads();
-  uint16_t* bufA = reinterpret_cast<uint16_t*>(sm + kBwdLdsWeights + wave * kBwdLdsWave);
-  uint16_t* bufB = bufA + 8192;
-  uint16_t* bufC = bufB + 2048;
-  for (int s = blockIdx.x * kBwdWaves + wave; s < n; s += gridDim.x * kBwdWaves) {
+  load_rows<9 * CH, kWS>(pk + kW1p + 3 * kWp, sWT, 3 * CH, tid, kBwdWaves * kWave);
+  for (int i = tid; i < 3 * 512; i += kBwdWaves * kWave) sWh[i] = P[kOffWh + i];
+  const float inv = 1.f / (float)n;
+  for (int s = blockIdx.x; s < n; s += gridDim.x) {
+    __syncthreads();  // weights loaded / the previous sample's buffers free
     const uint16_t* a = acts + (size_t)s * kActN;
     uint16_t* dz = dzs + (size_t)s * kDzN;
-    const float d0 = dO[3 * s], d1 = dO[3 * s + 1], d2 = dO[3 * s + 2];
-    // through the head and the last ReLU: dz4 (NHWC in bufB, [c][p] global)
-    for (int f = lane; f < 512; f += kWave) {
+    const float ex = 8.f * o[3 * s] - (float)lab[2 * s];
+    const float ey = 8.f * o[3 * s + 1] - (float)lab[2 * s + 1];
+    const float z = o[3 * s + 2];
+    const float q = 1.f / (1.f + expf(-4.f * (2.5f - fmaxf(fabsf(ex), fabsf(ey)))));
+    const float d0 = 8.f * fminf(fmaxf(ex, -1.f), 1.f) * inv;
+    const float d1 = 8.f * fminf(fmaxf(ey, -1.f), 1.f) * inv;
+    const float d2 = (1.f / (1.f + expf(-z)) - q) * inv;
+    if (tid == 0) {
+      dO[3 * s] = d0;
+      dO[3 * s + 1] = d1;
+      dO[3 * s + 2] = d2;
+      if (loss) {
+        auto hub = [](float e) { return fabsf(e) <= 1.f ? 0.5f * e * e : fabsf(e) - 0.5f; };
+        loss[s] = hub(ex) + hub(ey) + fmaxf(z, 0.f) - q * z + log1pf(expf(-fabsf(z)));
+      }
+    }
+    // through the head and the last ReLU: dz4 (LDS rows, [c][p] global)
+    for (int f = tid; f < 512; f += kBwdWaves * kWave) {
       const float da = sWh[f] * d0 + sWh[512 + f] * d1 + sWh[1024 + f] * d2;
       const uint16_t av = a[kActA4 + f];
       const uint16_t v = av != 0 && bf2f(av) > 0.f ? f2bf(da) : 0;
-      bufB[f] = v;
+      bufB[(f >> 5) * kPS + (f & 31)] = v;
       dz[kDz4 + (f % CH) * 16 + f / CH] = v;
     }
-    conv_bwd_data<8, 4, 2>(bufB, sWT + 2 * kWp, a + kActA3, bufC, dz + kDz3, lane);
-    conv_bwd_data<8, 8, 1>(bufC, sWT + kWp, a + kActA2, bufB, dz + kDz2, lane);
-    conv_bwd_data<16, 8, 2>(bufB, sWT, a + kActA1, bufA, dz + kDz1, lane);
+    __syncthreads();
+    conv_bwd_data<8, 4, 2>(bufB, sWT + 2 * CH * kWS, a + kActA3, bufC, dz + kDz3, lane, wave,
+                           kBwdWaves);
+    __syncthreads();
+    conv_bwd_data<8, 8, 1>(bufC, sWT + CH * kWS, a + kActA2, bufB, dz + kDz2, lane, wave,
+                           kBwdWaves);
+    __syncthreads();
+    conv_bwd_data<16, 8, 2>(bufB, sWT, a + kActA1, nullptr, dz + kDz1, lane, wave, kBwdWaves);
   }
 }
 
-// Weight and bias gradients of layer L (1..4) over the samples of this block:
+// Weight and bias gradients of layer L (1..4) over samples [s0, s1):
 // dW[co][tap][ci] = sum_{s,p} dz[s][co][p] a_in[s][in(p, tap)][ci]
-// (M = co, N = (tap, ci), K = (s, p)), written to part[block] in the master
-// layout.
+// (M = co, N = (tap, ci) and one column of ones for the bias, K = (s, p)),
+// written to out in the master layout. A sample's input activations are
+// staged channel-major, once for each of a tap row's three columns, shifted
+// and subsampled so that output position ox reads element ox: an operand's
+// four positions are one aligned 8-byte read, whatever the tap and stride.
+// The next sample's activations are loaded during the current one's products.
 template <int L>
-__global__ __launch_bounds__(256) void k_cnn_wgrad(const uint16_t* __restrict__ acts,
-                                                   const uint16_t* __restrict__ dzs, int n,
-                                                   int per_block, float* __restrict__ part) {
-  constexpr int CIN = L == 1 ? C1 : CH;
-  constexpr int HIN = L <= 2 ? 16 : 8;
-  constexpr int HOUT = L == 1 ? 16 : (L == 4 ? 4 : 8);
-  constexpr int S = (L == 2 || L == 4) ? 2 : 1;
+struct WgradGeom {
+  static constexpr int CIN = L == 1 ? C1 : CH;
+  static constexpr int HIN = L <= 2 ? 16 : 8;
+  static constexpr int HOUT = L == 1 ? 16 : (L == 4 ? 4 : 8);
+  static constexpr int S = (L == 2 || L == 4) ? 2 : 1;
+  static constexpr int ROWS = S == 2 ? HIN + 1 : HIN + 2;  // row -1 first
+  // elements per (column, channel) plane; the padding spreads the 16 planes
+  // of an operand over the banks
+  static constexpr int PL = ROWS * HOUT + (S == 2 ? 0 : 8);
+  static constexpr int LDS = 3 * CIN * PL;  // elements
+};
+constexpr int kWgradLds = WgradGeom<2>::LDS;
+static_assert(kWgradLds >= WgradGeom<1>::LDS && kWgradLds >= WgradGeom<3>::LDS &&
+              kWgradLds >= WgradGeom<4>::LDS, "the largest layer's staging");
+
+template <int L>
+__device__ void wgrad_layer(const uint16_t* __restrict__ acts, const uint16_t* __restrict__ dzs,
+                            int s0, int s1, uint16_t* sa, float* __restrict__ out) {
+  using G = WgradGeom<L>;
+  constexpr int CIN = G::CIN, HIN = G::HIN, HOUT = G::HOUT, S = G::S, PL = G::PL;
   constexpr int NP = HOUT * HOUT;
-  constexpr int NN = 9 * CIN;                 // 18 or 288
-  constexpr int NT = (NN + 15) / 16;          // N tiles
-  constexpr int NTW = (NT + 3) / 4;           // per wave
+  constexpr int NN = 9 * CIN;               // 36 or 288; column NN: the bias
+  constexpr int NT = (NN + 1 + 15) / 16;     // N tiles
+  constexpr int NTW = (NT + 3) / 4;          // per wave
   constexpr int AIN = L == 1 ? kActX : (L == 2 ? kActA1 : (L == 3 ? kActA2 : kActA3));
   constexpr int DZ = L == 1 ? kDz1 : (L == 2 ? kDz2 : (L == 3 ? kDz3 : kDz4));
-  __shared__ float bsum[8][CH];
+  constexpr int EV = CIN == CH ? 8 : 4;      // channels per staging load
+  constexpr int NV = HIN * HIN * CIN / EV / 256;
+  static_assert(HIN * HIN * CIN % (EV * 256) == 0, "whole staging rounds");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, g = lane >> 4;
-  const int s0 = blockIdx.x * per_block, s1 = min(n, s0 + per_block);
+  for (int i = tid; i < G::LDS / 2; i += 256) reinterpret_cast<uint32_t*>(sa)[i] = 0u;
+  // this wave's operand columns: LDS element offset of position 0, -1: ones,
+  // -2: none
+  int boff[NTW];
+#pragma unroll
+  for (int t = 0; t < NTW; ++t) {
+    const int nn = (wave + 4 * t) * 16 + r, tap = nn / CIN, ci = nn % CIN;
+    boff[t] = nn < NN ? (tap % 3 * CIN + ci) * PL + tap / 3 * HOUT : (nn == NN ? -1 : -2);
+  }
   f32x4 acc[2][NTW];
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int t = 0; t < NTW; ++t) acc[m][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  typedef uint16_t vec __attribute__((ext_vector_type(EV)));
+  vec st[NV];
+  auto fetch = [&](int s) {
+    const vec* a = reinterpret_cast<const vec*>(acts + (size_t)s * kActN + AIN);
+#pragma unroll
+    for (int u = 0; u < NV; ++u) st[u] = a[tid + 256 * u];
+  };
+  if (s0 < s1) fetch(s0);
   for (int s = s0; s < s1; ++s) {
+    __syncthreads();  // cleared / the previous sample's products done
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int i = tid + 256 * u, p = i / (CIN / EV), c0 = i % (CIN / EV) * EV;
+      const int iy = p / HIN, ix = p % HIN;
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        const int t = ix + 1 - dx;
+        if (t < 0 || t % S != 0 || t / S >= HOUT) continue;
+        uint16_t* d = sa + (dx * CIN + c0) * PL + (iy + 1) * HOUT + t / S;
+#pragma unroll
+        for (int e = 0; e < EV; ++e) d[e * PL] = st[u][e];
+      }
+    }
+    __syncthreads();
+    if (s + 1 < s1) fetch(s + 1);
     const uint16_t* dz = dzs + (size_t)s * kDzN + DZ;
-    const uint16_t* ain = acts + (size_t)s * kActN + AIN;
+#pragma unroll 4
     for (int k0 = 0; k0 < NP; k0 += 16) {
       const int p0 = k0 + g * 4;
       const bf16x4 a0 = ld4(dz + r * NP + p0);
       const bf16x4 a1 = ld4(dz + (16 + r) * NP + p0);
+      const int po = p0 / HOUT * S * HOUT + p0 % HOUT;
 #pragma unroll
       for (int t = 0; t < NTW; ++t) {
-        const int nt = wave + 4 * t;
-        if (nt >= NT) continue;
-        const int nn = nt * 16 + r;
-        bf16x4 b = {0, 0, 0, 0};
-        if (nn < NN) {
-          const int tap = nn / CIN, ci = nn % CIN;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int p = p0 + j, oy = p / HOUT, ox = p % HOUT;
-            const int iy = oy * S + tap / 3 - 1, ix = ox * S + tap % 3 - 1;
-            if (iy >= 0 && iy < HIN && ix >= 0 && ix < HIN)
-              b[j] = (short)ain[(iy * HIN + ix) * CIN + ci];
-          }
-        }
+        if (wave + 4 * t >= NT) continue;
+        const short one = boff[t] == -1 ? (short)0x3f80 : (short)0;
+        bf16x4 b = {one, one, one, one};
+        if (boff[t] >= 0) b = ld4(sa + boff[t] + po);
         acc[0][t] = mfma(a0, b, acc[0][t]);
         acc[1][t] = mfma(a1, b, acc[1][t]);
       }
     }
   }
-  float* out = part + (size_t)blockIdx.x * kNParam;
 #pragma unroll
   for (int t = 0; t < NTW; ++t) {
-    const int nt = wave + 4 * t;
-    const int nn = nt * 16 + r;
-    if (nt >= NT || nn >= NN) continue;
-    const int tap = nn / CIN, ci = nn % CIN;
+    const int nn = (wave + 4 * t) * 16 + r, tap = nn / CIN, ci = nn % CIN;
+    if (nn > NN) continue;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int co = m * 16 + g * 4 + j;
-        out[kOffW[L - 1] + (co * CIN + ci) * 9 + tap] = acc[m][t][j];
+        if (nn < NN) out[kOffW[L - 1] + (co * CIN + ci) * 9 + tap] = acc[m][t][j];
+        else out[kOffB[L - 1] + co] = acc[m][t][j];
       }
-  }
-  // bias gradient: 8 position groups per channel
-  {
-    const int co = tid & 31, grp = tid >> 5;
-    float sacc = 0.f;
-    for (int s = s0; s < s1; ++s) {
-      const uint16_t* dz = dzs + (size_t)s * kDzN + DZ + co * NP;
-      for (int p = grp; p < NP; p += 8) sacc += bf2f(dz[p]);
-    }
-    bsum[grp][co] = sacc;
-    __syncthreads();
-    if (tid < CH) {
-      float b = 0.f;
-      for (int q = 0; q < 8; ++q) b += bsum[q][tid];
-      out[kOffB[L - 1] + tid] = b;
-    }
   }
 }
 
-__global__ __launch_bounds__(256) void k_cnn_head_grad(const uint16_t* __restrict__ acts,
-                                                       const float* __restrict__ dO, int n,
-                                                       int per_block, float* __restrict__ part) {
+// head gradients over samples [s0, s1)
+__device__ void wgrad_head(const uint16_t* __restrict__ acts, const float* __restrict__ dO,
+                           int s0, int s1, float* __restrict__ out) {
   const int tid = threadIdx.x;
-  const int s0 = blockIdx.x * per_block, s1 = min(n, s0 + per_block);
-  float* out = part + (size_t)blockIdx.x * kNParam;
   for (int f = tid; f < 512; f += 256) {
     float g0 = 0.f, g1 = 0.f, g2 = 0.f;
     for (int s = s0; s < s1; ++s) {
@@ -587,6 +645,28 @@ __global__ __launch_bounds__(256) void k_cnn_head_grad(const uint16_t* __restric
   }
 }
 
+// Block (x, y): layer y + 1 (4: the head) over block x's samples, into
+// part[x]. Bound by the staging's latency per sample, so a block takes few
+// samples (cnn_grad_blocks): at a training batch of 256, 64 blocks per layer
+// of 4 samples, all layers in one launch, take 21 us; one launch per layer
+// with 4 blocks of 64 samples, reading the operands element by element from
+// global memory, took 2210 us.
+__global__ __launch_bounds__(256) void k_cnn_wgrad(const uint16_t* __restrict__ acts,
+                                                   const uint16_t* __restrict__ dzs,
+                                                   const float* __restrict__ dO, int n,
+                                                   int per_block, float* __restrict__ part) {
+  __shared__ __align__(16) uint16_t sa[kWgradLds];
+  const int s0 = min(n, (int)blockIdx.x * per_block), s1 = min(n, s0 + per_block);
+  float* out = part + (size_t)blockIdx.x * kNParam;
+  switch (blockIdx.y) {
+    case 0: wgrad_layer<1>(acts, dzs, s0, s1, sa, out); break;
+    case 1: wgrad_layer<2>(acts, dzs, s0, s1, sa, out); break;
+    case 2: wgrad_layer<3>(acts, dzs, s0, s1, sa, out); break;
+    case 3: wgrad_layer<4>(acts, dzs, s0, s1, sa, out); break;
+    default: wgrad_head(acts, dO, s0, s1, out); break;
+  }
+}
+
 struct AdamArgs {
   float lr, b1, b2, eps, wd, c1, c2;  // c1 = 1 - b1^t, c2 = 1 - b2^t
 };
@@ -594,10 +674,12 @@ struct AdamArgs {
 __global__ __launch_bounds__(256) void k_cnn_adamw(const float* __restrict__ part, int nblk,
                                                    float* __restrict__ P, float* __restrict__ m,
                                                    float* __restrict__ v, AdamArgs a,
-                                                   float* __restrict__ grad_out) {
+                                                   float* __restrict__ grad_out,
+                                                   uint16_t* __restrict__ pk) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= kNParam) return;
   float g = 0.f;
+#pragma unroll 16
   for (int b = 0; b < nblk; ++b) g += part[(size_t)b * kNParam + i];
   if (grad_out) grad_out[i] = g;
   if (a.lr == 0.f && a.wd == 0.f) return;  // gradient only
@@ -606,7 +688,9 @@ __global__ __launch_bounds__(256) void k_cnn_adamw(const float* __restrict__ par
   m[i] = mi;
   v[i] = vi;
   const float mh = mi / a.c1, vh = vi / a.c2;
-  P[i] = P[i] - a.lr * (mh / (sqrtf(vh) + a.eps) + a.wd * P[i]);
+  const float p = P[i] - a.lr * (mh / (sqrtf(vh) + a.eps) + a.wd * P[i]);
+  P[i] = p;
+  pack_param(i, p, pk);
 }
 
 }  // namespace
@@ -617,8 +701,10 @@ size_t cnn_act_elems() { return kActN; }
 size_t cnn_dz_elems() { return kDzN; }
 size_t cnn_input_elems() { return kIn; }
 
-hipError_t launch_cnn_pack(const float* params, uint16_t* packed, hipStream_t st) {
-  LNR_LAUNCH(k_cnn_pack, dim3((kPacked + 255) / 256), dim3(256), 0, st, params, packed);
+hipError_t launch_cnn_set(const float* src, float* params, bool fresh, uint16_t* packed,
+                          hipStream_t st) {
+  LNR_LAUNCH(k_cnn_set, dim3((kNParam + 255) / 256), dim3(256), 0, st, src, params, fresh ? 1 : 0,
+             packed);
   return hipGetLastError();
 }
 
@@ -631,11 +717,19 @@ hipError_t launch_cnn_input(const uint8_t* ref, const uint8_t* warped, int w, in
   return hipGetLastError();
 }
 
-// one workgroup per CU at most (each loads the weights once), looping over
-// the samples four at a time
-static int fwd_blocks(int n) {
-  int b = (n + kFwdSamples - 1) / kFwdSamples;
-  return b < 256 ? (b < 1 ? 1 : b) : 256;
+// at most one forward workgroup per CU (each loads the weights once), looping
+// over the samples spb at a time
+template <bool TRAIN, int SPB>
+static hipError_t launch_fwd(const uint16_t* packed, const float* params, const uint16_t* x, int n,
+                             float* out, uint16_t* acts, const ProposalOut& po, hipStream_t st) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cnn_fwd<TRAIN, SPB>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds(SPB));
+  if (e != hipSuccess) return e;
+  const int blocks = (n + SPB - 1) / SPB;
+  LNR_LAUNCH((k_cnn_fwd<TRAIN, SPB>), dim3(blocks < 256 ? blocks : 256),
+             dim3(SPB * kFwdGroupWaves * kWave), fwd_lds(SPB), st, packed, params, x, n, out, acts,
+             po);
+  return hipGetLastError();
 }
 
 hipError_t launch_cnn_forward(const uint16_t* packed, const float* params, const uint16_t* x,
@@ -644,25 +738,19 @@ hipError_t launch_cnn_forward(const uint16_t* packed, const float* params, const
                               const int32_t* tiles, const int* count, int* lists, int* counts) {
   if (n <= 0) return hipSuccess;
   ProposalOut po{centre, fallback, clampc, conf_logit, tiles, count, lists, counts, n};
-  hipError_t e;
-  if (acts) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cnn_fwd<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kFwdLds);
-    if (e != hipSuccess) return e;
-    LNR_LAUNCH(k_cnn_fwd<true>, dim3(fwd_blocks(n)), dim3(kFwdWaves * kWave), kFwdLds, st,
-               packed, params, x, n, out, acts, po);
-  } else {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cnn_fwd<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kFwdLds);
-    if (e != hipSuccess) return e;
-    LNR_LAUNCH(k_cnn_fwd<false>, dim3(fwd_blocks(n)), dim3(kFwdWaves * kWave), kFwdLds, st,
-               packed, params, x, n, out, acts, po);
-  }
-  return hipGetLastError();
+  const bool few = n <= 256;
+  if (acts)
+    return few ? launch_fwd<true, 1>(packed, params, x, n, out, acts, po, st)
+               : launch_fwd<true, kFwdMany>(packed, params, x, n, out, acts, po, st);
+  return few ? launch_fwd<false, 1>(packed, params, x, n, out, acts, po, st)
+             : launch_fwd<false, kFwdMany>(packed, params, x, n, out, acts, po, st);
 }
 
+// Samples per gradient block: the batch over 64 blocks per layer (320 in
+// all, a little over one per CU) down to one sample a block, over at most
+// 256 for large batches (their partial gradients are summed once more).
 int cnn_grad_blocks(int n, int* per_block) {
-  const int pb = 64;
+  const int pb = n <= 256 ? (n + 63) / 64 : (n + 255) / 256 < 4 ? 4 : (n + 255) / 256;
   *per_block = pb;
   return (n + pb - 1) / pb;
 }
@@ -672,27 +760,21 @@ hipError_t launch_cnn_backward(const uint16_t* packed, const float* params,
                                int n, float* dO, float* loss, uint16_t* dzs, float* part,
                                hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  LNR_LAUNCH(k_cnn_loss, dim3((n + 255) / 256), dim3(256), 0, st, out, labels, n, dO, loss);
-  hipError_t e = hipGetLastError();
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cnn_bwd),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLds);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cnn_bwd),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLds);
-  if (e != hipSuccess) return e;
-  LNR_LAUNCH(k_cnn_bwd, dim3(fwd_blocks(n)), dim3(kBwdWaves * kWave), kBwdLds, st, packed, params,
-             acts, dO, n, dzs);
+  LNR_LAUNCH(k_cnn_bwd, dim3(n < 512 ? n : 512), dim3(kBwdWaves * kWave), kBwdLds, st, packed,
+             params, acts, out, labels, n, dO, loss, dzs);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int pb = 0;
   const int nb = cnn_grad_blocks(n, &pb);
-  LNR_LAUNCH(k_cnn_wgrad<1>, dim3(nb), dim3(256), 0, st, acts, dzs, n, pb, part);
-  LNR_LAUNCH(k_cnn_wgrad<2>, dim3(nb), dim3(256), 0, st, acts, dzs, n, pb, part);
-  LNR_LAUNCH(k_cnn_wgrad<3>, dim3(nb), dim3(256), 0, st, acts, dzs, n, pb, part);
-  LNR_LAUNCH(k_cnn_wgrad<4>, dim3(nb), dim3(256), 0, st, acts, dzs, n, pb, part);
-  LNR_LAUNCH(k_cnn_head_grad, dim3(nb), dim3(256), 0, st, acts, dO, n, pb, part);
+  LNR_LAUNCH(k_cnn_wgrad, dim3(nb, 5), dim3(256), 0, st, acts, dzs, dO, n, pb, part);
   return hipGetLastError();
 }
 
 hipError_t launch_cnn_adamw(const float* part, int nblk, float* params, float* m, float* v,
-                            float lr, float wd, int step, float* grad_out, hipStream_t st) {
+                            float lr, float wd, int step, float* grad_out, uint16_t* packed,
+                            hipStream_t st) {
   AdamArgs a;
   a.lr = lr;
   a.b1 = 0.9f;
@@ -702,7 +784,7 @@ hipError_t launch_cnn_adamw(const float* part, int nblk, float* params, float* m
   a.c1 = (float)(1.0 - pow(0.9, step));
   a.c2 = (float)(1.0 - pow(0.999, step));
   LNR_LAUNCH(k_cnn_adamw, dim3((kNParam + 255) / 256), dim3(256), 0, st, part, nblk, params, m,
-             v, a, grad_out);
+             v, a, grad_out, packed);
   return hipGetLastError();
 }
 

@@ -1790,13 +1790,10 @@ lnr_status lnr_proposal_set(lnr_ctx* ctx, const float* params, void* stream) {
   TraceGuard tg(ctx);
   if (!params) return fail(ctx, LNR_E_ARG, "params is null");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, LNR_E_HIP, "hipSetDevice");
-  const size_t np = (size_t)cnn_param_count();
   lnr_status s;
   if ((s = ensure_cnn(ctx)) != LNR_OK) return s;
   const hipStream_t st = (hipStream_t)stream;
-  LNR_HIP(hipMemcpyAsync(ctx->cnn, params, np * sizeof(float), hipMemcpyDeviceToDevice, st));
-  LNR_HIP(hipMemsetAsync(ctx->cnn + np, 0, 2 * np * sizeof(float), st));
-  LNR_HIP(launch_cnn_pack(ctx->cnn, ctx->cnn_packed, st));
+  LNR_HIP(launch_cnn_set(params, ctx->cnn, true, ctx->cnn_packed, st));
   ctx->cnn_step = 0;
   return LNR_OK;
 }
@@ -1857,8 +1854,7 @@ lnr_status lnr_proposal_load(lnr_ctx* ctx, const char* path, void* stream) {
   if ((s = ensure_cnn(ctx)) != LNR_OK) return s;
   const hipStream_t st = (hipStream_t)stream;
   LNR_HIP(hipMemcpyAsync(ctx->cnn, host.data(), np * sizeof(float), hipMemcpyHostToDevice, st));
-  LNR_HIP(hipMemsetAsync(ctx->cnn + np, 0, 2 * np * sizeof(float), st));
-  LNR_HIP(launch_cnn_pack(ctx->cnn, ctx->cnn_packed, st));
+  LNR_HIP(launch_cnn_set(nullptr, ctx->cnn, true, ctx->cnn_packed, st));
   LNR_HIP(hipStreamSynchronize(st));  // the host copy is freed on return
   ctx->cnn_step = 0;
   return LNR_OK;
@@ -1917,7 +1913,7 @@ lnr_status lnr_proposal_checkpoint_load(lnr_ctx* ctx, const char* path, uint64_t
   const hipStream_t st = (hipStream_t)stream;
   LNR_HIP(hipMemcpyAsync(ctx->cnn, host.data(), 3 * np * sizeof(float), hipMemcpyHostToDevice,
                          st));
-  LNR_HIP(launch_cnn_pack(ctx->cnn, ctx->cnn_packed, st));
+  LNR_HIP(launch_cnn_set(nullptr, ctx->cnn, false, ctx->cnn_packed, st));
   LNR_HIP(hipStreamSynchronize(st));  // the host copy is freed on return
   ctx->cnn_step = (int)hdr[3];
   if (counter) *counter = ctr;
@@ -1982,8 +1978,7 @@ lnr_status lnr_proposal_train_step(lnr_ctx* ctx, const uint16_t* x, const int32_
   const bool update = lr != 0.f || wd != 0.f;
   if (update) ++ctx->cnn_step;
   LNR_HIP(launch_cnn_adamw(part, nb, ctx->cnn, ctx->cnn + np, ctx->cnn + 2 * np, lr, wd,
-                           update ? ctx->cnn_step : 1, grad, st));
-  if (update) LNR_HIP(launch_cnn_pack(ctx->cnn, ctx->cnn_packed, st));
+                           update ? ctx->cnn_step : 1, grad, ctx->cnn_packed, st));
   return LNR_OK;
 }
 

@@ -301,7 +301,10 @@ size_t cnn_act_elems();      // stored activations per sample (bf16)
 size_t cnn_dz_elems();       // activation gradients per sample (bf16)
 size_t cnn_input_elems();    // network input values per tile (bf16)
 int cnn_grad_blocks(int n, int* per_block);
-hipError_t launch_cnn_pack(const float* params, uint16_t* packed, hipStream_t st);
+// params from src (device; null: params already holds them) and its packed
+// layouts; fresh: the moments, which follow the parameters, are cleared
+hipError_t launch_cnn_set(const float* src, float* params, bool fresh, uint16_t* packed,
+                          hipStream_t st);
 // network inputs x[i] of tile tiles[i] (tile i without a list), i below
 // *count (without it, every tile)
 hipError_t launch_cnn_input(const uint8_t* ref, const uint8_t* warped, int w, int h, int ntx,
@@ -326,6 +329,7 @@ hipError_t launch_cnn_backward(const uint16_t* packed, const float* params,
                                int n, float* dO, float* loss, uint16_t* dzs, float* part,
                                hipStream_t st);
 hipError_t launch_cnn_adamw(const float* part, int nblk, float* params, float* m, float* v,
-                            float lr, float wd, int step, float* grad_out, hipStream_t st);
+                            float lr, float wd, int step, float* grad_out, uint16_t* packed,
+                            hipStream_t st);
 
 }  // namespace lnr
