@@ -104,17 +104,15 @@ __device__ inline uint32_t warp_px(const uint8_t* __restrict__ src, int w, int h
 }
 
 // Four consecutive pixels per thread, one 32-bit store when the row allows it.
-// Block (0, 0) also clears the level's valid-match bits vbz[0, nwords) and
-// least-squares sums (the search that follows fills the bits).
+// Block (0, 0) also clears the level's valid-match bits vbz[0, nwords) (the
+// search that follows sets them).
 __global__ __launch_bounds__(256) void k_warp_q8(const uint8_t* __restrict__ src, int w, int h,
                                                  const double* __restrict__ Hn,
                                                  uint8_t* __restrict__ out,
                                                  unsigned long long* __restrict__ vbz, int nwords,
-                                                 long long* __restrict__ sums,
                                                  int* __restrict__ zint, int nzint) {
   if (vbz && blockIdx.x == 0 && blockIdx.y == 0) {
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) vbz[i] = 0ull;
-    if (threadIdx.x < 24) sums[threadIdx.x] = 0;
     if (threadIdx.x < nzint) zint[threadIdx.x] = 0;
   }
   const int x = 4 * (blockIdx.x * blockDim.x + threadIdx.x), y = blockIdx.y;
@@ -135,7 +133,7 @@ __global__ __launch_bounds__(256) void k_warp_q8(const uint8_t* __restrict__ src
 
 // k_warp_q8 for a table of jobs: block b covers run b % nxb (1024 pixels) of
 // row b / nxb of all the jobs' levels (job j owns rows [row0[j], row0[j + 1])).
-// The first row's first run of each job clears that job's weeding bits and sums.
+// The first row's first run of each job clears that job's weeding bits.
 __global__ __launch_bounds__(256) void k_warp_jobs(const WarpJob* __restrict__ jobs,
                                                    const int* __restrict__ row0, int njobs,
                                                    int nxb) {
@@ -150,7 +148,6 @@ __global__ __launch_bounds__(256) void k_warp_jobs(const WarpJob* __restrict__ j
   const int y = gy - __builtin_amdgcn_readfirstlane(row0[lo]);
   if (y == 0 && bx == 0) {
     for (int i = threadIdx.x; i < J.nwords; i += blockDim.x) J.vb[i] = 0ull;
-    if (threadIdx.x < 24) J.sums[threadIdx.x] = 0;
   }
   const int x = 4 * (bx * blockDim.x + threadIdx.x);
   if (x >= J.w) return;
@@ -1056,7 +1053,7 @@ hipError_t launch_warp_q8(const uint8_t* src, int w, int h, const double* Hn, ui
                           hipStream_t st, const WeedBufs* wb, int nwords, int* zint, int nzint) {
   dim3 grid((w + 1023) / 1024, h);
   LNR_LAUNCH(k_warp_q8, grid, dim3(256), 0, st, src, w, h, Hn, out, wb ? wb->vb : nullptr,
-             nwords, wb ? wb->sums : nullptr, zint, zint ? nzint : 0);
+             nwords, zint, zint ? nzint : 0);
   return hipGetLastError();
 }
 

@@ -4,27 +4,25 @@
 // source side p + d - c, reference side p - c).
 //
 // k_valid: the valid-match bits of the tiles, one 64-bit word per 64 tiles
-//         (a wave ballot each); also clears the fit sums. In a registration
-//         the level's warp clears them and its search sets the bits instead.
-// k_hyp:  one lane per iteration, one wave per block. Each wave prefix-sums
-//         the words' popcounts, draws four distinct match indices from the
+//         (a wave ballot each). In a registration the level's warp clears
+//         them and its search sets the bits instead.
+// k_hyp:  a block draws and solves a group of hypotheses and tests every tile
+//         against them. Its first wave prefix-sums the words' popcounts,
+//         draws four distinct match indices per hypothesis from the
 //         counter-based SplitMix64 stream, maps them to tiles with a
-//         rank-select over the words, and solves the 8x8 system in double
-//         precision (partial pivoting, fixed operation order) with the matrix
-//         in registers.
-// k_test: a (256 tiles x 4 or 8 iterations) block tests its tiles against its
-//         hypotheses; wave ballots form each iteration's inlier bitmask row,
-//         and the block's count per iteration is added atomically.
-// k_union: a wave per word of 64 tiles. Every block reads the counts, takes
-//         the accepted iterations (count above delta) and the best consensus
-//         (most inliers, lowest iteration); a wave ORs the accepted rows of
-//         its word (M is the union of those rows; any split of the
-//         iterations gives the same M, as the paper notes), writes its tiles'
-//         flags and adds their terms of the least-squares normal equations of
-//         G: p -> p + d over the best hypothesis' inliers exactly in int64
-//         (order-free) to the level's sums.
-// k_solve: one lane solves the normal equations in double precision (the
-//         solver of k_hyp) and composes H_l = H_{l+1} o G.
+//         rank-select over the words and solves the 8x8 systems in double
+//         precision, a row per lane; wave ballots over the tiles give each
+//         hypothesis' count and inlier bits, so that the block knows by
+//         itself which of its hypotheses are accepted (count above delta),
+//         the union of their inliers and its best hypothesis.
+// k_fit:  M, the union of the blocks' unions (any split of the iterations
+//         gives the same M, as the paper notes), and the best consensus of
+//         all blocks (most inliers, lowest iteration), whose inliers are
+//         tested once more; writes the tiles' flags and sums the
+//         least-squares normal equations of G: p -> p + d over those inliers
+//         exactly in int64 (order-free), solves them (the solver of k_hyp)
+//         and composes H_l = H_{l+1} o G. One block up to kFitWords words;
+//         larger levels spread the tiles over blocks and k_solve finishes.
 // The kernels are ordered by the stream; no block waits for another.
 #include "lnr_device.h"
 #include "lnr_internal.h"
@@ -39,57 +37,118 @@ __device__ inline unsigned long long splitmix64(unsigned long long x) {
   return z ^ (z >> 31);
 }
 
-// 8x8 solve of the augmented system a (row-major 8 x 9), kept in registers
-// (every index is a compile-time constant): Gaussian elimination with partial
-// pivoting (first largest |pivot|); |pivot| < 1e-12 or NaN fails. Entries left
-// of the pivot column are never read again, so row swaps move columns c..8.
-__device__ inline bool solve8(double (&a)[72], double (&x)[8]) {
+// Lane exchanges within groups of eight lanes, on the vector ALU.
+template <int CTRL>
+__device__ inline int dpp_i32(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)dpp_i32<CTRL>((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)dpp_i32<CTRL>((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141;  // quad_perm, row_half_mirror
+
+// 8x8 solve of augmented systems, one per group of eight lanes: lane r of a
+// group holds row r (9 values). Gaussian elimination with partial pivoting:
+// of the rows not yet used, the largest |pivot|, the first on ties in the
+// order that swapping rows would leave them in (pos; rows stay in their
+// lanes); |pivot| < 1e-12 or NaN fails. Every value is computed with the
+// operations, in the order, of the one-lane elimination, so the solution
+// does not depend on the layout; a column's row updates and divisions run
+// side by side instead of one after another. Every lane keeps the pivot rows
+// (broadcast once per column) and substitutes back by itself. All 64 lanes
+// take part; a failed group goes on with meaningless values.
+// Quotients are formed as div2 does, from one reciprocal per pivot: the
+// values of a system of integer coordinates stay far from the ends of the
+// exponent range, where that differs from a plain division.
+__device__ inline bool solve8_rows(double (&a)[9], double (&x)[8]) {
+  const int lane = threadIdx.x & 63, group = lane & 56;
+  int pos = lane & 7;
+  bool ok = true;
+  double U[8][9], r[8];  // pivot rows and the pivots' reciprocals
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    int piv = c;
-    double best = fabs(a[c * 9 + c]);
-#pragma unroll
-    for (int r = c + 1; r < 8; ++r) {
-      const double v = fabs(a[r * 9 + c]);
-      if (v > best) { best = v; piv = r; }
+    // the largest high word decides unless two rows share it
+    const double v = fabs(a[c]);
+    const int hw = pos >= c ? __double2hiint(v) : -1;
+    int top = max(hw, dpp_i32<kXor1>(hw));
+    top = max(top, dpp_i32<kXor2>(top));
+    top = max(top, dpp_i32<kMirror8>(top));
+    double rc = __builtin_amdgcn_rcp(a[c]);  // every row's, while the search goes on
+    rc = fma(fma(-a[c], rc, 1.0), rc, rc);
+    rc = fma(fma(-a[c], rc, 1.0), rc, rc);
+    int at = (int)(__ballot(hw == top) >> group) & 255;
+    if (__any((at & (at - 1)) != 0)) {
+      const double w = pos >= c ? v : -1.0;
+      double best = fmax(w, dpp_f64<kXor1>(w));
+      best = fmax(best, dpp_f64<kXor2>(best));
+      best = fmax(best, dpp_f64<kMirror8>(best));
+      int first = w == best ? pos : 99;
+      first = min(first, dpp_i32<kXor1>(first));
+      first = min(first, dpp_i32<kXor2>(first));
+      first = min(first, dpp_i32<kMirror8>(first));
+      at = (int)(__ballot(pos == first) >> group) & 255;
     }
-    if (!(best >= 1e-12)) return false;
+    const int src = group | ((__ffs(at) - 1) & 7);
 #pragma unroll
-    for (int r = c + 1; r < 8; ++r)
-      if (piv == r) {
+    for (int j = c; j < 9; ++j) U[c][j] = __shfl(a[j], src);
+    r[c] = __shfl(rc, src);
+    const int was = __shfl(pos, src);
+    ok = ok && fabs(U[c][c]) >= 1e-12;
+    if (lane == src) pos = c;
+    else if (pos == c) pos = was;
+    const double q = a[c] * r[c];
+    const double f = fma(fma(-U[c][c], q, a[c]), r[c], q);  // a[c] / pivot
+    if (pos > c) {
 #pragma unroll
-        for (int j = c; j < 9; ++j) {
-          const double t = a[c * 9 + j];
-          a[c * 9 + j] = a[r * 9 + j];
-          a[r * 9 + j] = t;
-        }
-      }
-#pragma unroll
-    for (int r = c + 1; r < 8; ++r) {
-      const double f = a[r * 9 + c] / a[c * 9 + c];
-#pragma unroll
-      for (int j = c; j < 9; ++j) a[r * 9 + j] = a[r * 9 + j] - f * a[c * 9 + j];
+      for (int j = c + 1; j < 9; ++j) a[j] = a[j] - f * U[c][j];
     }
   }
 #pragma unroll
   for (int c = 7; c >= 0; --c) {
-    double s = a[c * 9 + 8];
+    double t = U[c][8];
 #pragma unroll
-    for (int j = c + 1; j < 8; ++j) s = s - a[c * 9 + j] * x[j];
-    x[c] = s / a[c * 9 + c];
+    for (int j = c + 1; j < 8; ++j) t = t - U[c][j] * x[j];
+    const double q = t * r[c];
+    x[c] = fma(fma(-U[c][c], q, t), r[c], q);  // t / pivot
   }
-  return true;
+  return ok;
 }
 
-// inlier test |G(s) - t|^2 < eps^2, fixed operation order
+// inlier test |G(s) - t|^2 < eps^2, fixed operation order. Without a plain
+// division (PLAIN false) the quotients come straight from div2's reciprocal,
+// with no branch, so that the tests of several hypotheses overlap: the same
+// decisions for coefficients below kPlainG, since the products of
+// coefficients and integer coordinates then stay in range, and the
+// denominator g6 x + g7 y + 1 is 0 (both forms reject) or at least 2^-54.
+constexpr double kPlainG = 0x1p400;
+
+template <bool PLAIN>
 __device__ inline bool is_inlier(const double* g, int4 m, double eps2) {
   const double sx = (double)m.x, sy = (double)m.y;
   const double den = (g[6] * sx + g[7] * sy) + 1.0;
-  const double gx = ((g[0] * sx + g[1] * sy) + g[2]) / den;
-  const double gy = ((g[3] * sx + g[4] * sy) + g[5]) / den;
+  const double nx = (g[0] * sx + g[1] * sy) + g[2], ny = (g[3] * sx + g[4] * sy) + g[5];
+  double gx, gy;
+  if constexpr (PLAIN) {
+    gx = nx / den;
+    gy = ny / den;
+  } else {
+    recip_quotients(nx, ny, den, gx, gy);
+  }
   const double ex = gx - (double)m.z, ey = gy - (double)m.w;
   const double e2 = ex * ex + ey * ey;
   return e2 < eps2;
+}
+
+// whether the tests of hypothesis g need plain divisions (NaN included)
+__device__ inline bool needs_plain(const double* g) {
+  bool small = true;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) small = small && fabs(g[i]) < kPlainG;
+  return !small;
 }
 
 __device__ inline int4 tile_match(const int32_t* __restrict__ cxy,
@@ -128,438 +187,589 @@ __device__ inline int select_bit(unsigned long long m, int k) {
 }
 
 constexpr int kValidThreads = 256;
-constexpr int kHypThreads = 64;
-// hypotheses per k_test block: 4 on levels of up to kTestSmall tiles (more
-// blocks for the few tiles), 8 above (fewer re-reads of the tiles)
-constexpr int kTestSmall = 2048;
-constexpr int kTestThreads = 256;
-constexpr int kUnionThreads = 512;
+constexpr int kFitThreads = 512;
+constexpr int kFitOne = 32;       // levels of up to this many words: one k_fit block
 constexpr int kMaxIters = 65536;  // the parameter check's bound on weed_iters
 constexpr int kMaxWords = 2304;   // tile bitmask words: (6144 / 16)^2 tiles
 
-// word wi of vb = valid-match bits of tiles 64 wi .. 64 wi + 63; block 0
-// also clears the level's least-squares sums
+// word wi of vb = valid-match bits of tiles 64 wi .. 64 wi + 63
 __global__ __launch_bounds__(kValidThreads) void k_valid(const uint8_t* __restrict__ flags,
                                                          int ntiles, int nwords,
-                                                         unsigned long long* __restrict__ vb,
-                                                         long long* __restrict__ sums) {
+                                                         unsigned long long* __restrict__ vb) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wi = blockIdx.x * (kValidThreads / 64) + (tid >> 6);
-  if (blockIdx.x == 0 && tid < 24) sums[tid] = 0;
   if (wi >= nwords) return;  // whole waves
   const int t = wi * 64 + lane;
   const unsigned long long m = __ballot(t < ntiles && (flags[t] & 2));
   if (lane == 0) vb[wi] = m;
 }
 
+// Orders the LDS accesses of one wave's lanes (they execute in order).
+__device__ inline void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// inclusive sums over the wave's lanes
+__device__ inline int wave_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// F(v, v of an earlier lane) folded over the wave on the vector ALU; the
+// total in every lane (0 is F's neutral value)
+template <typename F>
+__device__ inline unsigned long long wave_fold_u64(unsigned long long v, F&& f) {
+#define LNR_FOLD(CTRL, ROWS)                                                                    \
+  v = f(v, ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(                          \
+                0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false)                            \
+            << 32) |                                                                            \
+               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false))
+  LNR_FOLD(0x111, 0xf);  // row_shr 1, 2, 4, 8
+  LNR_FOLD(0x112, 0xf);
+  LNR_FOLD(0x114, 0xf);
+  LNR_FOLD(0x118, 0xf);
+  LNR_FOLD(0x142, 0xa);  // row_bcast 15, 31
+  LNR_FOLD(0x143, 0xc);
+#undef LNR_FOLD
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ inline unsigned long long wave_max_u64(unsigned long long v) {
+  return wave_fold_u64(v, [](unsigned long long p, unsigned long long q) { return q > p ? q : p; });
+}
+__device__ inline unsigned long long wave_or_u64(unsigned long long v) {
+  return wave_fold_u64(v, [](unsigned long long p, unsigned long long q) { return p | q; });
+}
+
+// dynamic LDS of k_hyp: the words, the union and the inlier bits of IPB
+// hypotheses (8 bytes a word each), then the prefix counts
+inline size_t hyp_lds(int words, int ipb) {
+  return (size_t)words * 8 * (2 + ipb) + ((size_t)words + 1) * 4;
+}
+
 // The kernels below take one level of one pair (JOBS false: the job is the
 // kernel argument) or a table of jobs, one per blockIdx.z (batches).
-template <bool JOBS>
-__global__ __launch_bounds__(kHypThreads) void k_hyp(WeedJob one,
-                                                     const WeedJob* __restrict__ jobs,
-                                                     WeedArgs a) {
+//
+// Hypotheses per k_hyp block and its threads: a pair's levels of more than
+// 256 tiles take four per 512 threads (every CU a block at the default 1024
+// iterations, half the tests per wave); the smallest levels, and batches,
+// whose jobs fill the chip anyway, eight (a full wave of eight-lane solves)
+// per 256.
+inline bool hyp_wide(int ntiles, int njobs) { return ntiles > 256 && njobs < 4; }
+
+// A coarse level (15 to 1200 tiles) is bound by the first wave's instruction
+// count, one every four or five cycles: eight-lane solves, draws in parallel,
+// tests without branches. 8.0 us at 300 tiles and 9 at 15; one system per
+// lane and a launch of its own for the tests took 8.6 + 4.2 us. At 4860
+// tiles the tests are the work: 17 us against 9.2 + 12.8.
+template <bool JOBS, int IPB, int NT>
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, const WeedJob* __restrict__ jobs,
+                                            WeedArgs a) {
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
   const unsigned long long* __restrict__ vbg = J.b.vb;
   const int32_t* __restrict__ cxy = J.cxy;
   const int32_t* __restrict__ disp = J.disp;
-  const int nwords = J.words, w = J.w, h = J.h;
-  double* __restrict__ G = J.b.G;
-  int32_t* __restrict__ cnt = J.b.cnt;
-  int32_t* __restrict__ nmatch = J.b.nmatch;
-  __shared__ unsigned long long vb[kMaxWords];  // valid-tile bits, tile order
-  __shared__ int wpre[kMaxWords + 1];            // valid tiles before each word
-  const int lane = threadIdx.x;
-  for (int q0 = 0; q0 < nwords; q0 += 8 * 64) {
-    unsigned long long r[8];  // eight loads in flight per lane
+  const int nwords = J.words, ntiles = J.ntiles;
+  const int ox = J.w / 2, oy = J.h / 2;
+  constexpr int NW = NT / 64;
+  extern __shared__ __align__(16) unsigned long long dyn[];
+  unsigned long long* vb = dyn;                    // valid-tile bits, tile order
+  unsigned long long* uni = vb + nwords;           // union of the accepted inliers
+  unsigned long long* inl = uni + nwords;          // [nwords][IPB] inlier bits
+  int* wpre = reinterpret_cast<int*>(inl + (size_t)nwords * IPB);  // valid tiles before a word
+  __shared__ __align__(16) double gs[IPB][8];
+  __shared__ int usable[IPB];   // 0: no, 1: yes, 2: yes, tested with plain divisions
+  __shared__ int wc[IPB][NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // this thread's first tile, in flight with the words
+  int4 mine = make_int4(0, 0, 0, 0);
+  if (ntiles > 0) mine = tile_match(cxy, disp, min(tid, ntiles - 1), ox, oy);
+  // The first wave prepares, solves and counts by itself; the others only
+  // test, between the two barriers of a group.
+  int N = 0, delta = 0;           // first wave
+  unsigned long long best = 0ull;  // this block's best key (first wave)
+  double bg = 0.0;                 // its coefficient `lane` (lanes 0..7)
+  const unsigned long long seed = a.seed ^ ((unsigned long long)(uint32_t)a.level << 56);
+  if (wave == 0) {
+    // exclusive prefix of the words' popcounts
+    int incl;
+    if (nwords <= 64) {
+      const unsigned long long v = lane < nwords ? vbg[lane] : 0ull;
+      const int c = __popcll(v);
+      incl = wave_scan_i32(c);
+      if (lane < nwords) {
+        vb[lane] = v;
+        uni[lane] = 0ull;
+        wpre[lane] = incl - c;
+      }
+    } else {
+      for (int q0 = 0; q0 < nwords; q0 += 8 * 64) {
+        unsigned long long r[8];  // eight loads in flight per lane
 #pragma unroll
-    for (int u = 0; u < 8; ++u) r[u] = vbg[min(q0 + u * 64 + lane, nwords - 1)];
+        for (int u = 0; u < 8; ++u) r[u] = vbg[min(q0 + u * 64 + lane, nwords - 1)];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int wi = q0 + u * 64 + lane;
-      if (wi < nwords) vb[wi] = r[u];
+        for (int u = 0; u < 8; ++u) {
+          const int wi = q0 + u * 64 + lane;
+          if (wi < nwords) {
+            vb[wi] = r[u];
+            uni[wi] = 0ull;
+          }
+        }
+      }
+      wave_lds_order();
+      const int K = (nwords + 63) / 64;  // lane owns a run of K words
+      int c = 0;
+      for (int j = 0; j < K; ++j) {
+        const int wi = lane * K + j;
+        if (wi < nwords) c += __popcll(vb[wi]);
+      }
+      incl = wave_scan_i32(c);
+      int run = incl - c;
+      for (int j = 0; j < K; ++j) {
+        const int wi = lane * K + j;
+        if (wi < nwords) {
+          wpre[wi] = run;
+          run += __popcll(vb[wi]);
+        }
+      }
     }
+    wave_lds_order();
+    N = __builtin_amdgcn_readlane(incl, 63);
+    delta = weed_delta(N, a);
+    if (blockIdx.x == 0 && lane == 0) *J.b.nmatch = N;
   }
-  __syncthreads();
-  // exclusive prefix of the words' popcounts: lane owns a run of K words
-  const int K = (nwords + 63) / 64;
-  int c = 0;
-  for (int j = 0; j < K; ++j) {
-    const int wi = lane * K + j;
-    if (wi < nwords) c += __popcll(vb[wi]);
-  }
-  int incl = c;
+  const int groups = (a.iters + IPB - 1) / IPB;
+  for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    const int it0 = grp * IPB;
+    if (wave == 0) {
+      // eight lanes per hypothesis: each draws one index of the first eight
+      // and sets up row (lane & 7) of the system, the x or y equation of
+      // match row / 2
+      const int q = min(lane >> 3, IPB - 1), row = lane & 7;
+      const int it = it0 + q;
+      const unsigned long long base = seed + (unsigned long long)it * 16ull;
+      auto draw = [&](int t) {
+        return (int)__umulhi((uint32_t)(splitmix64(base + (unsigned long long)t) >> 32),
+                             (uint32_t)N);
+      };
+      const int own = draw(row);
+      int pk[4];
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
-  const int N = __shfl(incl, 63);
-  int run = incl - c;
-  for (int j = 0; j < K; ++j) {
-    const int wi = lane * K + j;
-    if (wi < nwords) {
-      wpre[wi] = run;
-      run += __popcll(vb[wi]);
-    }
-  }
-  if (lane == 0) wpre[nwords] = N;
-  __syncthreads();
-  if (blockIdx.x == 0 && lane == 0) *nmatch = N;
-  const int it = blockIdx.x * kHypThreads + lane;
-  bool ok = N >= 4 && it < a.iters;
-  int pk[4] = {-1, -1, -1, -1};
-  if (ok) {
-    const unsigned long long base = a.seed ^ ((unsigned long long)(uint32_t)a.level << 56);
-    int np = 0;
-    for (int t = 0; t < 16 && np < 4; ++t) {
-      const unsigned long long u =
-          splitmix64(base + (unsigned long long)it * 16ull + (unsigned long long)t);
-      const int id = (int)(((u >> 32) * (unsigned long long)N) >> 32);
-      if (id == pk[0] || id == pk[1] || id == pk[2]) continue;  // a repeat: draw again
-      if (np == 0) pk[0] = id;
-      else if (np == 1) pk[1] = id;
-      else if (np == 2) pk[2] = id;
-      else pk[3] = id;
-      ++np;
-    }
-    ok = np == 4;
-  }
-  if (ok) {
-    const int ox = w / 2, oy = h / 2;
-    double A[72];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
+      for (int t = 0; t < 4; ++t) pk[t] = __shfl(own, (lane & 56) + t);
+      int np = 4;
+      if (__any(pk[1] == pk[0] || pk[2] == pk[0] || pk[2] == pk[1] || pk[3] == pk[0] ||
+                pk[3] == pk[1] || pk[3] == pk[2])) {
+        // a repeat is drawn again: the first four distinct of sixteen draws
+        pk[0] = pk[1] = pk[2] = pk[3] = -1;
+        np = 0;
+        for (int t = 0; t < 16; ++t) {
+          const int id = t < 8 ? __shfl(own, (lane & 56) + t) : draw(t);
+          const bool take = np < 4 && id != pk[0] && id != pk[1] && id != pk[2];
+          if (take && np == 0) pk[0] = id;
+          if (take && np == 1) pk[1] = id;
+          if (take && np == 2) pk[2] = id;
+          if (take && np == 3) pk[3] = id;
+          np += take;
+          if (t >= 7 && __all(np == 4)) break;
+        }
+      }
+      bool good = N >= 4 && np == 4 && it < a.iters;
       // match index -> tile: last word with wpre <= id, then the bit within it
-      const int id = pk[q];
+      const int m = row >> 1;
+      const int id = max(m == 0 ? pk[0] : m == 1 ? pk[1] : m == 2 ? pk[2] : pk[3], 0);
       int lo = 0, hi = nwords - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (wpre[mid] <= id) lo = mid;
         else hi = mid - 1;
       }
-      const int tq = lo * 64 + select_bit(vb[lo], id - wpre[lo]);
-      const int4 m = tile_match(cxy, disp, tq, ox, oy);
-      const double sx = (double)m.x, sy = (double)m.y, tx = (double)m.z, ty = (double)m.w;
-      double* r0 = A + (2 * q) * 9;
-      double* r1 = A + (2 * q + 1) * 9;
-      r0[0] = sx; r0[1] = sy; r0[2] = 1; r0[3] = 0; r0[4] = 0; r0[5] = 0;
-      r0[6] = -(sx * tx); r0[7] = -(sy * tx); r0[8] = tx;
-      r1[0] = 0; r1[1] = 0; r1[2] = 0; r1[3] = sx; r1[4] = sy; r1[5] = 1;
-      r1[6] = -(sx * ty); r1[7] = -(sy * ty); r1[8] = ty;
-    }
-    double g[8];
-    ok = solve8(A, g);
-    if (ok)
-      for (int i = 0; i < 8; ++i) G[(size_t)it * 8 + i] = g[i];
-  }
-  // k_test adds each tile chunk's inliers; -1: too few matches, degenerate draw or fit
-  if (it < a.iters) cnt[it] = ok ? 0 : -1;
-}
-
-// Tile chunk blockIdx.x x iteration group blockIdx.y: adds the chunk's inlier
-// counts to cnt[iter] and stores the inlier bits in bal[word][iter]
-// (word-major, so that the union reads each word's rows contiguously).
-template <bool JOBS, int IPB>
-__global__ __launch_bounds__(kTestThreads) void k_test(WeedJob one,
-                                                       const WeedJob* __restrict__ jobs,
-                                                       WeedArgs a) {
-  const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
-  const int ntiles = J.ntiles, w = J.w, h = J.h, wstride = J.words;
-  if (JOBS && (int)blockIdx.x * kTestThreads >= ntiles) return;  // past this job's tiles
-  const int32_t* __restrict__ cxy = J.cxy;
-  const int32_t* __restrict__ disp = J.disp;
-  const uint8_t* __restrict__ flags = J.flags;
-  const double* __restrict__ G = J.b.G;
-  int32_t* __restrict__ cnt = J.b.cnt;
-  unsigned long long* __restrict__ bal = J.b.bal;
-  __shared__ double gs[IPB][8];
-  __shared__ int ok[IPB];
-  __shared__ int wc[IPB][kTestThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int it0 = blockIdx.y * IPB;
-  // the tile, the hypotheses and their usability are loaded together
-  const int t = blockIdx.x * kTestThreads + tid;
-  const int tc = t < ntiles ? t : ntiles - 1;  // ntiles >= 1 here
-  const uint8_t tf = flags[tc];
-  const int4 mt = tile_match(cxy, disp, tc, w / 2, h / 2);
-  if (tid < 8 * IPB) {  // one coefficient per thread
-    const int it = min(it0 + (tid >> 3), a.iters - 1);
-    gs[tid >> 3][tid & 7] = G[(size_t)it * 8 + (tid & 7)];
-  }
-  if (tid < IPB) {
-    const int it = it0 + tid;
-    // usable hypotheses start at 0 and only grow, so the sign is stable
-    ok[tid] = it < a.iters && __atomic_load_n(&cnt[min(it, a.iters - 1)], __ATOMIC_RELAXED) >= 0;
-  }
-  __syncthreads();
-  const bool valid = t < ntiles && (tf & 2);
-  const int4 m = valid ? mt : make_int4(0, 0, 0, 0);
-  const int word = t >> 6;
-  for (int q = 0; q < IPB; ++q) {
-    if (!ok[q]) continue;
-    const bool in = valid && is_inlier(gs[q], m, a.eps2);
-    const unsigned long long b = __ballot(in);
-    if (lane == 0) {
-      if (word < wstride) bal[(size_t)word * a.iters + it0 + q] = b;
-      wc[q][wave] = __popcll(b);
-    }
-  }
-  __syncthreads();
-  if (tid < IPB && ok[tid]) {
-    int s = 0;
-    for (int q = 0; q < kTestThreads / 64; ++q) s += wc[tid][q];
-    if (s) atomicAdd(&cnt[it0 + tid], s);
-  }
-}
-
-__device__ inline long long wave_sum_i64(long long v) {
+      const int tq = max(min(lo * 64 + select_bit(vb[lo], id - wpre[lo]), ntiles - 1), 0);
+      int4 mt = make_int4(0, 0, 0, 0);
+      if (ntiles > 0) mt = tile_match(cxy, disp, tq, ox, oy);
+      const double sx = (double)mt.x, sy = (double)mt.y;
+      const bool yrow = row & 1;
+      const double tt = yrow ? (double)mt.w : (double)mt.z;
+      double A[9] = {yrow ? 0.0 : sx, yrow ? 0.0 : sy, yrow ? 0.0 : 1.0,
+                     yrow ? sx : 0.0, yrow ? sy : 0.0, yrow ? 1.0 : 0.0,
+                     -(sx * tt),      -(sy * tt),      tt};
+      double g[8];
+      const bool solved = solve8_rows(A, g);
+      good = good && solved;
+      if (row == 0 && (lane >> 3) < IPB) {
+        // not usable: too few matches, degenerate draw or fit
+        usable[q] = good ? (needs_plain(g) ? 2 : 1) : 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-__device__ inline unsigned long long wave_max_u64(unsigned long long v) {
+        for (int i = 0; i < 8; ++i) gs[q][i] = g[i];
+      }
+    }
+    __syncthreads();
+    // every tile against the group's hypotheses
+    bool plain = false;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long u = __shfl_xor(v, o);
-    v = u > v ? u : v;
+    for (int q = 0; q < IPB; ++q) plain = plain || usable[q] == 2;
+    int cnt = 0;  // lane q: hypothesis q
+    for (int t0 = 0; t0 < nwords * 64; t0 += NT) {
+      const int t = t0 + tid, word = t >> 6;
+      if (word >= nwords) break;  // whole waves
+      const bool valid = (vb[word] >> lane) & 1ull;
+      const int4 m = t0 == 0 ? mine : tile_match(cxy, disp, min(t, ntiles - 1), ox, oy);
+      unsigned long long keep = 0ull;
+#pragma unroll 4
+      for (int q = 0; q < IPB; ++q) {
+        const unsigned long long b = __ballot(valid && is_inlier<false>(gs[q], m, a.eps2));
+        if (lane == q) keep = b;
+      }
+      if (plain)
+        for (int q = 0; q < IPB; ++q) {
+          if (usable[q] != 2) continue;
+          const unsigned long long b = __ballot(valid && is_inlier<true>(gs[q], m, a.eps2));
+          if (lane == q) keep = b;
+        }
+      cnt += __popcll(keep);
+      if (lane < IPB) inl[(size_t)word * IPB + lane] = keep;
+    }
+    if (lane < IPB) wc[lane][wave] = cnt;
+    __syncthreads();
+    if (wave == 0) {
+      // lane q counts hypothesis q
+      int c = 0;
+      unsigned long long key = 0ull;
+      if (lane < IPB && usable[lane]) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) c += wc[lane][w];
+        key = ((unsigned long long)(uint32_t)c << 32) |
+              (unsigned long long)(~(uint32_t)(it0 + lane));
+      }
+      const unsigned int acc = (unsigned int)__ballot(c > delta);  // accepted
+      const unsigned long long top = wave_max_u64(key);
+      if (top > best) {
+        best = top;
+        const int q = (int)(~(uint32_t)top) - it0;
+        if (lane < 8) bg = gs[q][lane];
+      }
+      if (acc)
+        for (int w = lane; w < nwords; w += 64) {
+          unsigned long long v = uni[w];
+          for (unsigned int r = acc; r; r &= r - 1)
+            v |= inl[(size_t)w * IPB + __builtin_ctz(r)];
+          uni[w] = v;
+        }
+    }
   }
-  return v;
+  if (wave != 0) return;
+  if (lane < 8) J.b.G[(size_t)blockIdx.x * 8 + lane] = bg;
+  if (lane == 0) J.b.key[blockIdx.x] = best;
+  if ((int)(best >> 32) > delta)  // an accepted hypothesis: k_fit reads them
+    for (int w = lane; w < nwords; w += 64)
+      J.b.part[(size_t)w * gridDim.x + blockIdx.x] = uni[w];
 }
 
-// distinct sums of the normal equations (see k_fit)
-constexpr int kSums = 23;
+// distinct sums of the normal equations (order: 1, x, y, xx, xy, yy, u, v,
+// xu, yu, xv, yv, xxu, xyu, yyu, xxv, xyv, yyv, xq, yq, xxq, xyq, yyq with
+// q = u^2 + v^2), and a zero
+constexpr int kSums = 24;
+
+// The terms of degree two and more of one match, products of two in type T.
+template <typename T>
+__device__ inline void add_terms(long long (&s)[kSums], T x, T y, T u, T v) {
+  const T xx = x * x, xy = x * y, yy = y * y, q = u * u + v * v;
+  auto mad = [](long long& acc, T p, T r) { acc += (long long)p * (long long)r; };
+  s[3] += xx; s[4] += xy; s[5] += yy;
+  mad(s[8], x, u);   mad(s[9], y, u);   mad(s[10], x, v);  mad(s[11], y, v);
+  mad(s[12], xx, u); mad(s[13], xy, u); mad(s[14], yy, u);
+  mad(s[15], xx, v); mad(s[16], xy, v); mad(s[17], yy, v);
+  mad(s[18], x, q);  mad(s[19], y, q);
+  mad(s[20], xx, q); mad(s[21], xy, q); mad(s[22], yy, q);
+}
+
+// One step of summing N values over the wave: the lanes' halves (bit OFF)
+// keep half of the values each. Returns the values left per lane.
+template <int OFF, int N>
+__device__ inline void halve_sums(long long (&s)[kSums]) {
+  constexpr int H = (N + 1) / 2;
+  const bool hi = (threadIdx.x & OFF) != 0;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const long long up = i + H < N ? s[i + H] : 0;
+    const long long keep = hi ? up : s[i], give = hi ? s[i] : up;
+    s[i] = keep + __shfl_xor(give, OFF);
+  }
+}
+
+// The wave's totals of s[0, 24) into out[24] (exact int64, order-free): 25
+// exchanges of one value instead of 6 for each of the 24.
+__device__ inline void wave_sums(long long (&s)[kSums], long long* out) {
+  halve_sums<32, 24>(s);
+  halve_sums<16, 12>(s);
+  halve_sums<8, 6>(s);
+  halve_sums<4, 3>(s);
+  halve_sums<2, 2>(s);
+  s[0] += __shfl_xor(s[0], 1);
+  const int l = threadIdx.x;
+  const int k = (l & 4 ? 2 : 0) + (l & 2 ? 1 : 0);
+  if (!(l & 1) && k < 3) out[(l & 32 ? 12 : 0) + (l & 16 ? 6 : 0) + (l & 8 ? 3 : 0) + k] = s[0];
+}
 
 // polynomial degree of unknown i (h11 h12 h13 h21 h22 h23 h31 h32) in the
 // coordinates, for the power-of-two scaling
 __device__ inline int deg_of(int i) { return (i == 2 || i == 5) ? 0 : (i >= 6 ? 2 : 1); }
 
-// Entry (i, j) of A^T A from the 23 sums T (order: 1, x, y, xx, xy, yy, u, v,
-// xu, yu, xv, yv, xxu, xyu, yyu, xxv, xyv, yyv, xq, yq, xxq, xyq, yyq with
-// q = u^2 + v^2).
-__device__ inline long long normal_entry(const long long* T, int i, int j) {
-  if (i > j) { const int t = i; i = j; j = t; }
-  switch (i * 8 + j) {
-    case 0: return T[3];   case 1: return T[4];   case 2: return T[1];
-    case 6: return -T[12]; case 7: return -T[13];
-    case 9: return T[5];   case 10: return T[2];  case 14: return -T[13]; case 15: return -T[14];
-    case 18: return T[0];  case 22: return -T[8]; case 23: return -T[9];
-    case 27: return T[3];  case 28: return T[4];  case 29: return T[1];
-    case 30: return -T[15]; case 31: return -T[16];
-    case 36: return T[5];  case 37: return T[2];  case 38: return -T[16]; case 39: return -T[17];
-    case 45: return T[0];  case 46: return -T[10]; case 47: return -T[11];
-    case 54: return T[20]; case 55: return T[21];
-    case 63: return T[22];
-    default: return 0;
+// Row r of the normal equations A^T A | A^T b of the rows
+// (x, y, 1, 0, 0, 0, -xu, -yu | u) and (0, 0, 0, x, y, 1, -xv, -yv | v) as
+// codes of six bits from entry 0 up: the sum's index, plus 32 where negated
+// (23: the zero).
+constexpr unsigned long long row_code(const int (&e)[9]) {
+  unsigned long long c = 0ull;
+  for (int j = 0; j < 9; ++j) c |= (unsigned long long)e[j] << (6 * j);
+  return c;
+}
+constexpr int kZ = 23, kM = 32;
+constexpr int kRow[8][9] = {
+    {3, 4, 1, kZ, kZ, kZ, kM + 12, kM + 13, 8},
+    {4, 5, 2, kZ, kZ, kZ, kM + 13, kM + 14, 9},
+    {1, 2, 0, kZ, kZ, kZ, kM + 8, kM + 9, 6},
+    {kZ, kZ, kZ, 3, 4, 1, kM + 15, kM + 16, 10},
+    {kZ, kZ, kZ, 4, 5, 2, kM + 16, kM + 17, 11},
+    {kZ, kZ, kZ, 1, 2, 0, kM + 10, kM + 11, 7},
+    {kM + 12, kM + 13, kM + 8, kM + 15, kM + 16, kM + 10, 20, 21, kM + 18},
+    {kM + 13, kM + 14, kM + 9, kM + 16, kM + 17, kM + 11, 21, 22, kM + 19}};
+constexpr unsigned long long kCode[8] = {row_code(kRow[0]), row_code(kRow[1]), row_code(kRow[2]),
+                                         row_code(kRow[3]), row_code(kRow[4]), row_code(kRow[5]),
+                                         row_code(kRow[6]), row_code(kRow[7])};
+
+// The level fit from the sums (LDS: tot as doubles, msel of them), by the
+// first wave of a block, then H_l = Hbase o G with Hbase = H_{l+1} (matches
+// relative to the warped source) or the identity (absolute matches);
+// H_l = H_{l+1} when fewer than 4 matches were fitted or the solve fails.
+// A lane per row of the system, then a lane per entry of the product: lane
+// 3 i + j holds Hprev[i][j] in hp and row i of Hbase in hb.
+__device__ inline void solve_level(const WeedJob& J, const double* tot, int msel, double hp,
+                                   const double (&hb)[3]) {
+  const int w = J.w, h = J.h, lane = threadIdx.x & 63, row = lane & 7;
+  const int ox = w / 2, oy = h / 2;
+  const int mx = max(max(ox, oy), 1);
+  const int k = mx > 1 ? 32 - __clz(mx - 1) : 0;  // 2^k >= mx
+  unsigned long long code = kCode[0];
+#pragma unroll
+  for (int r = 1; r < 8; ++r) code = row == r ? kCode[r] : code;
+  const int dr = -k * deg_of(row);
+  double A[9];
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    const int e = (int)(code >> (6 * j)) & 63;
+    const double v = tot[e & 31];
+    A[j] = ldexp(e & 32 ? -v : v, dr - k * (j < 8 ? deg_of(j) : 1));
   }
+  double hs[8];
+  const bool ok = solve8_rows(A, hs);
+  double G[9];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) G[i] = ldexp(hs[i], k * (1 - deg_of(i)));
+  G[8] = 1.0;
+  // H = Hbase ((P G) Q), every entry's sum left to right as mat3_mul forms it
+  const double pox = (double)(2 * ox - (w - 1)), poy = (double)(2 * oy - (h - 1));
+  const double Pm[9] = {2, 0, pox, 0, 2, poy, 0, 0, (double)w};
+  double T[9];
+  mat3_mul(Pm, G, T);
+  const int j = min(lane, 8) % 3;
+  const double q0 = j == 0 ? (double)w : j == 2 ? -pox : 0.0;
+  const double q1 = j == 1 ? (double)w : j == 2 ? -poy : 0.0;
+  const double q2 = j == 2 ? 2.0 : 0.0;
+  double c[3];  // column j of (P G) Q
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    c[m] = T[3 * m] * q0;
+    c[m] = c[m] + T[3 * m + 1] * q1;
+    c[m] = c[m] + T[3 * m + 2] * q2;
+  }
+  double t = hb[0] * c[0];
+  t = t + hb[1] * c[1];
+  t = t + hb[2] * c[2];
+  const double d = __shfl(t, 8);
+  const double hn = t / d;
+  const bool take = msel >= 4 && ok && d != 0.0 && !__any(lane < 9 && !isfinite(hn));
+  if (lane < 9) J.Hout[lane] = take ? hn : hp;
+  if (lane == 0) J.counts[1] = msel;
 }
 
-// Entry i of A^T b
-__device__ inline long long normal_rhs(const long long* T, int i) {
-  switch (i) {
-    case 0: return T[8];  case 1: return T[9];  case 2: return T[6];  case 3: return T[10];
-    case 4: return T[11]; case 5: return T[7];  case 6: return -T[18];
-    default: return -T[19];
-  }
-}
-
-// Wave wd of the grid owns tile word wd: union M over the accepted rows,
-// flags 4 (in M) and 8 (in the fit) of its tiles, and their least-squares
-// terms, added exactly to the level's sums.
+// Block x owns tile words [x wpb, (x + 1) wpb): the union M over the blocks
+// of k_hyp (hypothesis groups of ipb iterations), flags 4 (in M) and 8 (in
+// the fit) of its tiles and their least-squares terms; the level's only block
+// then solves, several leave their sums to k_solve. One block is enough for
+// kFitOne words (2048 tiles, four per thread); beyond, its one CU is the
+// limit (4860 tiles: 20 us in one block, 7.5 us in five and 5.6 for k_solve).
+// 7.6 us at 300 tiles, where a union over all the iterations' inlier rows and
+// a one-lane solve in a launch of its own took 10.1 + 6.6.
 template <bool JOBS>
-__global__ __launch_bounds__(kUnionThreads) void k_union(WeedJob one,
-                                                         const WeedJob* __restrict__ jobs,
-                                                         WeedArgs a) {
+__global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
+                                                     const WeedJob* __restrict__ jobs,
+                                                     WeedArgs a, int ipb, int nhyp, int wpb) {
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
-  const int ntiles = J.ntiles, w = J.w, h = J.h, wstride = J.words;
-  if (JOBS && (int)blockIdx.x * (kUnionThreads / 64) >= wstride) return;  // past its words
+  const int ntiles = J.ntiles, words = J.words;
+  const int w0 = blockIdx.x * wpb, w1 = min(words, w0 + wpb);
+  if (blockIdx.x > 0 && w0 >= words) return;  // past this job's words
   const int32_t* __restrict__ cxy = J.cxy;
   const int32_t* __restrict__ disp = J.disp;
   uint8_t* __restrict__ flags = J.flags;
-  const int32_t* __restrict__ nmatch = J.b.nmatch;
-  const int32_t* __restrict__ cnt = J.b.cnt;
-  const unsigned long long* __restrict__ bal = J.b.bal;
-  long long* __restrict__ sums = J.b.sums;
-  int32_t* __restrict__ counts = J.counts;
-  __shared__ unsigned int accw[kMaxIters / 32];  // accepted iterations
-  __shared__ unsigned long long kmax[kUnionThreads / 64];
-  __shared__ long long part[kUnionThreads / 64][kSums];
-  constexpr int NWV = kUnionThreads / 64;
+  constexpr int NW = kFitThreads / 64;
+  __shared__ __align__(16) double Gs[kWeedBlocks * 8];
+  __shared__ unsigned long long M[kFitOne];
+  __shared__ long long part[NW][kSums];
+  __shared__ double tot[kSums];
+  __shared__ int msel;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wd = blockIdx.x * NWV + wave;
-  const int t = wd * 64 + lane;
-  const bool in = wd < wstride && t < ntiles;
-  // this lane's tile, in flight with the counts
-  const uint8_t tf = in ? flags[t] : 0;
-  const int tpx = in ? cxy[2 * t] : 0, tpy = in ? cxy[2 * t + 1] : 0;
-  const int tdx = in ? disp[2 * t] : 0, tdy = in ? disp[2 * t + 1] : 0;
-  const int N = *nmatch;
-  const int delta = weed_delta(N, a);
-  // per-iteration counts -> acceptance bits and the best key
-  unsigned long long kb = 0ull;
-  for (int i0 = 0; i0 < a.iters; i0 += 2 * kUnionThreads) {
-    int c[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {  // loads in flight with the match count
-      const int i = i0 + r * kUnionThreads + tid;
-      c[r] = cnt[min(i, a.iters - 1)];
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int i = i0 + r * kUnionThreads + tid;
-      if (i >= a.iters || N < 4) c[r] = -1;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int i = i0 + r * kUnionThreads + tid;
-      const int ib = i0 + r * kUnionThreads + wave * 64;
-      const unsigned long long acc = __ballot(c[r] > delta);
-      if (lane == 0 && ib < a.iters) {
-        accw[ib >> 5] = (unsigned int)acc;
-        accw[(ib >> 5) + 1] = (unsigned int)(acc >> 32);
-      }
-      if (c[r] >= 0) {
-        const unsigned long long key =
-            ((unsigned long long)(uint32_t)c[r] << 32) | (unsigned long long)(~(uint32_t)i);
-        kb = key > kb ? key : kb;
-      }
-    }
+  const int ox = J.w / 2, oy = J.h / 2;
+  // everything that does not depend on the keys is in flight with them: this
+  // thread's first tile, the best hypotheses, the unions' first words
+  const int tc0 = min(w0 * 64 + tid, max(ntiles - 1, 0));
+  uint8_t f0 = 0;
+  int4 m0 = make_int4(0, 0, 0, 0);
+  if (ntiles > 0) {
+    f0 = flags[tc0];
+    m0 = tile_match(cxy, disp, tc0, ox, oy);
   }
-  kb = wave_max_u64(kb);
-  if (lane == 0) kmax[wave] = kb;
-  __syncthreads();
-  unsigned long long bkey = 0ull;
-  for (int q = 0; q < NWV; ++q) bkey = kmax[q] > bkey ? kmax[q] : bkey;
-  const int bc = N >= 4 && bkey ? (int)(bkey >> 32) : -1;
-  const int bi = N >= 4 && bkey ? (int)(~(uint32_t)(bkey & 0xffffffffull)) : -1;
+  const int N = *J.b.nmatch;
+  constexpr int NK = kWeedBlocks / 64;  // hypothesis blocks per lane
+  static_assert(kWeedBlocks * 8 == 4 * kFitThreads, "four coefficients per thread");
+  unsigned long long key[NK];
+#pragma unroll
+  for (int u = 0; u < NK; ++u) {
+    const int b = lane + 64 * u;
+    key[u] = J.b.key[min(b, nhyp - 1)];
+    if (b >= nhyp) key[u] = 0ull;
+  }
+  double gr[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) gr[u] = J.b.G[min(tid + u * kFitThreads, nhyp * 8 - 1)];
+  // word wd's unions, a block per lane
+  unsigned long long pr[NK];
+  auto fetch = [&](int wd) {
+    const unsigned long long* p = J.b.part + (size_t)wd * nhyp;
+#pragma unroll
+    for (int u = 0; u < NK; ++u) pr[u] = p[min(lane + 64 * u, nhyp - 1)];
+  };
+  if (w0 + wave < w1) fetch(w0 + wave);
+  double hp = 0.0, hb[3] = {0.0, 0.0, 0.0};
+  if (wave == 0) {
+    const int e = min(lane, 8);
+    hp = J.Hprev[e];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) hb[i] = J.Hbase[e / 3 * 3 + i];
+  }
+  const int delta = weed_delta(N, a);
+  unsigned long long bkey = key[0];
+#pragma unroll
+  for (int u = 1; u < NK; ++u) bkey = key[u] > bkey ? key[u] : bkey;
+  bkey = wave_max_u64(bkey);
+  const int bc = bkey ? (int)(bkey >> 32) : -1;
+  const int bi = bkey ? (int)(~(uint32_t)(bkey & 0xffffffffull)) : -1;
+  const int bb = bkey ? bi / ipb % nhyp : 0;  // the block that solved iteration bi
   const bool fit = bc > delta;
   if (blockIdx.x == 0 && tid == 0) {
-    counts[0] = N;
-    counts[2] = bc;
-    counts[3] = bi;
+    J.counts[0] = N;
+    J.counts[2] = bc;
+    J.counts[3] = bi;
   }
+  // M, a wave per word: the union over the blocks with an accepted hypothesis
+  for (int wd = w0 + wave; wd < w1; wd += NW) {
+    unsigned long long v = 0ull;
+#pragma unroll
+    for (int u = 0; u < NK; ++u)
+      if ((int)(key[u] >> 32) > delta) v |= pr[u];
+    if (wd + NW < w1) fetch(wd + NW);
+    v = wave_or_u64(v);
+    if (lane == 0) M[wd - w0] = v;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) Gs[tid + u * kFitThreads] = gr[u];
+  __syncthreads();
+  double g[8];  // the best hypothesis
+#pragma unroll
+  for (int i = 0; i < 8; ++i) g[i] = Gs[bb * 8 + i];
+  const bool plain = needs_plain(g);
   long long s[kSums];
 #pragma unroll
   for (int i = 0; i < kSums; ++i) s[i] = 0;
-  if (wd < wstride) {  // whole waves
-    const unsigned long long brow = fit ? bal[(size_t)wd * a.iters + bi] : 0ull;
-    unsigned long long v = 0ull;
-    for (int i0 = 0; i0 < a.iters; i0 += 64 * 16) {
-      unsigned long long r[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int i = i0 + u * 64 + lane;
-        r[u] = bal[(size_t)wd * a.iters + min(i, a.iters - 1)];  // used only if i < iters
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int i = i0 + u * 64 + lane;
-        if (i < a.iters && ((accw[i >> 5] >> (i & 31)) & 1u)) v |= r[u];
-      }
+  for (int t0 = w0 * 64; t0 < w1 * 64; t0 += kFitThreads) {
+    const int t = t0 + tid, word = t >> 6;
+    if (word >= w1) break;  // whole waves
+    const bool first = t0 == w0 * 64;
+    const int tc = max(min(t, ntiles - 1), 0);
+    uint8_t tf = f0;
+    int4 m = m0;
+    if (!first) {
+      tf = flags[tc];
+      m = tile_match(cxy, disp, tc, ox, oy);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o);
-    if (in && (tf & 2)) {
-      const bool inM = (v >> lane) & 1ull;
-      const bool sel = (brow >> lane) & 1ull;
-      flags[t] = (uint8_t)((tf & 0x13) | (inM ? 4 : 0) | (sel ? 8 : 0));
-      if (sel) {
-        // normal equations of G: (x, y) -> (u, v), reference side to source
-        // side; the 8x8 matrix has 23 distinct sums
-        const long long x = tpx - w / 2, y = tpy - h / 2, u = x + tdx, vv = y + tdy;
-        const long long xx = x * x, xy = x * y, yy = y * y, q = u * u + vv * vv;
-        s[0] = 1;        s[1] = x;        s[2] = y;
-        s[3] = xx;       s[4] = xy;       s[5] = yy;
-        s[6] = u;        s[7] = vv;
-        s[8] = x * u;    s[9] = y * u;    s[10] = x * vv;  s[11] = y * vv;
-        s[12] = xx * u;  s[13] = xy * u;  s[14] = yy * u;
-        s[15] = xx * vv; s[16] = xy * vv; s[17] = yy * vv;
-        s[18] = x * q;   s[19] = y * q;
-        s[20] = xx * q;  s[21] = xy * q;  s[22] = yy * q;
+    if (t >= ntiles || !(tf & 2)) continue;
+    const bool inM = (M[word - w0] >> lane) & 1ull;
+    const bool sel = fit && (plain ? is_inlier<true>(g, m, a.eps2)
+                                   : is_inlier<false>(g, m, a.eps2));
+    flags[t] = (uint8_t)((tf & 0x13) | (inM ? 4 : 0) | (sel ? 8 : 0));
+    if (sel) {
+      // normal equations of G: (x, y) -> (u, v), reference side to source side
+      const int x = m.z, y = m.w, u = m.x, v = m.y;
+      s[0] += 1; s[1] += x; s[2] += y; s[6] += u; s[7] += v;
+      if (max(max(abs(x), abs(y)), max(abs(u), abs(v))) <= 32767) {
+        // products of two coordinates (and q) stay below 2^31: 32 x 32 -> 64
+        // bit multiply-adds
+        add_terms<int>(s, x, y, u, v);
+      } else {  // a caller's matches far outside any image
+        add_terms<long long>(s, x, y, u, v);
       }
     }
   }
-  // exact (order-free) int64 reduction
   if (__ballot(s[0] != 0)) {
-#pragma unroll
-    for (int i = 0; i < kSums; ++i) s[i] = wave_sum_i64(s[i]);
+    wave_sums(s, part[wave]);
+  } else if (lane < kSums) {
+    part[wave][lane] = 0;
   }
-  if (lane == 0)
-    for (int i = 0; i < kSums; ++i) part[wave][i] = s[i];
   __syncthreads();
-  if (tid < kSums) {
-    long long z = 0;
-    for (int q = 0; q < NWV; ++q) z += part[q][tid];
-    if (z != 0)
-      atomicAdd(reinterpret_cast<unsigned long long*>(sums + tid), (unsigned long long)z);
+  if (wave == 0) {
+    if (lane < kSums) {
+      long long z = 0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) z += part[q][lane];
+      tot[lane] = (double)z;
+      if (lane == 0) msel = (int)z;
+      if (gridDim.x > 1) J.b.psum[(size_t)blockIdx.x * kSums + lane] = z;
+    }
+    if (gridDim.x > 1) return;
+    wave_lds_order();
+    solve_level(J, tot, msel, hp, hb);
+  } else if (gridDim.x == 1 && J.clear_vb) {  // the next level's search sets bits
+    for (int i = tid - 64; i < J.clear_words; i += kFitThreads - 64) J.clear_vb[i] = 0ull;
   }
 }
 
-// The level fit from the sums (A^T A and A^T b of the rows
-// (x, y, 1, 0, 0, 0, -xu, -yu | u) and (0, 0, 0, x, y, 1, -xv, -yv | v),
-// scaled by powers of two), solved by one lane with the matrix in registers,
-// then H_l = Hbase o G with Hbase = H_{l+1} (matches relative to the warped
-// source) or the identity (absolute matches); H_l = H_{l+1} when fewer than
-// 4 matches were fitted or the solve fails.
+// The fit of a level whose sums several k_fit blocks left.
 template <bool JOBS>
-__global__ __launch_bounds__(64) void k_solve(WeedJob one, const WeedJob* __restrict__ jobs) {
+__global__ __launch_bounds__(64) void k_solve(WeedJob one, const WeedJob* __restrict__ jobs,
+                                              int wpb) {
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
-  const int w = J.w, h = J.h;
-  const long long* __restrict__ sums = J.b.sums;
-  const double* __restrict__ Hprev = J.Hprev;
-  const double* __restrict__ Hbase = J.Hbase;
-  double* __restrict__ Hout = J.Hout;
-  int32_t* __restrict__ counts = J.counts;
-  __shared__ long long tot[kSums];
-  const int lane = threadIdx.x;
-  if (lane < kSums) tot[lane] = sums[lane];
-  double Hp[9], Hb[9];  // loaded with the sums
-  for (int i = 0; i < 9; ++i) Hp[i] = Hprev[i];
-  for (int i = 0; i < 9; ++i) Hb[i] = Hbase[i];
-  __syncthreads();
-  if (J.clear_vb) {  // the next level's search sets bits and its weeding adds sums
+  __shared__ double tot[kSums];
+  __shared__ int msel;
+  const int lane = threadIdx.x, e = min(lane, 8);
+  const double hp = J.Hprev[e];
+  const double hb[3] = {J.Hbase[e / 3 * 3], J.Hbase[e / 3 * 3 + 1], J.Hbase[e / 3 * 3 + 2]};
+  if (lane < kSums) {
+    long long z = 0;
+#pragma unroll 8
+    for (int b = 0; b < (J.words + wpb - 1) / wpb; ++b) z += J.b.psum[(size_t)b * kSums + lane];
+    tot[lane] = (double)z;
+    if (lane == 0) msel = (int)z;
+  }
+  if (J.clear_vb)
     for (int i = lane; i < J.clear_words; i += 64) J.clear_vb[i] = 0ull;
-    if (lane < 24) J.b.sums[lane] = 0;
-  }
-  if (lane != 0) return;
-  const int msel = (int)tot[0];
-  counts[1] = msel;
-  for (int i = 0; i < 9; ++i) Hout[i] = Hp[i];
-  if (msel < 4) return;
-  const int ox = w / 2, oy = h / 2;
-  int k = 0;
-  const int mx = ox > oy ? (ox > 1 ? ox : 1) : (oy > 1 ? oy : 1);
-  while ((1 << k) < mx) ++k;
-  const int deg[8] = {1, 1, 0, 1, 1, 0, 2, 2};
-  double A[72];
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-      const long long v = j < 8 ? normal_entry(tot, r, j) : normal_rhs(tot, r);
-      const int e = j < 8 ? -k * (deg_of(r) + deg[j]) : -k * (deg_of(r) + 1);
-      A[r * 9 + j] = ldexp((double)v, e);
-    }
-  double hs[8];
-  if (!solve8(A, hs)) return;
-  double Gc[9];
-  for (int i = 0; i < 8; ++i) Gc[i] = ldexp(hs[i], k * (1 - deg[i]));
-  Gc[8] = 1.0;
-  const double pox = (double)(2 * ox - (w - 1)), poy = (double)(2 * oy - (h - 1));
-  const double Pm[9] = {2, 0, pox, 0, 2, poy, 0, 0, (double)w};
-  const double Qm[9] = {(double)w, 0, -pox, 0, (double)w, -poy, 0, 0, 2};
-  double T1[9], T2[9], T3[9];
-  mat3_mul(Pm, Gc, T1);
-  mat3_mul(T1, Qm, T2);
-  mat3_mul(Hb, T2, T3);
-  const double d = T3[8];
-  if (d == 0.0) return;
-  double Hn[9];
-  for (int i = 0; i < 9; ++i) {
-    Hn[i] = T3[i] / d;
-    if (!isfinite(Hn[i])) return;
-  }
-  for (int i = 0; i < 9; ++i) Hout[i] = Hn[i];
+  wave_lds_order();
+  solve_level(J, tot, msel, hp, hb);
 }
 
 WeedArgs weed_args(const lnr_params& p, int level) {
@@ -575,76 +785,72 @@ WeedArgs weed_args(const lnr_params& p, int level) {
 
 }  // namespace
 
+namespace {
+// k_hyp, k_fit and, for a level of more than one k_fit block, k_solve over
+// njobs jobs of at most ntiles tiles.
+template <bool JOBS, int IPB, int NT>
+hipError_t launch_hyp(const WeedJob& one, const WeedJob* jobs, int njobs, int words,
+                      const WeedArgs& a, hipStream_t st) {
+  const size_t lds = hyp_lds(words, IPB);
+  if (lds > 64 * 1024) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hyp<JOBS, IPB, NT>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  LNR_LAUNCH((k_hyp<JOBS, IPB, NT>), dim3(weed_blocks(a.iters, IPB), 1, njobs), dim3(NT), lds, st,
+             one, jobs, a);
+  return hipGetLastError();
+}
+
+template <bool JOBS>
+hipError_t launch_weed(const WeedJob& one, const WeedJob* jobs, int njobs, int ntiles,
+                       const WeedArgs& a, hipStream_t st) {
+  const int words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
+  if (words > kMaxWords || a.iters > kMaxIters) return hipErrorInvalidValue;
+  const bool wide = hyp_wide(ntiles, njobs);
+  hipError_t e = wide ? launch_hyp<JOBS, 4, 512>(one, jobs, njobs, words, a, st)
+                      : launch_hyp<JOBS, 8, 256>(one, jobs, njobs, words, a, st);
+  if (e != hipSuccess) return e;
+  const int wpb = words <= kFitOne ? kFitOne : kFitWords;
+  const int blocks = (words + wpb - 1) / wpb;
+  LNR_LAUNCH(k_fit<JOBS>, dim3(blocks, 1, njobs), dim3(kFitThreads), 0, st, one, jobs, a,
+             wide ? 4 : 8, weed_blocks(a.iters, wide ? 4 : 8), wpb);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (blocks > 1) {
+    LNR_LAUNCH(k_solve<JOBS>, dim3(1, 1, njobs), dim3(64), 0, st, one, jobs, wpb);
+    e = hipGetLastError();
+  }
+  return e;
+}
+}  // namespace
+
 hipError_t launch_weed_fit(const int32_t* corner_xy, const int32_t* disp, uint8_t* flags,
                            int ntiles, int w, int h, int level, const lnr_params& p,
                            const double* H_prev, double* H_out, int32_t* counts,
                            const WeedBufs& b, hipStream_t st, bool vb_ready,
                            const double* H_base, int clear_words) {
-  const WeedArgs a = weed_args(p, level);
-  const int words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
-  const int chunks = ntiles > 0 ? (ntiles + kTestThreads - 1) / kTestThreads : 1;
-  const int ipb = ntiles <= kTestSmall ? 4 : 8;
-  const int groups = (a.iters + ipb - 1) / ipb;
-  if (words > kMaxWords || a.iters > kMaxIters) return hipErrorInvalidValue;
   WeedJob J;
   J.cxy = corner_xy; J.disp = disp; J.flags = flags;
-  J.ntiles = ntiles; J.w = w; J.h = h; J.words = words;
+  J.ntiles = ntiles; J.w = w; J.h = h; J.words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
   J.b = b;
   J.Hprev = H_prev; J.Hbase = H_base ? H_base : H_prev; J.Hout = H_out; J.counts = counts;
   J.clear_vb = clear_words > 0 ? b.vb : nullptr;
   J.clear_words = clear_words;
-  hipError_t e;
-  if (!vb_ready) {  // else the level's search set the bits (and its warp cleared the sums)
-    LNR_LAUNCH(k_valid, dim3((words + kValidThreads / 64 - 1) / (kValidThreads / 64)),
-               dim3(kValidThreads), 0, st, flags, ntiles, words, b.vb, b.sums);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (J.words > kMaxWords) return hipErrorInvalidValue;
+  if (!vb_ready) {  // else the level's search set the bits
+    LNR_LAUNCH(k_valid, dim3((J.words + kValidThreads / 64 - 1) / (kValidThreads / 64)),
+               dim3(kValidThreads), 0, st, flags, ntiles, J.words, b.vb);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  LNR_LAUNCH(k_hyp<false>, dim3((a.iters + kHypThreads - 1) / kHypThreads), dim3(kHypThreads), 0,
-             st, J, nullptr, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (ntiles > 0) {
-    if (ipb == 4)
-      LNR_LAUNCH((k_test<false, 4>), dim3(chunks, groups), dim3(kTestThreads), 0, st, J, nullptr,
-                 a);
-    else
-      LNR_LAUNCH((k_test<false, 8>), dim3(chunks, groups), dim3(kTestThreads), 0, st, J, nullptr,
-                 a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  LNR_LAUNCH(k_union<false>, dim3((words + kUnionThreads / 64 - 1) / (kUnionThreads / 64)),
-             dim3(kUnionThreads), 0, st, J, nullptr, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  LNR_LAUNCH(k_solve<false>, dim3(1), dim3(64), 0, st, J, nullptr);
-  return hipGetLastError();
+  return launch_weed<false>(J, nullptr, 1, ntiles, weed_args(p, level), st);
 }
 
 hipError_t launch_weed_jobs(const WeedJob* jobs, int njobs, int max_tiles, int level,
                             const lnr_params& p, hipStream_t st) {
   if (njobs < 1) return hipSuccess;
-  const WeedArgs a = weed_args(p, level);
-  const int words = max_tiles > 0 ? (max_tiles + 63) / 64 : 1;
-  const int chunks = max_tiles > 0 ? (max_tiles + kTestThreads - 1) / kTestThreads : 1;
-  const int ipb = max_tiles <= kTestSmall ? 4 : 8;
-  const int groups = (a.iters + ipb - 1) / ipb;
-  if (words > kMaxWords || a.iters > kMaxIters) return hipErrorInvalidValue;
-  WeedJob none{};
-  hipError_t e;
-  LNR_LAUNCH(k_hyp<true>, dim3((a.iters + kHypThreads - 1) / kHypThreads, 1, njobs),
-             dim3(kHypThreads), 0, st, none, jobs, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (ipb == 4)
-    LNR_LAUNCH((k_test<true, 4>), dim3(chunks, groups, njobs), dim3(kTestThreads), 0, st, none,
-               jobs, a);
-  else
-    LNR_LAUNCH((k_test<true, 8>), dim3(chunks, groups, njobs), dim3(kTestThreads), 0, st, none,
-               jobs, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  LNR_LAUNCH(k_union<true>,
-             dim3((words + kUnionThreads / 64 - 1) / (kUnionThreads / 64), 1, njobs),
-             dim3(kUnionThreads), 0, st, none, jobs, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  LNR_LAUNCH(k_solve<true>, dim3(1, 1, njobs), dim3(64), 0, st, none, jobs);
-  return hipGetLastError();
+  return launch_weed<true>(WeedJob{}, jobs, njobs, max_tiles, weed_args(p, level), st);
 }
 
 }  // namespace lnr

@@ -340,29 +340,30 @@ void bind_scratch(lnr_ctx* c, int device) {
 }
 
 struct WeedPlan {
-  size_t nmatch, G, cnt, bal, vb, sums;
+  size_t nmatch, key, G, part, psum, vb;
 };
 
 WeedPlan plan_weed(Plan& pl, int ntiles, int iters) {
   WeedPlan w;
-  const int nt = ntiles > 0 ? ntiles : 1;
+  const size_t words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
+  const size_t blocks = (size_t)weed_blocks(iters, 4);
   w.nmatch = pl.take(sizeof(int32_t));
-  w.G = pl.take(sizeof(double) * 8 * (size_t)iters);
-  w.cnt = pl.take(sizeof(int32_t) * (size_t)iters);
-  w.bal = pl.take(sizeof(unsigned long long) * (size_t)iters * ((nt + 63) / 64));
-  w.vb = pl.take(sizeof(unsigned long long) * (size_t)((nt + 63) / 64));
-  w.sums = pl.take(sizeof(long long) * 24);
+  w.key = pl.take(sizeof(unsigned long long) * blocks);
+  w.G = pl.take(sizeof(double) * 8 * blocks);
+  w.part = pl.take(sizeof(unsigned long long) * words * blocks);
+  w.psum = pl.take(sizeof(long long) * 24 * ((words + kFitWords - 1) / kFitWords));
+  w.vb = pl.take(sizeof(unsigned long long) * words);
   return w;
 }
 
 WeedBufs weed_bufs(char* base, const WeedPlan& w) {
   WeedBufs b;
   b.nmatch = reinterpret_cast<int32_t*>(base + w.nmatch);
+  b.key = reinterpret_cast<unsigned long long*>(base + w.key);
   b.G = reinterpret_cast<double*>(base + w.G);
-  b.cnt = reinterpret_cast<int32_t*>(base + w.cnt);
-  b.bal = reinterpret_cast<unsigned long long*>(base + w.bal);
+  b.part = reinterpret_cast<unsigned long long*>(base + w.part);
+  b.psum = reinterpret_cast<long long*>(base + w.psum);
   b.vb = reinterpret_cast<unsigned long long*>(base + w.vb);
-  b.sums = reinterpret_cast<long long*>(base + w.sums);
   return b;
 }
 
@@ -444,10 +445,10 @@ lnr_status enqueue_pair_setup(lnr_ctx* ctx, const lnr_frame* ref, const lnr_fram
   uint8_t* psrc = reinterpret_cast<uint8_t*>(base + q.o_psrc);
   uint8_t* guide_t = reinterpret_cast<uint8_t*>(base + q.o_gt);
   double* coef = reinterpret_cast<double*>(base + q.o_coef);
-  // (also cleared: the top level's weeding bits and sums, which its search fills)
+  // (also cleared: the top level's weeding bits, which its search sets)
   const WeedBufs wb = weed_bufs(base, q.wp);
   LNR_HIP(launch_dt_coef(*p, coef, hist, 512, out->H + 9 * g.levels, st, wb.vb,
-                         level_words(g.lv[g.levels - 1]), wb.sums));
+                         level_words(g.lv[g.levels - 1])));
   LNR_HIP(launch_hist(ref->plane[0], ref->stride[0], src->plane[0], src->stride[0], W, H, hist, 2, st));
   LNR_HIP(launch_lut_pyr(ref->plane[0], ref->stride[0], src->plane[0], src->stride[0], hist, g,
                          pref, psrc, nullptr, 2, st, out->yeq_ref, out->yeq_src, guide_t));
@@ -493,7 +494,7 @@ lnr_status enqueue_source_setup(lnr_ctx* ctx, const lnr_frame* src, const lnr_pa
   double* coef = reinterpret_cast<double*>(base + q.o_coef);
   const WeedBufs wb = weed_bufs(base, q.wp);
   LNR_HIP(launch_dt_coef(*p, coef, hist, 512, out->H + 9 * g.levels, st, wb.vb,
-                         level_words(g.lv[g.levels - 1]), wb.sums));
+                         level_words(g.lv[g.levels - 1])));
   LNR_HIP(launch_hist(src->plane[0], src->stride[0], src->plane[0], src->stride[0], W, H, hist, 1,
                       st));
   LNR_HIP(launch_lut_pyr(src->plane[0], src->stride[0], src->plane[0], src->stride[0], hist, g,
@@ -559,7 +560,7 @@ lnr_status enqueue_pair_levels(lnr_ctx* ctx, const lnr_frame* ref, const lnr_fra
       continue;
     }
     // the coarse levels' searches warp their windows on the fly (the set-up or
-    // the previous level's solve cleared the weeding bits and sums); level 0
+    // the previous level's fit cleared the weeding bits); level 0
     // is warped in full, straight into the output when it is wanted, and the
     // warp clears the level's weeding buffers and the learned path's counts
     if (l == 0 && out->warped0) warped = out->warped0;
@@ -1296,7 +1297,7 @@ void fill_batch_tables(BatchLayout& b, int n, const lnr_params* p, lnr_registrat
       wj.w = L.w; wj.h = L.h; wj.nwords = words;
       wj.Hn = o.H + 9 * (l + 1);
       wj.out = warped;
-      wj.vb = wb.vb; wj.sums = wb.sums;
+      wj.vb = wb.vb;
       memcpy(b.blob.data() + T.o_warp + k * sizeof(WarpJob), &wj, sizeof(wj));
       memcpy(b.blob.data() + T.o_row0 + k * sizeof(int), &row, sizeof(int));
       // coarse levels warp their windows on the fly, as in a single registration

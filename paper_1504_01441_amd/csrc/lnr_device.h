@@ -6,6 +6,21 @@
 
 namespace lnr {
 
+// nx / den and ny / den from one reciprocal: two Newton steps from the
+// hardware's approximation, then each quotient corrected by its exact
+// residual -- the steps a compiled double division takes for operands that
+// need no scaling, so the quotients are the same correctly rounded ones
+// wherever operands and quotients stay clear of the ends of the exponent
+// range (and den of 0).
+__device__ inline void recip_quotients(double nx, double ny, double den, double& qx, double& qy) {
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(fma(-den, r, 1.0), r, r);
+  r = fma(fma(-den, r, 1.0), r, r);
+  const double x = nx * r, y = ny * r;
+  qx = fma(fma(-den, x, nx), r, x);
+  qy = fma(fma(-den, y, ny), r, y);
+}
+
 // out = a b for row-major 3x3 matrices; each entry sums left to right.
 __device__ inline void mat3_mul(const double* a, const double* b, double* out) {
   double t[9];

@@ -78,8 +78,8 @@ hipError_t launch_lut_pyr(const uint8_t* y0, int s0, const uint8_t* y1, int s1,
 
 // ---- warp + search (k_search.hip)
 struct WeedBufs;
-// wb (optional): the level's weeding buffers, whose valid-match bits and
-// least-squares sums the warp clears and the search then fills
+// wb (optional): the level's weeding buffers, whose valid-match bits the warp
+// clears and the search then sets
 // zint: nzint (<= 256) counters to clear as well (the learned path's lists)
 hipError_t launch_warp_q8(const uint8_t* src, int w, int h, const double* Hn, uint8_t* out,
                           hipStream_t st, const WeedBufs* wb = nullptr, int nwords = 0,
@@ -139,8 +139,7 @@ struct WarpJob {
   int w, h, nwords;
   const double* Hn;         // the previous level's homography
   uint8_t* out;             // warped level
-  unsigned long long* vb;   // the level's weeding bits and sums, cleared here
-  long long* sums;
+  unsigned long long* vb;   // the level's weeding bits, cleared here
 };
 hipError_t launch_warp_jobs(const WarpJob* jobs, const int* row0, int njobs, int rows,
                             int wmax, hipStream_t st);
@@ -166,13 +165,22 @@ int search_split_candidates(int R, const SearchCfg& c, int* out, int max);
 hipError_t launch_texture(uint8_t* p, int n, uint32_t seed, hipStream_t st);
 
 // ---- weeding + level homography (k_weed.hip)
+// Hypothesis blocks of one level: each takes its share of the iterations (at
+// least 4 each) and leaves one union of accepted inlier bits and one best
+// hypothesis.
+constexpr int kWeedBlocks = 256;
+inline int weed_blocks(int iters, int per_block) {
+  const int n = (iters + per_block - 1) / per_block;
+  return n < kWeedBlocks ? n : kWeedBlocks;
+}
+constexpr int kFitWords = 16;  // tile words per k_fit block where the level needs several
 struct WeedBufs {
   int32_t* nmatch;          // [1] valid matches of the level
-  double* G;                // [iters][8] hypothesis homographies
-  int32_t* cnt;             // [iters] inlier counts (-1: hypothesis unusable)
-  unsigned long long* bal;  // [ceil(ntiles/64)][iters] inlier bitmask rows
+  unsigned long long* key;  // [blocks] best (count << 32 | ~iteration), 0: none usable
+  double* G;                // [blocks][8] the best hypothesis
+  unsigned long long* part; // [words][blocks] union of the block's accepted inlier bits
+  long long* psum;          // [fit blocks][24] partial least-squares sums
   unsigned long long* vb;   // [ceil(ntiles/64)] valid-match bits, tile order
-  long long* sums;          // [23] least-squares sums of the level fit
 };
 // one level of one pair for the weeding and level fit
 struct WeedJob {
@@ -185,17 +193,17 @@ struct WeedJob {
   const double* Hbase;  // the map G is composed on (H^{l+1}, or the identity)
   double* Hout;
   int32_t* counts;
-  // cleared by the solve for the next level's search (null: nothing)
+  // cleared by the fit for the next level's search (null: nothing)
   unsigned long long* clear_vb;
   int clear_words;
 };
 // the weeding kernels over a device table of jobs (the search set the
-// valid-match bits and the warp cleared the sums); max_tiles: the largest
+// valid-match bits); max_tiles: the largest
 // job's tiles
 hipError_t launch_weed_jobs(const WeedJob* jobs, int njobs, int max_tiles, int level,
                             const lnr_params& p, hipStream_t st);
-// clear_words > 0: the solve then clears the first clear_words valid-match
-// words and the sums, for the next level's search
+// clear_words > 0: the fit then clears the first clear_words valid-match
+// words, for the next level's search
 hipError_t launch_weed_fit(const int32_t* corner_xy, const int32_t* disp, uint8_t* flags,
                            int ntiles, int w, int h, int level, const lnr_params& p,
                            const double* H_prev, double* H_out, int32_t* counts,
@@ -258,7 +266,7 @@ __device__ inline void store_tile_columns(const uint8_t* tile, int bx, int by, i
 // also clears zero[0, nzero) and sets ident (optional) to the 3x3 identity
 hipError_t launch_dt_coef(const lnr_params& p, double* coef, uint32_t* zero, int nzero,
                           double* ident, hipStream_t st, unsigned long long* zero64 = nullptr,
-                          int nzero64 = 0, long long* sums = nullptr);
+                          int nzero64 = 0);
 
 // ---- backward warp (k_warp.hip)
 // Chroma of a 4:2:0 frame: U at u[(y/2) su + (x/2) cs], V likewise (I420: two

@@ -44,3 +44,36 @@ def test_training_step_at_block_edges(lnr, ctx, n):
     after = lnr.proposal_forward(ctx, xb)
     lnr.proposal_set(ctx, lnr.proposal_get(ctx))
     assert torch.equal(after, lnr.proposal_forward(ctx, xb))
+
+
+# one word / two; the narrow and the wide hypothesis blocks; the last size of
+# one fit block and the first of several; more iterations than blocks take at
+# once, and counts that leave a group short; few matches with repeated draws
+@pytest.mark.parametrize("nx,ny,iters,keep", [
+    (5, 1, 1024, 1.0), (4, 2, 5, 0.6), (13, 5, 1023, 0.9), (16, 16, 37, 0.9), (257, 1, 1024, 0.9),
+    (64, 32, 300, 0.8), (47, 45, 1024, 0.8), (70, 61, 3001, 0.7)])
+def test_weeding_at_split_edges(lnr, ctx, nx, ny, iters, keep):
+    rng = np.random.default_rng(nx * 100 + ny)
+    p, op = lnr.Params(weed_iters=iters), oracle.params(weed_iters=iters)
+    tile = 16 if nx > 190 else 32
+    w, h = nx * tile, max(ny * tile, tile)
+    gy, gx = np.mgrid[0:ny, 0:nx]
+    cx = (gx * tile + tile // 2 + 2 * rng.integers(-2, 3, gx.shape)).ravel().astype(np.int32)
+    cy = (gy * tile + tile // 2 + 2 * rng.integers(-2, 3, gx.shape)).ravel().astype(np.int32)
+    dx = (np.rint(0.01 * (cx - w / 2) - 3) + rng.integers(-1, 2, cx.shape)).astype(np.int32)
+    dy = (np.rint(0.02 * (cy - h / 2) + 2) + rng.integers(-1, 2, cx.shape)).astype(np.int32)
+    far = rng.random(cx.shape) < 0.3
+    dx[far], dy[far] = rng.integers(-16, 17, far.sum()), rng.integers(-16, 17, far.sum())
+    valid = (rng.random(cx.shape) < keep).astype(np.uint8)
+    M, n, bc, bi = oracle.weed(cx, cy, dx, dy, valid, w, h, 1, op)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    flags, H, counts = lnr.stage_weed_fit(
+        ctx, t(np.stack([cx, cy], 1)), t(np.stack([dx, dy], 1)),
+        t((valid * 3).astype(np.uint8)), w, h, 1, torch.eye(3, dtype=torch.float64).reshape(9), p)
+    f, c = flags.cpu().numpy(), counts.cpu().numpy()
+    assert np.array_equal((f & 4) > 0, M > 0)
+    assert c[0] == valid.sum() and c[2] == bc and c[3] == bi
+    sel = (f & 8) > 0
+    assert c[1] == sel.sum() == (bc if bc > oracle.weed_delta(int(valid.sum()), op) else 0)
+    want, _ = oracle.fit_level(cx, cy, dx, dy, sel.astype(np.uint8), w, h, np.eye(3))
+    assert np.array_equal(H.cpu().numpy().reshape(3, 3), want)
