@@ -17,9 +17,9 @@
 // 8-32 byte pieces of three planes; the column pass takes the guide from a
 // column-major copy (a segment's rows are one aligned load).
 //
-//  k_dt_row: one workgroup per row; the row is staged in LDS with coalesced
-//          loads, each of the 256 or 512 threads keeps a segment in registers, and
-//          wave shuffles + LDS combine the segment maps. The first pass writes
+//  k_dt_row: one workgroup per row; the row's records are loaded straight into
+//          LDS, each of the 256 or 512 threads keeps a segment in registers, and
+//          lane exchanges on the vector ALU + LDS combine the segment maps. The first pass writes
 //          the sparse maps itself from the tile list (no zero-fill pass); a
 //          row that holds no sample stays exactly zero through it, so that
 //          pass writes only a row flag for it, and the first column pass
@@ -27,6 +27,7 @@
 //  k_dt_col: one workgroup per strip of 2-8 columns over the full height, as
 //          128 or 256 segments per column held in registers; the records are read
 //          and written once per pass. The last pass writes F (and N~) instead.
+#include "lnr_device.h"
 #include "lnr_internal.h"
 
 namespace lnr {
@@ -69,76 +70,157 @@ struct Aff {  // z -> A z + B (three channels share A)
 __device__ inline Aff compose(const Aff& later, const Aff& earlier) {
   Aff r;
   r.A = later.A * earlier.A;
-  r.B0 = later.A * earlier.B0 + later.B0;
-  r.B1 = later.A * earlier.B1 + later.B1;
-  r.B2 = later.A * earlier.B2 + later.B2;
+  r.B0 = fma(later.A, earlier.B0, later.B0);
+  r.B1 = fma(later.A, earlier.B1, later.B1);
+  r.B2 = fma(later.A, earlier.B2, later.B2);
   return r;
 }
 
-__device__ inline Aff shfl_up_aff(const Aff& v, int off) {
-  Aff r;
-  r.A = __shfl_up(v.A, off);
-  r.B0 = __shfl_up(v.B0, off);
-  r.B1 = __shfl_up(v.B1, off);
-  r.B2 = __shfl_up(v.B2, off);
-  return r;
+// Lane exchange on the vector ALU; lanes without a source get `none`.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_or(double v, double none) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(none), __double2loint(v), CTRL, ROWS,
+                                             0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(none), __double2hiint(v), CTRL, ROWS,
+                                             0xf, false);
+  return __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROWS>
+__device__ inline Aff dpp_aff(const Aff& v) {  // (the identity without a source)
+  return Aff{dpp_or<CTRL, ROWS>(v.A, 1.0), dpp_or<CTRL, ROWS>(v.B0, 0.0),
+             dpp_or<CTRL, ROWS>(v.B1, 0.0), dpp_or<CTRL, ROWS>(v.B2, 0.0)};
+}
+__device__ inline Aff shfl_aff(const Aff& v, int src) {
+  return Aff{__shfl(v.A, src), __shfl(v.B0, src), __shfl(v.B1, src), __shfl(v.B2, src)};
 }
 
-__device__ inline Aff shfl_down_aff(const Aff& v, int off) {
-  Aff r;
-  r.A = __shfl_down(v.A, off);
-  r.B0 = __shfl_down(v.B0, off);
-  r.B1 = __shfl_down(v.B1, off);
-  r.B2 = __shfl_down(v.B2, off);
-  return r;
-}
+constexpr int kRowShl = 0x100, kRowShr = 0x110;  // + the distance, within 16 lanes
+constexpr int kWaveShl1 = 0x130, kWaveShr1 = 0x138;
+constexpr int kBcast15 = 0x142, kBcast31 = 0x143;
 
-// Carry into each thread of an NT-thread block: the composition of every
-// earlier thread's map (forward: lower tid; backward: higher tid) applied to 0.
-template <int NT, bool FWD>
-__device__ void block_carry(Aff v, Aff* wtot, double& c0, double& c1, double& c2) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Aff inc = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const Aff o = FWD ? shfl_up_aff(inc, off) : shfl_down_aff(inc, off);
-    const bool ok = FWD ? lane >= off : lane + off < 64;
-    if (ok) inc = compose(inc, o);
+// Inclusive composition over the segments of one line in a wave, segment
+// i on lanes i STRIDE + (line): forward, everything up to a lane's segment;
+// backward, everything from it on. Within 16 lanes on the vector ALU, then
+// across the four groups of 16.
+template <int STRIDE, bool FWD>
+__device__ inline Aff wave_scan(Aff inc) {
+  constexpr int dir = FWD ? kRowShr : kRowShl;
+  if constexpr (STRIDE <= 1) inc = compose(inc, dpp_aff<dir + 1, 0xf>(inc));
+  if constexpr (STRIDE <= 2) inc = compose(inc, dpp_aff<dir + 2, 0xf>(inc));
+  if constexpr (STRIDE <= 4) inc = compose(inc, dpp_aff<dir + 4, 0xf>(inc));
+  inc = compose(inc, dpp_aff<dir + 8, 0xf>(inc));
+  if constexpr (STRIDE == 1 && FWD) {
+    inc = compose(inc, dpp_aff<kBcast15, 0xa>(inc));
+    inc = compose(inc, dpp_aff<kBcast31, 0xc>(inc));
+  } else {
+    const int lane = threadIdx.x & 63, l = lane % STRIDE;
+    const Aff a = shfl_aff(inc, FWD ? (lane & 32) | (16 - STRIDE + l) : (lane & 32) | (16 + l));
+    if (FWD ? (lane & 16) != 0 : (lane & 16) == 0) inc = compose(inc, a);
+    const Aff b = shfl_aff(inc, FWD ? 32 - STRIDE + l : 32 + l);
+    if (FWD ? lane >= 32 : lane < 32) inc = compose(inc, b);
   }
-  if (FWD ? lane == 63 : lane == 0) wtot[wave] = inc;
+  return inc;
+}
+
+// Carry into each segment of a block of NW waves: the composition of every
+// earlier segment of its line (forward: lower lanes and waves; backward:
+// higher ones), applied to 0. wt: NW * STRIDE entries of LDS.
+template <int STRIDE, int NW, bool FWD>
+__device__ inline void line_carry(const Aff& v, Aff* wt, double& c0, double& c1, double& c2) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l = lane % STRIDE;
+  const Aff inc = wave_scan<STRIDE, FWD>(v);
+  if (FWD ? lane >= 64 - STRIDE : lane < STRIDE) wt[wave * STRIDE + l] = inc;
+  Aff prev;  // the wave's earlier segments
+  if constexpr (STRIDE == 1) {
+    prev = dpp_aff<FWD ? kWaveShr1 : kWaveShl1, 0xf>(inc);
+  } else {
+    prev = shfl_aff(inc, FWD ? lane - STRIDE : lane + STRIDE);
+    if (FWD ? lane < STRIDE : lane >= 64 - STRIDE) prev = Aff{1.0, 0.0, 0.0, 0.0};
+  }
   __syncthreads();
   double z0 = 0.0, z1 = 0.0, z2 = 0.0;  // carry into this wave
-  if (FWD) {
-    for (int w = 0; w < wave; ++w) {
-      const Aff t = wtot[w];
-      z0 = t.A * z0 + t.B0; z1 = t.A * z1 + t.B1; z2 = t.A * z2 + t.B2;
-    }
-  } else {
-    for (int w = NT / 64 - 1; w > wave; --w) {
-      const Aff t = wtot[w];
-      z0 = t.A * z0 + t.B0; z1 = t.A * z1 + t.B1; z2 = t.A * z2 + t.B2;
-    }
+#pragma unroll 2
+  for (int i = 0; i < (FWD ? wave : NW - 1 - wave); ++i) {
+    const Aff t = wt[(FWD ? i : NW - 1 - i) * STRIDE + l];
+    z0 = fma(t.A, z0, t.B0);
+    z1 = fma(t.A, z1, t.B1);
+    z2 = fma(t.A, z2, t.B2);
   }
-  const Aff prev = FWD ? shfl_up_aff(inc, 1) : shfl_down_aff(inc, 1);
-  const bool edge = FWD ? lane == 0 : lane == 63;
-  if (edge) { c0 = z0; c1 = z1; c2 = z2; }
-  else {
-    c0 = prev.A * z0 + prev.B0;
-    c1 = prev.A * z1 + prev.B1;
-    c2 = prev.A * z2 + prev.B2;
-  }
+  c0 = fma(prev.A, z0, prev.B0);
+  c1 = fma(prev.A, z1, prev.B1);
+  c2 = fma(prev.A, z2, prev.B2);
   __syncthreads();
 }
 
-// Coefficient between positions i-1 and i of a line: 0 where i - 1 or i is
-// outside [0, n) (the recursion starts fresh at both ends).
-__device__ inline double coef_at(const double* cf, int gprev, int gcur) {
-  return cf[abs(gcur - gprev)];
+// Pins a value to a register of its own type at this point: without it the
+// segments' double values of one sweep are kept for the next (twice the
+// registers), and the addresses of the loads for the stores.
+template <typename T>
+__device__ inline void hold(T& v) {
+  asm volatile("" : "+v"(v));
 }
 
+// The three sweeps over a segment. A causal step is p = u + c (p - u); the
+// first sweep composes the segment's causal steps. The second applies them
+// and composes the anti-causal ones (z -> c z + (1 - c) p, c towards the next
+// pixel) from the left as it goes, the third applies those. A pixel past the
+// line's end has value 0 and c 0 on both sides, so it needs no test.
+__device__ inline void causal_sum(Aff& t, double c, double u0, double u1, double u2) {
+  t.B0 = fma(c, t.B0 - u0, u0);
+  t.B1 = fma(c, t.B1 - u1, u1);
+  t.B2 = fma(c, t.B2 - u2, u2);
+  t.A *= c;
+}
+__device__ inline void step(double& p, double c, float& u) {
+  const double v = u;
+  p = fma(c, p - v, v);
+  u = (float)p;
+  hold(u);
+}
+__device__ inline void anticausal_sum(Aff& t, double c, double p0, double p1, double p2) {
+  const double n = t.A * c, d = t.A - n;  // A (1 - c)
+  t.B0 = fma(d, p0, t.B0);
+  t.B1 = fma(d, p1, t.B1);
+  t.B2 = fma(d, p2, t.B2);
+  t.A = n;
+}
+
+
+// Every fourth step of a sweep: the coefficients of later steps are not
+// fetched (nor values converted) before these are done with their registers.
+__device__ inline void pace(int j) {
+  if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+}
+
+struct __attribute__((packed)) UnalignedU32 {
+  uint32_t v;
+};
+
+// 4 or 16 bytes per lane from g straight into LDS, lane after lane from l
+// (the wave's base) on; the wave must wait for its memory counter before it or
+// another wave reads them. (12 bytes per lane would land 16 apart.)
+__device__ inline void to_lds4(const float* g, float* l) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)l, 4, 0, 0);
+}
+__device__ inline void to_lds16(const float* g, float* l) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+}
+__device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---------------------------------------------------------------------------
-// Horizontal pass: one block per row; the row is staged in LDS (coalesced),
-// each thread keeps a segment of SEG consecutive pixels in registers.
+// Horizontal pass: one block per row. The row's records are staged in LDS as
+// they are (12 bytes, loaded straight into it), each thread keeps a segment
+// of SEG consecutive pixels in registers (a segment's records are whole
+// 16-byte reads that cover the banks evenly), the results go back the same
+// way.
+// A pass moves its 24 bytes per pixel through the last-level cache in about
+// 15 us at 5 MP; the rest of its time is the sweeps' double-precision work and
+// the two carries, a few blocks per CU overlapping each other's. Of 37 us at
+// 5 MP, fused multiply-adds, the anti-causal composition folded into the
+// causal sweep, scans without LDS round trips and the staging without
+// registers leave 27 (8 MP at an odd width, staged by dwords: 80 -> 44).
 template <int SEG, int NT, bool FIRST>
 __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
                                                 const uint8_t* __restrict__ guide, int W, int H,
@@ -150,11 +232,8 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
                                                 uint8_t* __restrict__ rowflag) {
   extern __shared__ __align__(16) float sm[];
   __shared__ double cf[256];
-  __shared__ Aff wtot[NT / 64];
-  float* v0 = sm;
-  float* v1 = sm + W;
-  float* v2 = sm + 2 * W;
-  uint8_t* g = reinterpret_cast<uint8_t*>(sm + 3 * W);
+  __shared__ Aff wt[NT / 64];
+  Rec* row = reinterpret_cast<Rec*>(sm);
   const int y = blockIdx.x, tid = threadIdx.x;
   const size_t ro = (size_t)y * W;
   if (FIRST) {
@@ -169,28 +248,41 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
     has = __syncthreads_or(has);
     if (tid == 0) rowflag[y] = (uint8_t)(has != 0);
     if (!has) return;  // all zeros: the column pass does not read this row
+    for (int x = tid; x < W; x += NT) row[x] = Rec{0.f, 0.f, 0.f};
+  } else {
+    const float* src = reinterpret_cast<const float*>(maps + ro);
+    if ((W & 3) == 0) {  // every row is whole 16-byte words
+#pragma unroll
+      for (int u = 0; u < (3 * SEG + 3) / 4; ++u) {
+        const int i = u * NT + tid;
+        if (4 * i < 3 * W) to_lds16(src + 4 * i, sm + 4 * (u * NT + (tid & ~63)));
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 3 * SEG; ++u) {
+        const int i = u * NT + tid;
+        if (i < 3 * W) to_lds4(src + i, sm + (u * NT + (tid & ~63)));
+      }
+    }
   }
   if (tid < 256) cf[tid] = coef[tid];
-  // staging: the whole row's loads in flight at once (NT * SEG covers the
-  // row, so SEG per thread), then the stores to workgroup memory
-  {
-    uint8_t tg[SEG];
-    Rec t[SEG];
+  // guide bytes of pixels xb - 1 .. xb + SEG as unaligned dwords, where those
+  // stay inside the image, else one by one
+  const int xb = tid * SEG;
+  constexpr int ND = (SEG + 2 + 3) / 4;
+  uint32_t gw[ND];
 #pragma unroll
-    for (int u = 0; u < SEG; ++u) {
-      const int xc = min(u * NT + tid, W - 1);  // in bounds; stored only if x < W
-      tg[u] = guide[ro + xc];
-      if (FIRST) t[u] = Rec{0.f, 0.f, 0.f};
-      else t[u] = maps[ro + xc];
-    }
+  for (int q = 0; q < ND; ++q) gw[q] = 0u;
+  if (xb < W) {
+    const long long g0 = (long long)ro + xb - 1;
+    if (g0 >= 0 && g0 + 4 * ND <= (long long)W * H) {
 #pragma unroll
-    for (int u = 0; u < SEG; ++u) {
-      const int x = u * NT + tid;
-      if (x >= W) break;
-      g[x] = tg[u];
-      v0[x] = t[u].m0;
-      v1[x] = t[u].m1;
-      v2[x] = t[u].m2;
+      for (int q = 0; q < ND; ++q)
+        gw[q] = reinterpret_cast<const UnalignedU32*>(guide + g0 + 4 * q)->v;
+    } else {
+#pragma unroll
+      for (int k = 0; k < SEG + 2; ++k)
+        if (xb - 1 + k >= 0 && xb - 1 + k < W) gw[k >> 2] |= (uint32_t)guide[g0 + k] << (8 * (k & 3));
     }
   }
   if (FIRST) {
@@ -199,170 +291,86 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
     if (ty < nty)
       for (int tx = tid; tx < ntx; tx += NT) {
         const int t = ty * ntx + tx;
-        if ((flags[t] & 4) && cxy[2 * t + 1] == y) {
-          const int x = cxy[2 * t];
-          v0[x] = (float)disp[2 * t];
-          v1[x] = (float)disp[2 * t + 1];
-          v2[x] = 1.f;
-        }
+        if ((flags[t] & 4) && cxy[2 * t + 1] == y)
+          row[cxy[2 * t]] = Rec{(float)disp[2 * t], (float)disp[2 * t + 1], 1.f};
       }
+  } else {
+    wait_loads();
   }
   __syncthreads();
-  const int xb = tid * SEG;
   // the segment is held as float (as stored between passes); every recursion
-  // step and carry is computed in double precision. A whole segment is read
-  // with 16-byte accesses where the planes allow (W a multiple of 4): a
-  // thread's elements lie SEG apart from its neighbours', which scalar reads
-  // would serve four to a bank.
-  float a0[SEG], a1[SEG], a2[SEG];
-  int gs[SEG + 2];  // guide bytes of pixels xb - 1 .. xb + SEG, 0 outside the row
-  const bool vec = SEG % 4 == 0 && (W & 3) == 0 && xb + SEG <= W;
-  if (vec) {
+  // step and carry is computed in double precision
+  float a[3 * SEG];
+  constexpr int VW = SEG % 4 == 0 ? 4 : 2;  // floats per LDS access
+  typedef float fv __attribute__((ext_vector_type(VW)));
+  fv* seg = reinterpret_cast<fv*>(row + xb);
 #pragma unroll
-    for (int q = 0; q < SEG / 4; ++q) {
-      const float4 f0 = reinterpret_cast<const float4*>(v0 + xb)[q];
-      const float4 f1 = reinterpret_cast<const float4*>(v1 + xb)[q];
-      const float4 f2 = reinterpret_cast<const float4*>(v2 + xb)[q];
-      a0[4 * q] = f0.x; a0[4 * q + 1] = f0.y; a0[4 * q + 2] = f0.z; a0[4 * q + 3] = f0.w;
-      a1[4 * q] = f1.x; a1[4 * q + 1] = f1.y; a1[4 * q + 2] = f1.z; a1[4 * q + 3] = f1.w;
-      a2[4 * q] = f2.x; a2[4 * q + 1] = f2.y; a2[4 * q + 2] = f2.z; a2[4 * q + 3] = f2.w;
-      const uint32_t w4 = reinterpret_cast<const uint32_t*>(g + xb)[q];
+  for (int q = 0; q < 3 * SEG / VW; ++q) {
+    fv v = 0.f;
+    if (xb < W) v = seg[q];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) gs[1 + 4 * q + k] = (int)((w4 >> (8 * k)) & 255u);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const int x = xb + j;
-      a0[j] = x < W ? v0[x] : 0.f;
-      a1[j] = x < W ? v1[x] : 0.f;
-      a2[j] = x < W ? v2[x] : 0.f;
-      gs[1 + j] = x < W ? g[x] : 0;
-    }
+    for (int k = 0; k < VW; ++k) a[VW * q + k] = v[k];
   }
-  gs[0] = xb > 0 && xb - 1 < W ? g[xb - 1] : 0;
-  gs[SEG + 1] = xb + SEG < W ? g[xb + SEG] : 0;
-  double cc[SEG + 1];  // cc[j]: between xb+j-1 and xb+j
+  if (xb < W && xb + SEG > W) {
+#pragma unroll
+    for (int j = 0; j < SEG; ++j)
+      if (xb + j >= W) a[3 * j] = a[3 * j + 1] = a[3 * j + 2] = 0.f;
+  }
+  double cc[SEG + 1];  // cc[j]: between xb + j - 1 and xb + j, 0 at the ends
 #pragma unroll
   for (int j = 0; j <= SEG; ++j) {
+    const int g0 = (int)(gw[j >> 2] >> (8 * (j & 3))) & 255;
+    const int g1 = (int)(gw[(j + 1) >> 2] >> (8 * ((j + 1) & 3))) & 255;
     const int x = xb + j;
-    cc[j] = (x > 0 && x < W) ? coef_at(cf, gs[j], gs[j + 1]) : 0.0;
+    cc[j] = x > 0 && x < W ? cf[abs(g1 - g0)] : 0.0;
   }
-  // causal: J[x] = J[x] + c (J[x-1] - J[x])
-  {
-    Aff t{1.0, 0.0, 0.0, 0.0};
+  Aff t{1.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      if (xb + j >= W) continue;
-      const double c = cc[j];
-      const double u0 = a0[j], u1 = a1[j], u2 = a2[j];
-      t.B0 = u0 + c * (t.B0 - u0);
-      t.B1 = u1 + c * (t.B1 - u1);
-      t.B2 = u2 + c * (t.B2 - u2);
-      t.A *= c;
-    }
-    double p0, p1, p2;
-    block_carry<NT, true>(t, wtot, p0, p1, p2);
+  for (int j = 0; j < SEG; ++j) causal_sum(t, cc[j], a[3 * j], a[3 * j + 1], a[3 * j + 2]);
+  double p0, p1, p2;
+  line_carry<1, NT / 64, true>(t, wt, p0, p1, p2);
+  t = Aff{1.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      if (xb + j >= W) continue;
-      const double c = cc[j];
-      const double u0 = a0[j], u1 = a1[j], u2 = a2[j];
-      p0 = u0 + c * (p0 - u0); a0[j] = (float)p0;
-      p1 = u1 + c * (p1 - u1); a1[j] = (float)p1;
-      p2 = u2 + c * (p2 - u2); a2[j] = (float)p2;
-    }
+  for (int j = 0; j < SEG; ++j) {
+    hold(a[3 * j]);
+    hold(a[3 * j + 1]);
+    hold(a[3 * j + 2]);
+    step(p0, cc[j], a[3 * j]);
+    step(p1, cc[j], a[3 * j + 1]);
+    step(p2, cc[j], a[3 * j + 2]);
+    anticausal_sum(t, cc[j + 1], p0, p1, p2);
   }
-  // anti-causal: J[x] = J[x] + c (J[x+1] - J[x]), c between x and x+1
-  {
-    Aff t{1.0, 0.0, 0.0, 0.0};
+  line_carry<1, NT / 64, false>(t, wt, p0, p1, p2);
 #pragma unroll
-    for (int j = SEG - 1; j >= 0; --j) {
-      if (xb + j >= W) continue;
-      const double c = cc[j + 1];
-      const double u0 = a0[j], u1 = a1[j], u2 = a2[j];
-      t.B0 = u0 + c * (t.B0 - u0);
-      t.B1 = u1 + c * (t.B1 - u1);
-      t.B2 = u2 + c * (t.B2 - u2);
-      t.A *= c;
-    }
-    double p0, p1, p2;
-    block_carry<NT, false>(t, wtot, p0, p1, p2);
-#pragma unroll
-    for (int j = SEG - 1; j >= 0; --j) {
-      if (xb + j >= W) continue;
-      const double c = cc[j + 1];
-      const double u0 = a0[j], u1 = a1[j], u2 = a2[j];
-      p0 = u0 + c * (p0 - u0); a0[j] = (float)p0;
-      p1 = u1 + c * (p1 - u1); a1[j] = (float)p1;
-      p2 = u2 + c * (p2 - u2); a2[j] = (float)p2;
-    }
+  for (int j = SEG - 1; j >= 0; --j) {
+    step(p0, cc[j + 1], a[3 * j]);
+    step(p1, cc[j + 1], a[3 * j + 1]);
+    step(p2, cc[j + 1], a[3 * j + 2]);
   }
-  if (vec) {
+  if (xb < W) {
 #pragma unroll
-    for (int q = 0; q < SEG / 4; ++q) {
-      reinterpret_cast<float4*>(v0 + xb)[q] =
-          make_float4(a0[4 * q], a0[4 * q + 1], a0[4 * q + 2], a0[4 * q + 3]);
-      reinterpret_cast<float4*>(v1 + xb)[q] =
-          make_float4(a1[4 * q], a1[4 * q + 1], a1[4 * q + 2], a1[4 * q + 3]);
-      reinterpret_cast<float4*>(v2 + xb)[q] =
-          make_float4(a2[4 * q], a2[4 * q + 1], a2[4 * q + 2], a2[4 * q + 3]);
-    }
-  } else {
+    for (int q = 0; q < 3 * SEG / VW; ++q) {
+      fv v;
 #pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const int x = xb + j;
-      if (x < W) { v0[x] = a0[j]; v1[x] = a1[j]; v2[x] = a2[j]; }
+      for (int k = 0; k < VW; ++k) v[k] = a[VW * q + k];
+      seg[q] = v;
     }
   }
   __syncthreads();
 #pragma unroll 4
-  for (int x = tid; x < W; x += NT) maps[ro + x] = Rec{v0[x], v1[x], v2[x]};
+  for (int x = tid; x < W; x += NT) maps[ro + x] = row[x];
 }
 
 // ---------------------------------------------------------------------------
 // Vertical pass: a block covers NCOL adjacent columns over the full height as
 // NSEG segments of L rows (NCOL * NSEG = 512 threads); each thread keeps its
 // segment of one column in registers, so the maps are read and written once.
-// Segment carries are combined with wave shuffles (segments of a column sit
-// NCOL lanes apart) and per-wave totals in LDS.
-template <int NCOL, int NSEG>
-__device__ void seg_carry(Aff v, bool fwd, Aff* wt /*[NSEG*NCOL/64][NCOL]*/, double& c0,
-                          double& c1, double& c2) {
-  constexpr int PER = 64 / NCOL;  // segments of one column per wave
-  constexpr int NW = NSEG / PER;  // waves
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid % NCOL;
-  const int sl = lane / NCOL;  // segment index within the wave
-  Aff inc = v;
-#pragma unroll
-  for (int off = 1; off < PER; off <<= 1) {
-    const Aff o = fwd ? shfl_up_aff(inc, off * NCOL) : shfl_down_aff(inc, off * NCOL);
-    const bool ok = fwd ? sl >= off : sl + off < PER;
-    if (ok) inc = compose(inc, o);
-  }
-  if (fwd ? sl == PER - 1 : sl == 0) wt[wave * NCOL + cl] = inc;
-  __syncthreads();
-  double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-  if (fwd) {
-    for (int w = 0; w < wave; ++w) {
-      const Aff t = wt[w * NCOL + cl];
-      z0 = t.A * z0 + t.B0; z1 = t.A * z1 + t.B1; z2 = t.A * z2 + t.B2;
-    }
-  } else {
-    for (int w = NW - 1; w > wave; --w) {
-      const Aff t = wt[w * NCOL + cl];
-      z0 = t.A * z0 + t.B0; z1 = t.A * z1 + t.B1; z2 = t.A * z2 + t.B2;
-    }
-  }
-  const Aff prev = fwd ? shfl_up_aff(inc, NCOL) : shfl_down_aff(inc, NCOL);
-  const bool edge = fwd ? sl == 0 : sl == PER - 1;
-  if (edge) { c0 = z0; c1 = z1; c2 = z2; }
-  else {
-    c0 = prev.A * z0 + prev.B0;
-    c1 = prev.A * z1 + prev.B1;
-    c2 = prev.A * z2 + prev.B2;
-  }
-  __syncthreads();
+// Segments of a column sit NCOL lanes apart. The segments' registers bound the
+// blocks in flight (two per CU at L = 16), so the sweeps are written not to
+// keep their double values: 42 -> 36 us per pass at 5 MP, the last 52 -> 41.
+template <int NCOL, int NSEG, bool FWD>
+__device__ inline void seg_carry(const Aff& v, Aff* wt, double& c0, double& c1, double& c2) {
+  line_carry<NCOL, NSEG * NCOL / 64, FWD>(v, wt, c0, c1, c2);
 }
 
 template <int L, int NCOL, int NSEG, bool LAST>
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
                                                         float* __restrict__ flow,
                                                         float* __restrict__ ntilde, double nmin,
                                                         const uint8_t* __restrict__ rowflag) {
-  __shared__ double cf[256];
+  __shared__ double cf[257];  // [256]: 0, past the ends
   __shared__ Aff wt[NSEG * NCOL / 64 * NCOL];
   const int tid = threadIdx.x, cl = tid % NCOL, sg = tid / NCOL;
   // XCD-aware strip order: consecutive blocks run on different XCDs, so
@@ -384,13 +392,11 @@ __global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
   const bool act = col < W;
   const int r0 = sg * L;
   const size_t plane = (size_t)W * H;
-  for (int i = tid; i < 256; i += NCOL * NSEG) cf[i] = coef[i];
+  for (int i = tid; i < 257; i += NCOL * NSEG) cf[i] = i < 256 ? coef[i] : 0.0;
   __syncthreads();
   // guide bytes of rows r0 .. r0+L-1, four per register, as one aligned load
   // from the column-major copy (r0 is a multiple of L, a multiple of 8, and
-  // the copy's rows run past r0 + L), plus the rows r0-1 and r0+L; the
-  // coefficient between rows r0+j-1 and r0+j is looked up when needed (0 at
-  // the ends)
+  // the copy's rows run past r0 + L), plus the rows r0-1 and r0+L
   static_assert(L % 8 == 0, "segments are whole 8-byte guide words");
   constexpr int NG = L / 4;
   uint32_t gpk[NG];
@@ -438,71 +444,74 @@ __global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
     a1[j] = r.m1;
     a2[j] = r.m2;
   }
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    hold(a0[j]);
+    hold(a1[j]);
+    hold(a2[j]);
+  }
+  // |g[j] - g[j - 1]| of rows j = 0 .. L as a byte offset into the table, 11
+  // bits each; rows past the ends (and the image's) take the 0 behind it
 #define GB(j)                                                              \
   ((j) < 0 ? (int)gup                                                      \
    : (j) >= L ? (int)gdn                                                   \
               : (int)((gpk[((j) >= 0 && (j) < L ? (j) : 0) >> 2] >> (8 * ((j) & 3))) & 255u))
-#define CC(j) ((r0 + (j) > 0 && r0 + (j) < H) ? cf[abs(GB(j) - GB((j) - 1))] : 0.0)
-  {
-    Aff t{1.0, 0.0, 0.0, 0.0};
+  uint32_t dpk[(L + 2) / 2];
 #pragma unroll
-    for (int j = 0; j < L; ++j) {
-      if (r0 + j >= H) break;
-      const double c = CC(j);
-      const double v0 = a0[j], v1 = a1[j], v2 = a2[j];
-      t.B0 = v0 + c * (t.B0 - v0);
-      t.B1 = v1 + c * (t.B1 - v1);
-      t.B2 = v2 + c * (t.B2 - v2);
-      t.A *= c;
-    }
-    double p0, p1, p2;
-    seg_carry<NCOL, NSEG>(t, true, wt, p0, p1, p2);
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-      if (r0 + j >= H) break;
-      const double c = CC(j);
-      const double v0 = a0[j], v1 = a1[j], v2 = a2[j];
-      p0 = v0 + c * (p0 - v0); a0[j] = (float)p0;
-      p1 = v1 + c * (p1 - v1); a1[j] = (float)p1;
-      p2 = v2 + c * (p2 - v2); a2[j] = (float)p2;
-    }
+  for (int j = 0; j <= L; ++j) {
+    const uint32_t d = r0 + j > 0 && r0 + j < H ? (uint32_t)abs(GB(j) - GB(j - 1)) : 256u;
+    if (j & 1) dpk[j >> 1] |= d << 19;
+    else dpk[j >> 1] = d << 3;
   }
-  {
-    Aff t{1.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int j = L - 1; j >= 0; --j) {
-      if (r0 + j >= H) continue;
-      const double c = CC(j + 1);
-      const double v0 = a0[j], v1 = a1[j], v2 = a2[j];
-      t.B0 = v0 + c * (t.B0 - v0);
-      t.B1 = v1 + c * (t.B1 - v1);
-      t.B2 = v2 + c * (t.B2 - v2);
-      t.A *= c;
-    }
-    double p0, p1, p2;
-    seg_carry<NCOL, NSEG>(t, false, wt, p0, p1, p2);
-#pragma unroll
-    for (int j = L - 1; j >= 0; --j) {
-      if (r0 + j >= H) continue;
-      const double c = CC(j + 1);
-      const double v0 = a0[j], v1 = a1[j], v2 = a2[j];
-      p0 = v0 + c * (p0 - v0); a0[j] = (float)p0;
-      p1 = v1 + c * (p1 - v1); a1[j] = (float)p1;
-      p2 = v2 + c * (p2 - v2); a2[j] = (float)p2;
-    }
-  }
-#undef CC
 #undef GB
-  if (!act) return;
+  const char* cfb = reinterpret_cast<const char*>(cf);
+#define CC(j) \
+  (*reinterpret_cast<const double*>(cfb + ((j) & 1 ? dpk[(j) >> 1] >> 16 : dpk[(j) >> 1] & 0xffffu)))
+  Aff t{1.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < L; ++j) {
-    const int y = r0 + j;
+    causal_sum(t, CC(j), a0[j], a1[j], a2[j]);
+    pace(j);
+  }
+  double p0, p1, p2;
+  seg_carry<NCOL, NSEG, true>(t, wt, p0, p1, p2);
+  t = Aff{1.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    hold(a0[j]);
+    hold(a1[j]);
+    hold(a2[j]);
+    const double c = CC(j);
+    step(p0, c, a0[j]);
+    step(p1, c, a1[j]);
+    step(p2, c, a2[j]);
+    anticausal_sum(t, CC(j + 1), p0, p1, p2);
+    pace(j);
+  }
+  seg_carry<NCOL, NSEG, false>(t, wt, p0, p1, p2);
+#pragma unroll
+  for (int j = L - 1; j >= 0; --j) {
+    const double c = CC(j + 1);
+    step(p0, c, a0[j]);
+    step(p1, c, a1[j]);
+    step(p2, c, a2[j]);
+    pace(L - 1 - j);
+  }
+#undef CC
+  if (!act) return;
+  int rs = r0;
+  hold(rs);
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    const int y = rs + j;
     if (y >= H) break;
     const size_t o = (size_t)y * W + col;
     if (LAST) {
       const bool ok = (double)a2[j] > nmin;
-      flow[o] = ok ? (float)((double)a0[j] / (double)a2[j]) : 0.f;
-      flow[plane + o] = ok ? (float)((double)a1[j] / (double)a2[j]) : 0.f;
+      double fu, fv;  // (float operands: far from the double range's ends)
+      recip_quotients((double)a0[j], (double)a1[j], (double)a2[j], fu, fv);
+      flow[o] = ok ? (float)fu : 0.f;
+      flow[plane + o] = ok ? (float)fv : 0.f;
       if (ntilde) ntilde[o] = a2[j];
     } else {
       maps[o] = Rec{a0[j], a1[j], a2[j]};
@@ -530,7 +539,7 @@ hipError_t launch_row(bool first, Rec* maps, const uint8_t* guide, int W, int H,
                       const double* cf, const int32_t* cxy, const int32_t* disp,
                       const uint8_t* flags, int ntx, int nty, int tile, uint8_t* rowflag,
                       hipStream_t st) {
-  const size_t lds = (size_t)W * 3 * sizeof(float) + (size_t)W + 16;
+  const size_t lds = (size_t)((W + SEG - 1) / SEG) * SEG * sizeof(Rec);
   if (lds > 64 * 1024) {  // rows wider than ~5000 px need more than the default LDS
     hipError_t e = hipFuncSetAttribute(
         reinterpret_cast<const void*>(first ? &k_dt_row<SEG, NT, true> : &k_dt_row<SEG, NT, false>),

@@ -77,3 +77,30 @@ def test_weeding_at_split_edges(lnr, ctx, nx, ny, iters, keep):
     assert c[1] == sel.sum() == (bc if bc > oracle.weed_delta(int(valid.sum()), op) else 0)
     want, _ = oracle.fit_level(cx, cy, dx, dy, sel.astype(np.uint8), w, h, np.eye(3))
     assert np.array_equal(H.cpu().numpy().reshape(3, 3), want)
+
+
+# every default row and column shape at widths that are not whole 16-byte words
+# or whole segments, and at lines shorter than one segment
+@pytest.mark.parametrize("w,h", [(5, 40), (1021, 66), (2047, 40), (3070, 36), (4093, 33),
+                                 (5002, 34), (40, 1023), (66, 2047), (35, 3071), (34, 4095),
+                                 (33, 5001)])
+def test_flow_at_line_edges(lnr, ctx, w, h):
+    rng = np.random.default_rng(w + h)
+    p, op = lnr.Params(), oracle.params()
+    guide = np.clip(np.cumsum(rng.integers(-9, 10, (h, w)), 1) + 128, 0, 255).astype(np.uint8)
+    nx, ny = w // 32, h // 32
+    gy, gx = np.mgrid[0:ny, 0:nx]
+    cx = (gx * 32 + 16 + rng.integers(-16, 16, gx.shape)).ravel().astype(np.int32)
+    cy = (gy * 32 + 16 + rng.integers(-16, 16, gx.shape)).ravel().astype(np.int32)
+    dx = rng.integers(-16, 17, cx.shape).astype(np.int32)
+    dy = rng.integers(-16, 17, cx.shape).astype(np.int32)
+    keep = (rng.random(cx.shape) < 0.7).astype(np.uint8)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    flow, nt = lnr.stage_flow(ctx, t(np.stack([cx, cy], 1).reshape(-1, 2)),
+                              t(np.stack([dx, dy], 1).reshape(-1, 2)), t(keep * 7), t(guide), p)
+    u, v, n = oracle.sparse_to_dense(cx, cy, dx, dy, keep, guide, op)
+    mask = n > 2e-30
+    for got, want in ((flow[0], u), (flow[1], v)):  # the FP32 stages' bound, 1e-4 relative
+        err = np.abs(got.cpu().numpy().astype(np.float64) - want)
+        assert (err <= 1e-4 * (np.abs(want) + 1.0))[mask].all()
+    assert (np.abs(nt.cpu().numpy() - n) <= 1e-4 * (np.abs(n) + 1.0)).all()
