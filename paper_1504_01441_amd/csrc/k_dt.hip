@@ -27,6 +27,8 @@
 //  k_dt_col: one workgroup per strip of 2-8 columns over the full height, as
 //          128 or 256 segments per column held in registers; the records are read
 //          and written once per pass. The last pass writes F (and N~) instead.
+#include <algorithm>
+
 #include "lnr_device.h"
 #include "lnr_internal.h"
 
@@ -222,19 +224,15 @@ __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "mem
 // causal sweep, scans without LDS round trips and the staging without
 // registers leave 27 (8 MP at an odd width, staged by dwords: 80 -> 44).
 template <int SEG, int NT, bool FIRST>
-__global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
-                                                const uint8_t* __restrict__ guide, int W, int H,
-                                                const double* __restrict__ coef,
-                                                const int32_t* __restrict__ cxy,
-                                                const int32_t* __restrict__ disp,
-                                                const uint8_t* __restrict__ flags, int ntx,
-                                                int nty, int tile,
-                                                uint8_t* __restrict__ rowflag) {
-  extern __shared__ __align__(16) float sm[];
-  __shared__ double cf[256];
-  __shared__ Aff wt[NT / 64];
+__device__ __forceinline__ void row_pass_of(int y, Rec* __restrict__ maps,
+                                            const uint8_t* __restrict__ guide, int W, int H,
+                                            const double* cf, Aff* wt, float* sm,
+                                            const int32_t* __restrict__ cxy,
+                                            const int32_t* __restrict__ disp,
+                                            const uint8_t* __restrict__ flags, int ntx, int nty,
+                                            int tile, uint8_t* __restrict__ rowflag) {
   Rec* row = reinterpret_cast<Rec*>(sm);
-  const int y = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   const size_t ro = (size_t)y * W;
   if (FIRST) {
     // the row's samples (kept level-0 matches whose corner lies on it)
@@ -265,7 +263,6 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
       }
     }
   }
-  if (tid < 256) cf[tid] = coef[tid];
   // guide bytes of pixels xb - 1 .. xb + SEG as unaligned dwords, where those
   // stay inside the image, else one by one
   const int xb = tid * SEG;
@@ -361,6 +358,36 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
   for (int x = tid; x < W; x += NT) maps[ro + x] = row[x];
 }
 
+template <int SEG, int NT, bool FIRST>
+__global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
+                                                const uint8_t* __restrict__ guide, int W, int H,
+                                                const double* __restrict__ coef,
+                                                const int32_t* __restrict__ cxy,
+                                                const int32_t* __restrict__ disp,
+                                                const uint8_t* __restrict__ flags, int ntx,
+                                                int nty, int tile,
+                                                uint8_t* __restrict__ rowflag) {
+  extern __shared__ __align__(16) float sm[];
+  __shared__ double cf[256];
+  __shared__ Aff wt[NT / 64];
+  if (threadIdx.x < 256) cf[threadIdx.x] = coef[threadIdx.x];
+  if (FIRST) {
+    // several rows per block: most hold no sample and end at once. The rows
+    // are dealt by their place within the tiles first, since the corners lie
+    // on the few rows around the tiles' centres.
+    const int nr = (H + tile - 1) / tile;
+    for (int i = blockIdx.x; i < nr * tile; i += gridDim.x) {
+      const int y = i % nr * tile + i / nr;
+      if (y < H)
+        row_pass_of<SEG, NT, true>(y, maps, guide, W, H, cf, wt, sm, cxy, disp, flags, ntx, nty,
+                                   tile, rowflag);
+    }
+  } else {
+    row_pass_of<SEG, NT, false>(blockIdx.x, maps, guide, W, H, cf, wt, sm, cxy, disp, flags, ntx,
+                                nty, tile, rowflag);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Vertical pass: a block covers NCOL adjacent columns over the full height as
 // NSEG segments of L rows (NCOL * NSEG = 512 threads); each thread keeps its
@@ -374,7 +401,7 @@ __device__ inline void seg_carry(const Aff& v, Aff* wt, double& c0, double& c1, 
 }
 
 template <int L, int NCOL, int NSEG, bool LAST>
-__global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
+__global__ __launch_bounds__(NCOL * NSEG, 4) void k_dt_col(Rec* __restrict__ maps,
                                                         const uint8_t* __restrict__ gt, int hp,
                                                         int W, int H,
                                                         const double* __restrict__ coef,
@@ -395,22 +422,18 @@ __global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
   for (int i = tid; i < 257; i += NCOL * NSEG) cf[i] = i < 256 ? coef[i] : 0.0;
   __syncthreads();
   // guide bytes of rows r0 .. r0+L-1, four per register, as one aligned load
-  // from the column-major copy (r0 is a multiple of L, a multiple of 8, and
+  // from the column-major copy (r0 is a multiple of L, a multiple of 4, and
   // the copy's rows run past r0 + L), plus the rows r0-1 and r0+L
-  static_assert(L % 8 == 0, "segments are whole 8-byte guide words");
+  static_assert(L % 4 == 0, "segments are whole 4-byte guide words");
   constexpr int NG = L / 4;
   uint32_t gpk[NG];
   uint32_t gup = 0u, gdn = 0u;
   const bool seg_in = act && r0 < H;
   const uint8_t* gcol = gt + (size_t)col * hp;
   if (seg_in) {
-    const uint2* gw = reinterpret_cast<const uint2*>(gcol + r0);
+    const uint32_t* gw = reinterpret_cast<const uint32_t*>(gcol + r0);
 #pragma unroll
-    for (int q = 0; q < NG / 2; ++q) {
-      const uint2 v = gw[q];
-      gpk[2 * q] = v.x;
-      gpk[2 * q + 1] = v.y;
-    }
+    for (int q = 0; q < NG; ++q) gpk[q] = gw[q];
     if (r0 > 0) gup = gcol[r0 - 1];
     if (r0 + L < H) gdn = gcol[r0 + L];
   } else {
@@ -418,19 +441,15 @@ __global__ __launch_bounds__(NCOL * NSEG) void k_dt_col(Rec* __restrict__ maps,
     for (int q = 0; q < NG; ++q) gpk[q] = 0u;
   }
   // first pass: the rows the row pass left at zero are not read (their
-  // flags, as for the guide, one aligned load per 8 rows; the flag buffer
-  // runs past the last row)
+  // flags, as for the guide, aligned loads; the flag buffer runs past the
+  // last row)
   uint32_t rf[NG];
 #pragma unroll
   for (int q = 0; q < NG; ++q) rf[q] = 0x01010101u;
   if (rowflag) {
-    const uint2* rw = reinterpret_cast<const uint2*>(rowflag + r0);
+    const uint32_t* rw = reinterpret_cast<const uint32_t*>(rowflag + r0);
 #pragma unroll
-    for (int q = 0; q < NG / 2; ++q) {
-      const uint2 v = seg_in ? rw[q] : uint2{0u, 0u};
-      rf[2 * q] = v.x;
-      rf[2 * q + 1] = v.y;
-    }
+    for (int q = 0; q < NG; ++q) rf[q] = seg_in ? rw[q] : 0u;
   }
   // the segment is held as float (as stored between passes); every recursion
   // step and carry is computed in double precision
@@ -546,8 +565,13 @@ hipError_t launch_row(bool first, Rec* maps, const uint8_t* guide, int W, int H,
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
+  // first pass: as many rows per block as leave every block resident at once
+  // (16 waves per CU, which the registers of every shape allow, and the LDS);
+  // one row per block took two rounds at 5 MP: 23 us against 15
+  const int per_cu = (int)std::min<size_t>(1024 / NT, 160 * 1024 / (lds + 3072));
+  const int resident = 256 * std::max(per_cu, 1), turns = (H + resident - 1) / resident;
   if (first)
-    LNR_LAUNCH((k_dt_row<SEG, NT, true>), dim3(H), dim3(NT), lds, st, maps, guide, W, H, cf, cxy,
+    LNR_LAUNCH((k_dt_row<SEG, NT, true>), dim3((H + turns - 1) / turns), dim3(NT), lds, st, maps, guide, W, H, cf, cxy,
                disp, flags, ntx, nty, tile, rowflag);
   else
     LNR_LAUNCH((k_dt_row<SEG, NT, false>), dim3(H), dim3(NT), lds, st, maps, guide, W, H, cf, cxy,
@@ -596,11 +620,16 @@ hipError_t row_pass(const DtShape& s, bool first, Rec* maps, const uint8_t* guid
 hipError_t col_pass(const DtShape& s, bool last, Rec* maps, const uint8_t* gt, int W, int H,
                     const double* cf, float* flow, float* ntilde, double nmin,
                     const uint8_t* rowflag, hipStream_t st) {
+  // The shape's rows per segment are the most it may take; the fewest that
+  // cover the height leave no segment idle (5 MP's 1944 rows fill 122 of 128
+  // segments of 16, but 1440 would fill 90: of 12, all 120).
+  const int need = (H + s.nseg - 1) / s.nseg, l = min(s.l, (need + 3) / 4 * 4);
 #define COL(L, NC, NS)                                                                       \
-  if (s.l == L && s.ncol == NC && s.nseg == NS)                                               \
+  if (l == L && s.ncol == NC && s.nseg == NS)                                                 \
     return launch_col<L, NC, NS>(last, maps, gt, W, H, cf, flow, ntilde, nmin, rowflag, st);
-  COL(8, 8, 128) COL(8, 4, 128) COL(16, 4, 128) COL(8, 2, 256) COL(24, 4, 128)
-  COL(16, 2, 256) COL(24, 2, 256)
+  COL(4, 8, 128) COL(8, 8, 128)
+  COL(4, 4, 128) COL(8, 4, 128) COL(12, 4, 128) COL(16, 4, 128) COL(20, 4, 128) COL(24, 4, 128)
+  COL(4, 2, 256) COL(8, 2, 256) COL(12, 2, 256) COL(16, 2, 256) COL(20, 2, 256) COL(24, 2, 256)
 #undef COL
   return hipErrorInvalidValue;
 }
