@@ -24,7 +24,7 @@
 //          row that holds no sample stays exactly zero through it, so that
 //          pass writes only a row flag for it, and the first column pass
 //          reads the records of flagged rows only (the rest are zeros).
-//  k_dt_col: one workgroup per strip of 2-8 columns over the full height, as
+//  k_dt_col: one workgroup per strip of 4 or 8 columns over the full height, as
 //          128 or 256 segments per column held in registers; the records are read
 //          and written once per pass. The last pass writes F (and N~) instead.
 #include <algorithm>
@@ -222,7 +222,7 @@ __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "mem
 // the two carries, a few blocks per CU overlapping each other's. Of 37 us at
 // 5 MP, fused multiply-adds, the anti-causal composition folded into the
 // causal sweep, scans without LDS round trips and the staging without
-// registers leave 27 (8 MP at an odd width, staged by dwords: 80 -> 44).
+// registers leave 26 (8 MP at an odd width, staged by dwords: 80 -> 44).
 template <int SEG, int NT, bool FIRST>
 __device__ __forceinline__ void row_pass_of(int y, Rec* __restrict__ maps,
                                             const uint8_t* __restrict__ guide, int W, int H,
@@ -390,11 +390,14 @@ __global__ __launch_bounds__(NT) void k_dt_row(Rec* __restrict__ maps,
 
 // ---------------------------------------------------------------------------
 // Vertical pass: a block covers NCOL adjacent columns over the full height as
-// NSEG segments of L rows (NCOL * NSEG = 512 threads); each thread keeps its
+// NSEG segments of L rows (512 or 1024 threads); each thread keeps its
 // segment of one column in registers, so the maps are read and written once.
 // Segments of a column sit NCOL lanes apart. The segments' registers bound the
 // blocks in flight (two per CU at L = 16), so the sweeps are written not to
-// keep their double values: 42 -> 36 us per pass at 5 MP, the last 52 -> 41.
+// keep their double values: 42 -> 35 us per pass at 5 MP, the last 52 -> 41.
+// Runs of 48 bytes per row cost more than the recursion: a copy with this
+// access takes 34 us, with runs of 192 bytes 21, but a block of 16 such
+// columns would not fit a CU's registers.
 template <int NCOL, int NSEG, bool FWD>
 __device__ inline void seg_carry(const Aff& v, Aff* wt, double& c0, double& c1, double& c2) {
   line_carry<NCOL, NSEG * NCOL / 64, FWD>(v, wt, c0, c1, c2);
@@ -624,12 +627,16 @@ hipError_t col_pass(const DtShape& s, bool last, Rec* maps, const uint8_t* gt, i
   // cover the height leave no segment idle (5 MP's 1944 rows fill 122 of 128
   // segments of 16, but 1440 would fill 90: of 12, all 120).
   const int need = (H + s.nseg - 1) / s.nseg, l = min(s.l, (need + 3) / 4 * 4);
-#define COL(L, NC, NS)                                                                       \
+  // (the shapes of two columns by 256 segments run as blocks of four: runs of
+  // 48 bytes instead of 24 per row, 3000 x 4000: 85 -> 72 us, last 139 -> 103)
+#define COL(L, NC, NS, BLOCK)                                                                \
   if (l == L && s.ncol == NC && s.nseg == NS)                                                 \
-    return launch_col<L, NC, NS>(last, maps, gt, W, H, cf, flow, ntilde, nmin, rowflag, st);
-  COL(4, 8, 128) COL(8, 8, 128)
-  COL(4, 4, 128) COL(8, 4, 128) COL(12, 4, 128) COL(16, 4, 128) COL(20, 4, 128) COL(24, 4, 128)
-  COL(4, 2, 256) COL(8, 2, 256) COL(12, 2, 256) COL(16, 2, 256) COL(20, 2, 256) COL(24, 2, 256)
+    return launch_col<L, BLOCK, NS>(last, maps, gt, W, H, cf, flow, ntilde, nmin, rowflag, st);
+  COL(4, 8, 128, 8) COL(8, 8, 128, 8)
+  COL(4, 4, 128, 4) COL(8, 4, 128, 4) COL(12, 4, 128, 4) COL(16, 4, 128, 4) COL(20, 4, 128, 4)
+  COL(24, 4, 128, 4)
+  COL(4, 2, 256, 4) COL(8, 2, 256, 4) COL(12, 2, 256, 4) COL(16, 2, 256, 4) COL(20, 2, 256, 4)
+  COL(24, 2, 256, 4)
 #undef COL
   return hipErrorInvalidValue;
 }
