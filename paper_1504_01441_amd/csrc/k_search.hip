@@ -1082,6 +1082,22 @@ int search_split_candidates(int R, const SearchCfg& c, int* out, int max) {
   return n;
 }
 
+// The shape of a search that no caller tuned or pinned: the matrix cores from
+// radius 11 on, and from radius 8 where the level has at least 2048 tiles,
+// with patch-row groups for about 2400 waves in all; else (0) 8 candidates
+// per lane with make_shape's split. Measured on whole frames, us, against
+// the best 8-candidate shape: radius 16 15 (300 tiles, two groups) / 18, 21
+// (1200, one) / 28, 52 (4860) / 76, 102 (11625) / 160; radius 10 27 / 31 at
+// 3072 tiles but 17.7 / 17.4 at 1200; radius 32 28 / 32 at 300.
+int auto_shape(int R, const SearchCfg& c, long long ntiles) {
+  const int nb = (2 * R + 16) / 16;  // blocks of 16 candidates
+  if (R < 8 || (R < 11 && ntiles < 2048)) return 0;
+  int split = (int)((2400 + ntiles * nb / 2) / std::max(ntiles * nb, 1ll));
+  split = std::min(std::max(split, 1), 3);
+  while (split > 1 && !search_shape_fits(R, c, split | kSearchMfma)) --split;
+  return search_shape_fits(R, c, split | kSearchMfma) ? split | kSearchMfma : 0;
+}
+
 hipError_t launch_tile_lists(const uint8_t* flags, const uint8_t* mode, int n, int* lists,
                              int* counts, hipStream_t st) {
   LNR_LAUNCH(k_tile_lists, dim3(1), dim3(1024), 0, st, flags, mode, n, lists, counts);
@@ -1126,6 +1142,7 @@ hipError_t launch_search(const SearchJob& J, int nty, int R, const SearchCfg& c,
   if (J.Hwarp && role != kRoleCoarse) return hipErrorInvalidValue;  // no warp in that kernel
   // a tuned choice: the split (1..7), plus kSearchKx12 (12 candidates per
   // lane) or kSearchMfma (matrix-core cross terms)
+  if (!split) split = auto_shape(R, c, ntiles);
   const int kx = shape_kx(split, 8);
   // (a shape that does not fit these patch and corner parameters: the
   // automatic split)
@@ -1174,6 +1191,10 @@ hipError_t launch_search_work(const SearchJob* jobs, const SearchWork& wk, int R
   if (grid < 1) return hipSuccess;
   // a single job with a warp needs the kernel that carries it
   if (one && one->Hwarp && !(warp && visit == kVisitSearchAll)) return hipErrorInvalidValue;
+  if (kx < 0) {  // automatic
+    kx = 8;
+    if (!split) split = auto_shape(R, c, grid);
+  }
   kx = shape_kx(split, kx);  // flags in a tuned shape code take precedence
   if ((split & kSearchSplitMask) && !search_shape_fits(R, c, split)) split = 0;
   split &= kSearchSplitMask;

@@ -605,7 +605,7 @@ lnr_status enqueue_pair_levels(lnr_ctx* ctx, const lnr_frame* ref, const lnr_fra
       wf.njobs = 1;
       wf.list = lists + 2 * nt;
       wf.count = counts + 2;
-      LNR_HIP(launch_search_work(nullptr, wf, R, cfg, kVisitKnownCorner, 1, tuned(L.w, L.h, R), 8,
+      LNR_HIP(launch_search_work(nullptr, wf, R, cfg, kVisitKnownCorner, 1, tuned(L.w, L.h, R), -1,
                                  nt, st, &Jc));
     } else {
       const SearchJob J = search_job(
@@ -1430,7 +1430,7 @@ lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_fra
   push_bytes(shape, p, sizeof(*p));
   for (int i = 0; i < n; ++i)
     shape.push_back(((uint64_t)refs[i].width << 32) | (uint32_t)refs[i].height);
-  int K = n < 4 ? n : 4, kx = 8;
+  int K = n < 4 ? n : 4, kx = -1;
   // the level-synchronous batch's job tables (device pointers into the
   // workspace, which must not move after they are written)
   auto upload_eager_tables = [&]() -> lnr_status {
@@ -1492,11 +1492,11 @@ lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_fra
       const int k = cand[c];
       if (k > n) break;
       float ms = 0.f;
-      if ((s = time_one(k, 8, &ms)) != LNR_OK) return s;
+      if ((s = time_one(k, -1, &ms)) != LNR_OK) return s;
       if (c == 0 || ms < best) { best = ms; K = k; }
     }
     if (levels)
-      for (const int kxx : {12, 0}) {  // 12 candidates per lane, the matrix cores
+      for (const int kxx : {8, 12, 0}) {  // 8 or 12 candidates per lane, the matrix cores
         float ms = 0.f;
         if ((s = time_one(K, kxx, &ms)) != LNR_OK) return s;
         if (ms < best) { best = ms; kx = kxx; }

@@ -148,7 +148,8 @@ hipError_t launch_search(const SearchJob& J, int nty, int R, const SearchCfg& c,
                          hipStream_t st, const uint8_t* mode = nullptr, int want = 0,
                          int split = 0);
 // `grid` workgroups, one per item of the work (at least the number of items);
-// kx: candidates per lane (8 or 12); jobs null: the single job `one` (by
+// kx: candidates per lane (8 or 12), 0 the matrix cores, -1 automatic (by the
+// radius and the items, unless split is a tuned shape); jobs null: the single job `one` (by
 // value), whose tiles the work's items are; warp: the jobs may warp their
 // windows on the fly (Hwarp; only with kVisitSearchAll)
 hipError_t launch_search_work(const SearchJob* jobs, const SearchWork& wk, int R,
