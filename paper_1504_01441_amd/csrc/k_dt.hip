@@ -194,10 +194,6 @@ __device__ inline void pace(int j) {
   if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
 }
 
-struct __attribute__((packed)) UnalignedU32 {
-  uint32_t v;
-};
-
 // 4 or 16 bytes per lane from g straight into LDS, lane after lane from l
 // (the wave's base) on; the wave must wait for its memory counter before it or
 // another wave reads them. (12 bytes per lane would land 16 apart.)

@@ -58,11 +58,12 @@ namespace {
 constexpr int NW = 6;        // patch row dwords (2P+1 <= 24)
 constexpr int kMaxNB = 5;    // blocks of 16 candidates per axis (2R + 1 <= 65)
 
-__device__ inline long long q8(double s) {
+// floor(256 s + 1/2), clamped far outside any image (NaN too)
+__device__ inline int q8(double s) {
   double q = floor(s * 256.0 + 0.5);
   if (!(q > -1073741824.0)) q = -1073741824.0;
   if (q > 1073741824.0) q = 1073741824.0;
-  return (long long)q;
+  return (int)q;
 }
 
 // The Q8 sample of output pixel (x, y): the four clamped taps and the Q8
@@ -72,38 +73,84 @@ struct Q8Tap {
   uint32_t fx, fy;
 };
 
-__device__ inline Q8Tap warp_tap(const double* hp, int w, int h, int x, int y) {
+// PLAIN: with plain divisions (also where the tile's staging is bound by its
+// registers: 15.1 us per coarse VGA search against 17); else from the shared
+// reciprocal, with no branch so that the samples of one thread overlap, and ok
+// cleared where den is too near 0 for that.
+template <bool PLAIN>
+__device__ inline Q8Tap warp_tap(const double* hp, int w, int h, int x, int y, bool& ok) {
   const double X = (double)x, Y = (double)y;
   const double den = (hp[6] * X + hp[7] * Y) + hp[8];
-  const double sx = ((hp[0] * X + hp[1] * Y) + hp[2]) / den;
-  const double sy = ((hp[3] * X + hp[4] * Y) + hp[5]) / den;
-  const long long QX = q8(sx), QY = q8(sy);
-  const long long ix = QX >> 8, iy = QY >> 8;
+  const double nx = (hp[0] * X + hp[1] * Y) + hp[2], ny = (hp[3] * X + hp[4] * Y) + hp[5];
+  double sx, sy;
+  if constexpr (PLAIN) {
+    sx = nx / den;
+    sy = ny / den;
+  } else {
+    recip_quotients(nx, ny, den, sx, sy);
+    ok = ok && fabs(den) > 0x1p-400;
+  }
+  const int QX = q8(sx), QY = q8(sy);
+  const int ix = QX >> 8, iy = QY >> 8;
   Q8Tap t;
   t.fx = (uint32_t)(QX & 255);
   t.fy = (uint32_t)(QY & 255);
-  t.x0 = (int)(ix < 0 ? 0 : (ix > w - 1 ? w - 1 : ix));
-  t.x1 = (int)(ix + 1 < 0 ? 0 : (ix + 1 > w - 1 ? w - 1 : ix + 1));
-  t.y0 = (int)(iy < 0 ? 0 : (iy > h - 1 ? h - 1 : iy));
-  t.y1 = (int)(iy + 1 < 0 ? 0 : (iy + 1 > h - 1 ? h - 1 : iy + 1));
+  t.x0 = min(max(ix, 0), w - 1);
+  t.x1 = min(max(ix + 1, 0), w - 1);
+  t.y0 = min(max(iy, 0), h - 1);
+  t.y1 = min(max(iy + 1, 0), h - 1);
   return t;
 }
 
-__device__ inline uint32_t blend_q8(uint32_t p00, uint32_t p10, uint32_t p01, uint32_t p11,
-                                    uint32_t fx, uint32_t fy) {
-  const uint32_t acc = (256 - fx) * (256 - fy) * p00 + fx * (256 - fy) * p10 +
-                       (256 - fx) * fy * p01 + fx * fy * p11;
+struct Q8Quad {
+  uint32_t p00, p10, p01, p11;
+};
+
+// the four taps, two bytes of each row in one load (levels are narrower than
+// 2^31 bytes in all, so the offsets are 32 bits)
+__device__ inline Q8Quad load_quad(const uint8_t* __restrict__ src, int w, const Q8Tap& t) {
+  const uint32_t r0 = (uint32_t)t.y0 * (uint32_t)w, r1 = (uint32_t)t.y1 * (uint32_t)w;
+  if (w < 2) return Q8Quad{src[r0], src[r0], src[r1], src[r1]};
+  const uint32_t b = pair_base(t.x0, w);
+  const uint32_t a = load_pair(src + (r0 + b)), c = load_pair(src + (r1 + b));
+  const int s0 = t.x0 == (int)b ? 0 : 8, s1 = t.x1 == (int)b ? 0 : 8;
+  return Q8Quad{(a >> s0) & 255u, (a >> s1) & 255u, (c >> s0) & 255u, (c >> s1) & 255u};
+}
+
+__device__ inline uint32_t blend_q8(const Q8Quad& p, uint32_t fx, uint32_t fy) {
+  const uint32_t acc = (256 - fx) * (256 - fy) * p.p00 + fx * (256 - fy) * p.p10 +
+                       (256 - fx) * fy * p.p01 + fx * fy * p.p11;
   return (acc + 32768u) >> 16;
 }
 
-__device__ inline uint32_t warp_px(const uint8_t* __restrict__ src, int w, int h,
-                                   const double* hp, int x, int y) {
-  const Q8Tap t = warp_tap(hp, w, h, x, y);
-  return blend_q8(src[(size_t)t.y0 * w + t.x0], src[(size_t)t.y0 * w + t.x1],
-                  src[(size_t)t.y1 * w + t.x0], src[(size_t)t.y1 * w + t.x1], t.fx, t.fy);
+// Output pixels x .. x + 3 of row y (those inside the level), at row + x: the
+// sample positions first, then all eight loads in flight, then the blends.
+__device__ inline void warp_four(const uint8_t* __restrict__ src, int w, int h, const double* hp,
+                                 int x, int y, uint8_t* row) {
+  bool ok = moderate(hp);
+  Q8Tap t[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) t[k] = warp_tap<false>(hp, w, h, min(x + k, w - 1), y, ok);
+  if (!__all(ok))
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = warp_tap<true>(hp, w, h, min(x + k, w - 1), y, ok);
+  Q8Quad p[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) p[k] = load_quad(src, w, t[k]);
+  uint32_t v = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v |= blend_q8(p[k], t[k].fx, t[k].fy) << (8 * k);
+  if (x + 4 <= w && ((reinterpret_cast<uintptr_t>(row + x) & 3u) == 0)) {
+    *reinterpret_cast<uint32_t*>(row + x) = v;
+  } else {
+    for (int k = 0; k < 4 && x + k < w; ++k) row[x + k] = (uint8_t)(v >> (8 * k));
+  }
 }
 
-// Four consecutive pixels per thread, one 32-bit store when the row allows it.
+// Four consecutive pixels per thread, one 32-bit store when the row allows
+// it. Bound by its double-precision instructions: with byte gathers, two
+// divisions per pixel and 64-bit coordinates 25 us at 5 MP, now 20 (four rows
+// per thread: 20 too, and 8 us instead of 5 at VGA).
 // Block (0, 0) also clears the level's valid-match bits vbz[0, nwords) (the
 // search that follows sets them).
 __global__ __launch_bounds__(256) void k_warp_q8(const uint8_t* __restrict__ src, int w, int h,
@@ -119,16 +166,8 @@ __global__ __launch_bounds__(256) void k_warp_q8(const uint8_t* __restrict__ src
   if (x >= w) return;
   // every thread forms the pixel homography itself (uniform, no barrier)
   double hp[9];
-  pixel_homography(Hn, w, h, hp);
-  uint8_t* row = out + (size_t)y * w;
-  if (x + 4 <= w && ((reinterpret_cast<uintptr_t>(row + x) & 3u) == 0)) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v |= warp_px(src, w, h, hp, x + k, y) << (8 * k);
-    *reinterpret_cast<uint32_t*>(row + x) = v;
-  } else {
-    for (int k = 0; k < 4 && x + k < w; ++k) row[x + k] = (uint8_t)warp_px(src, w, h, hp, x + k, y);
-  }
+  pixel_homography_sparse(Hn, w, h, hp);
+  warp_four(src, w, h, hp, x, y, out + (size_t)y * w);
 }
 
 // k_warp_q8 for a table of jobs: block b covers run b % nxb (1024 pixels) of
@@ -152,17 +191,8 @@ __global__ __launch_bounds__(256) void k_warp_jobs(const WarpJob* __restrict__ j
   const int x = 4 * (bx * blockDim.x + threadIdx.x);
   if (x >= J.w) return;
   double hp[9];
-  pixel_homography(J.Hn, J.w, J.h, hp);
-  uint8_t* row = J.out + (size_t)y * J.w;
-  if (x + 4 <= J.w && ((reinterpret_cast<uintptr_t>(row + x) & 3u) == 0)) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v |= warp_px(J.src, J.w, J.h, hp, x + k, y) << (8 * k);
-    *reinterpret_cast<uint32_t*>(row + x) = v;
-  } else {
-    for (int k = 0; k < 4 && x + k < J.w; ++k)
-      row[x + k] = (uint8_t)warp_px(J.src, J.w, J.h, hp, x + k, y);
-  }
+  pixel_homography_sparse(J.Hn, J.w, J.h, hp);
+  warp_four(J.src, J.w, J.h, hp, x, y, J.out + (size_t)y * J.w);
 }
 
 // Copy rows [y0, y0 + nrows) x bytes [x0, x0 + 4 * ndw) of an 8-bit image
@@ -261,32 +291,28 @@ __device__ inline void stage_warped(const uint8_t* __restrict__ src, int w, int 
   const int total = nrows * ndw * 4;
   for (int i0 = tid; i0 < total; i0 += U * nt) {
     Q8Tap t[U];
-    bool in[U];
+    bool in[U], ok = true;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + u * nt;
       const int r = i / (4 * ndw), b = i % (4 * ndw);
       const int gy = y0 + r, gx = x0 + b;
       in[u] = i < total && gy >= 0 && gy < h && gx >= 0 && gx < w;
-      t[u] = warp_tap(hp, w, h, in[u] ? gx : 0, in[u] ? gy : 0);
+      t[u] = warp_tap<true>(hp, w, h, in[u] ? gx : 0, in[u] ? gy : 0, ok);
     }
-    uint32_t p[U][4];
+    Q8Quad p[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint8_t* r0 = src + (size_t)t[u].y0 * w;
       const uint8_t* r1 = src + (size_t)t[u].y1 * w;
-      p[u][0] = r0[t[u].x0];
-      p[u][1] = r0[t[u].x1];
-      p[u][2] = r1[t[u].x0];
-      p[u][3] = r1[t[u].x1];
+      p[u] = Q8Quad{r0[t[u].x0], r0[t[u].x1], r1[t[u].x0], r1[t[u].x1]};
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + u * nt;
       if (i >= total) break;
       const int r = i / (4 * ndw), b = i % (4 * ndw);
-      const uint32_t v = in[u] ? blend_q8(p[u][0], p[u][1], p[u][2], p[u][3], t[u].fx, t[u].fy)
-                               : 0u;
+      const uint32_t v = in[u] ? blend_q8(p[u], t[u].fx, t[u].fy) : 0u;
       dst[r * ldst + b] = (uint8_t)(v ^ flip);
     }
   }

@@ -3,6 +3,7 @@
 // results whose rounding decides an integer are reproducible.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace lnr {
 
@@ -44,6 +45,68 @@ __device__ inline void pixel_homography(const double* H, int w, int h, double* H
   double T[9];
   mat3_mul(H, C, T);
   mat3_mul(B, T, Hp);
+}
+
+// pixel_homography with the products written out without the terms that
+// multiply by 0 (they add nothing to a finite sum); a homography that is not
+// finite takes the full products. For the warps, where every thread forms it
+// (the search's kernels, short of registers, are slower with it).
+__device__ inline void pixel_homography_sparse(const double* H, int w, int h, double* Hp) {
+  double all = 0.0;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) all += fabs(H[i]);
+  if (!(all < 0x1p1000)) {
+    pixel_homography(H, w, h, Hp);
+    return;
+  }
+  const double W = (double)w, cx = (double)(w - 1), cy = (double)(h - 1);
+  double T[9];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    T[3 * i] = H[3 * i] * 2.0;
+    T[3 * i + 1] = H[3 * i + 1] * 2.0;
+    T[3 * i + 2] = (H[3 * i] * -cx + H[3 * i + 1] * -cy) + H[3 * i + 2] * W;
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    Hp[j] = W * T[j] + cx * T[6 + j];
+    Hp[3 + j] = W * T[3 + j] + cy * T[6 + j];
+    Hp[6 + j] = 2.0 * T[6 + j];
+  }
+}
+
+// Whether the products of these coefficients and pixel coordinates stay clear
+// of the exponent range's upper end (not so for NaN), for recip_quotients.
+__device__ inline bool moderate(const double* hp) {
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) ok = ok && fabs(hp[i]) < 0x1p400;
+  return ok;
+}
+
+// nx / den and ny / den; fast: the operands' upper ends are known to be
+// moderate. A den near 0 (or NaN) is divided plainly.
+__device__ inline void div2(double nx, double ny, double den, bool fast, double& qx, double& qy) {
+  if (fast && fabs(den) > 0x1p-400) {
+    recip_quotients(nx, ny, den, qx, qy);
+  } else {
+    qx = nx / den;
+    qy = ny / den;
+  }
+}
+
+struct __attribute__((packed)) UnalignedU16 {
+  uint16_t v;
+};
+struct __attribute__((packed)) UnalignedU32 {
+  uint32_t v;
+};
+
+// The bytes at x0 and x1 of a row of at least two: both lie in the two bytes
+// from b on, one load.
+__device__ inline uint32_t pair_base(int x0, int n) { return (uint32_t)min(x0, n - 2); }
+__device__ inline uint32_t load_pair(const uint8_t* p) {
+  return reinterpret_cast<const UnalignedU16*>(p)->v;
 }
 
 }  // namespace lnr

@@ -46,6 +46,54 @@ def test_training_step_at_block_edges(lnr, ctx, n):
     assert torch.equal(after, lnr.proposal_forward(ctx, xb))
 
 
+def _homographies(w, h):
+    """By kind: ordinary; a denominator that is 0 on a line through the frame;
+    entries beyond (and far below) what the shared reciprocal takes; not finite."""
+    a = np.array([[0.97, -0.05, 0.04], [0.06, 1.02, -0.03], [0.02, -0.03, 1.0]])
+    cross = np.array([[1.0, 0.1, 0.0], [0.0, 1.0, 0.1], [1.0, 0.0, 0.0]])
+    odd = a.copy()
+    odd[0, 1] = np.nan
+    return {"plain": a, "cross": cross, "huge": a * 1e150, "tiny": a * 1e-150, "nan": odd}
+
+
+# the narrowest rows, whose two taps are not two bytes, rows that leave a
+# thread 1, 2 and 3 of its 4 pixels, rows past one block
+@pytest.mark.parametrize("w,h", [(1, 1), (1, 5), (2, 3), (3, 2), (5, 4), (1026, 3), (6, 40)])
+def test_q8_warp_edges(lnr, ctx, w, h):
+    img = np.random.default_rng(w * 7 + h).integers(0, 256, (h, w)).astype(np.uint8)
+    for kind, H in _homographies(w, h).items():
+        got = lnr.stage_warp_q8(ctx, torch.from_numpy(img).cuda(), torch.from_numpy(H.reshape(9)))
+        want = oracle.warp_q8(img, oracle.pixel_homography(H, w, h))
+        assert np.array_equal(got.cpu().numpy(), want), kind
+
+
+# luma rows of one byte, chroma rows of one sample and two, one row per thread
+# and (from 2 MP) four, with two rows left over
+@pytest.mark.parametrize("fmt", ["y8", "i420", "nv12"])
+@pytest.mark.parametrize("w,h", [(1, 3), (2, 2), (4, 6), (258, 6), (2048, 1030)])
+def test_backward_warp_edges(lnr, ctx, w, h, fmt):
+    if fmt != "y8" and w % 2:
+        pytest.skip("4:2:0 frames are even")
+    rng = np.random.default_rng(w + h)
+    b = lambda *s: rng.integers(0, 256, s).astype(np.uint8)
+    y, yeq, u, v = b(h, w), b(h, w), b(h // 2, w // 2), b(h // 2, w // 2)
+    if fmt == "y8":
+        u = v = None
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    f = (lnr.Frame.nv12_from_numpy(y, np.stack([u, v], 2).reshape(h // 2, w)) if fmt == "nv12"
+         else lnr.Frame.from_numpy(y, u, v))
+    flow = rng.uniform(-3, 3, (2, h, w)).astype(np.float32)
+    flow[0, h // 2, w // 2] = 1e30  # far outside, on either side
+    flow[1, 0, 0] = -1e38
+    for kind, H in _homographies(w, h).items():
+        img, yw = lnr.stage_backward_warp(ctx, f, t(yeq), torch.from_numpy(H.reshape(9)), t(flow))
+        want, ywant = oracle.backward_warp(y, u, v, yeq, oracle.pixel_homography(H, w, h),
+                                           flow[0].astype(np.float64), flow[1].astype(np.float64))
+        # FP32 samples of values up to 2, the bound of the FP32 stages
+        assert (np.abs(img.cpu().numpy() - want) <= 1e-4 * (np.abs(want) + 1.0)).all(), kind
+        assert (np.abs(yw.cpu().numpy() - ywant) <= 1e-4 * (ywant + 1.0)).all(), kind
+
+
 # one word / two; the narrow and the wide hypothesis blocks; the last size of
 # one fit block and the first of several; more iterations than blocks take at
 # once, and counts that leave a group short; few matches with repeated draws
