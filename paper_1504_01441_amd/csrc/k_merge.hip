@@ -39,6 +39,12 @@ struct SsimWin {
   double g[2 * kSsimMaxR + 1];
 };
 
+// the warped frames' planes and their maps, one frame per blockIdx.z
+struct SsimMaps {
+  const float* b[16];
+  float* out[16];
+};
+
 // One block: kSsimTH output rows by 256 - 2R output columns. SSIM needs the
 // Gaussian sums of x, y, xy and of x^2 + y^2 (only the sum of the two
 // variances enters it), accumulated in double precision: SSIM divides
@@ -52,11 +58,15 @@ struct SsimWin {
 //  2. the vertical sums go to LDS; thread t takes output columns 2t and 2t+1
 //     of half the tile's rows, reading the shared window as aligned pairs of
 //     doubles (16-byte LDS reads, half the reads of one column per thread).
+// Bound by the double-precision units (about 140 instructions per pixel) and
+// the LDS reads beside them; a 5 MP map took 51 us with separate multiplies
+// and adds, takes 32 with fused ones and 32-bit load offsets; two 1 MP maps,
+// which are one launch, 34 -> 20.
 template <int R>
-__global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a,
-                                              const float* __restrict__ b, int W, int H,
-                                              SsimWin win, double c1, double c2,
-                                              float* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a, SsimMaps maps, int W,
+                                              int H, SsimWin win, double c1, double c2) {
+  const float* __restrict__ b = maps.b[blockIdx.z];
+  float* __restrict__ out = maps.out[blockIdx.z];
   constexpr int TW = 256 - 2 * R, NR = kSsimTH + 2 * R, NS = 4;
   static_assert(kSsimTH % 2 == 0, "two row halves");
   __shared__ double2 vs[NS][kSsimTH][128];  // column pairs of the vertical sums
@@ -69,9 +79,11 @@ __global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a,
     float pa[NR], pb[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {  // every load in flight before the sums
-      const size_t o = (size_t)min(max(oy - R + i, 0), H - 1) * W + gx;
-      pa[i] = a[o];
-      pb[i] = b[o];
+      // (32-bit byte offsets, since a plane has at most 2^26 pixels: 64-bit
+      // addresses of all the loads would cost a block per CU)
+      const uint32_t o = 4u * ((uint32_t)min(max(oy - R + i, 0), H - 1) * (uint32_t)W + (uint32_t)gx);
+      pa[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a) + o);
+      pb[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + o);
     }
     double acc[kSsimTH][NS];
 #pragma unroll
@@ -81,16 +93,16 @@ __global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a,
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const double p = pa[i], q = pb[i];
-      const double ss = p * p + q * q, pq = p * q;
+      const double ss = fma(p, p, q * q), pq = p * q;
 #pragma unroll
       for (int o = 0; o < kSsimTH; ++o) {
         const int k = i - o;  // tap of input row oy - R + i for output row oy + o
         if (k < 0 || k > 2 * R) continue;
         const double wd = win.g[k];
-        acc[o][0] += wd * p;
-        acc[o][1] += wd * q;
-        acc[o][2] += wd * ss;
-        acc[o][3] += wd * pq;
+        acc[o][0] = fma(wd, p, acc[o][0]);
+        acc[o][1] = fma(wd, q, acc[o][1]);
+        acc[o][2] = fma(wd, ss, acc[o][2]);
+        acc[o][3] = fma(wd, pq, acc[o][3]);
       }
     }
     double* vd = reinterpret_cast<double*>(vs);
@@ -120,12 +132,15 @@ __global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a,
         const double2 v = vs[t][o][pr + m];
         // output 2pr takes taps 2m (v.x) and 2m + 1 (v.y); output 2pr + 1
         // takes taps 2m - 1 (v.x) and 2m (v.y)
-        s0[t] += wl * v.x;
-        if (2 * m + 1 <= 2 * R) s0[t] += wr * v.y;
-        if (m > 0) s1[t] += wp * v.x;
-        s1[t] += wl * v.y;
+        s0[t] = fma(wl, v.x, s0[t]);
+        if (2 * m + 1 <= 2 * R) s0[t] = fma(wr, v.y, s0[t]);
+        if (m > 0) s1[t] = fma(wp, v.x, s1[t]);
+        s1[t] = fma(wl, v.y, s1[t]);
       }
     }
+    // (else the second column's sums are put off past the branch below and the
+    // window's values held for them: 106 registers, not 60, a block per CU less)
+    asm volatile("" : "+v"(s1[0]), "+v"(s1[1]), "+v"(s1[2]), "+v"(s1[3]));
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       if (c == 1 && !two) break;
@@ -594,35 +609,36 @@ size_t merge_pyr_elems(int W, int H, int levels) {
 hipError_t launch_ssim_maps(int n, int W, int H, const float* const* yeqs, int ref_index,
                             const lnr_params& p, float* ssim, hipStream_t st) {
   const size_t N = (size_t)W * H;
-  hipError_t e;
+  const int r = p.ssim_radius;
+  SsimWin win;
+  double gs = 0.0;
+  for (int j = -r; j <= r; ++j) {
+    win.g[j + r] = exp(-(double)(j * j) / (2.0 * p.ssim_sigma * p.ssim_sigma));
+    gs += win.g[j + r];
+  }
+  for (int j = 0; j <= 2 * r; ++j) win.g[j] /= gs;
+  SsimMaps maps;
+  int m = 0;
   for (int k = 0; k < n; ++k) {
     if (k == ref_index) continue;
-    const int r = p.ssim_radius;
-    SsimWin win;
-    double gs = 0.0;
-    for (int j = -r; j <= r; ++j) {
-      win.g[j + r] = exp(-(double)(j * j) / (2.0 * p.ssim_sigma * p.ssim_sigma));
-      gs += win.g[j + r];
-    }
-    for (int j = 0; j <= 2 * r; ++j) win.g[j] /= gs;
-    const int tw = 256 - 2 * r;
-    dim3 g((W + tw - 1) / tw, (H + kSsimTH - 1) / kSsimTH);
-    const float* ya = yeqs[ref_index];
-    const float* yb = yeqs[k];
-    float* so = ssim + (size_t)k * N;
-    switch (r) {
-#define SSIM_CASE(R_)                                                                          \
-  case R_:                                                                                     \
-    LNR_LAUNCH(k_ssim<R_>, g, dim3(256), 0, st, ya, yb, W, H, win, p.ssim_c1, p.ssim_c2, so); \
-    break;
-      SSIM_CASE(1) SSIM_CASE(2) SSIM_CASE(3) SSIM_CASE(4)
-      SSIM_CASE(5) SSIM_CASE(6) SSIM_CASE(7) SSIM_CASE(8)
-#undef SSIM_CASE
-      default: return hipErrorInvalidValue;
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    maps.b[m] = yeqs[k];
+    maps.out[m++] = ssim + (size_t)k * N;
   }
-  return hipSuccess;
+  if (m == 0) return hipSuccess;
+  const int tw = 256 - 2 * r;
+  const dim3 g((W + tw - 1) / tw, (H + kSsimTH - 1) / kSsimTH, m);
+  const float* ya = yeqs[ref_index];
+  switch (r) {
+#define SSIM_CASE(R_)                                                                           \
+  case R_:                                                                                      \
+    LNR_LAUNCH(k_ssim<R_>, g, dim3(256), 0, st, ya, maps, W, H, win, p.ssim_c1, p.ssim_c2);     \
+    break;
+    SSIM_CASE(1) SSIM_CASE(2) SSIM_CASE(3) SSIM_CASE(4)
+    SSIM_CASE(5) SSIM_CASE(6) SSIM_CASE(7) SSIM_CASE(8)
+#undef SSIM_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_merge(int n, int ch, int W, int H, const float* const* imgs,
