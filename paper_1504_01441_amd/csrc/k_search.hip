@@ -195,17 +195,29 @@ __global__ __launch_bounds__(256) void k_warp_jobs(const WarpJob* __restrict__ j
   warp_four(J.src, J.w, J.h, hp, x, y, J.out + (size_t)y * J.w);
 }
 
+// Division by a launch constant d: i / d as a 24-bit product and a shift, exact
+// for i (d - 1) < 2^22 and i < 1024 d (div_by; the index ranges of a tile, at
+// most 90 rows of 136 bytes, stay far below).
+struct Div {
+  uint32_t d, m;
+};
+inline Div div_by(int d) { return Div{(uint32_t)d, ((1u << 22) + (uint32_t)d - 1u) / (uint32_t)d}; }
+__device__ inline int quot(int i, const Div& q) { return (int)(__umul24((uint32_t)i, q.m) >> 22); }
+__device__ inline int rest(int i, int q, const Div& v) {
+  return i - (int)__umul24((uint32_t)q, v.d);
+}
+
 // Copy rows [y0, y0 + nrows) x bytes [x0, x0 + 4 * ndw) of an 8-bit image
 // into LDS (row stride `ldst`), 0 outside the image. Interior dwords are read
 // as two aligned dwords realigned with v_alignbyte_b32, unrolled so that
 // several loads are in flight per thread.
 __device__ inline void stage_rows(const uint8_t* __restrict__ img, int w, int h, int x0, int y0,
-                                  int nrows, int ndw, uint8_t* dst, int ldst, int tid, int nt,
-                                  uint32_t flip = 0u) {
-  const int total = nrows * ndw;
+                                  int nrows, const Div& ndw, uint8_t* dst, int ldst, int tid,
+                                  int nt, uint32_t flip = 0u) {
+  const int total = nrows * (int)ndw.d;
 #pragma unroll 4
   for (int i = tid; i < total; i += nt) {
-    const int r = i / ndw, j = i % ndw;
+    const int r = quot(i, ndw), j = rest(i, r, ndw);
     const int gy = y0 + r, gx = x0 + 4 * j;
     uint32_t v = 0;
     if (gy >= 0 && gy < h) {
@@ -232,9 +244,9 @@ __device__ inline void stage_rows(const uint8_t* __restrict__ img, int w, int h,
 // of loads (four dwords) is in flight, before their LDS stores.
 template <typename F>
 __device__ inline void stage_rows_around(const uint8_t* __restrict__ img, int w, int h, int x0,
-                                         int y0, int nrows, int ndw, uint8_t* dst, int ldst,
-                                         int tid, int nt, uint32_t flip, F&& between) {
-  const int total = nrows * ndw;
+                                         int y0, int nrows, const Div& ndw, uint8_t* dst,
+                                         int ldst, int tid, int nt, uint32_t flip, F&& between) {
+  const int total = nrows * (int)ndw.d;
   bool pending = true;
   for (int i0 = tid; i0 < total; i0 += 4 * nt) {
     uint32_t v[4];
@@ -243,7 +255,7 @@ __device__ inline void stage_rows_around(const uint8_t* __restrict__ img, int w,
       const int i = i0 + u * nt;
       v[u] = 0;
       if (i >= total) continue;
-      const int r = i / ndw, j = i % ndw;
+      const int r = quot(i, ndw), j = rest(i, r, ndw);
       const int gy = y0 + r, gx = x0 + 4 * j;
       if (gy >= 0 && gy < h) {
         const uint8_t* row = img + (size_t)gy * w;
@@ -270,7 +282,7 @@ __device__ inline void stage_rows_around(const uint8_t* __restrict__ img, int w,
     for (int u = 0; u < 4; ++u) {
       const int i = i0 + u * nt;
       if (i < total) {
-        const int r = i / ndw, j = i % ndw;
+        const int r = quot(i, ndw), j = rest(i, r, ndw);
         *reinterpret_cast<uint32_t*>(dst + r * ldst + 4 * j) = v[u] ^ flip;
       }
     }
@@ -281,22 +293,25 @@ __device__ inline void stage_rows_around(const uint8_t* __restrict__ img, int w,
 // The window rows [y0, y0 + nrows) x bytes [x0, x0 + 4 * ndw) of the level
 // warped on the fly: each pixel inside the level is warp_px of the unwarped
 // source (the value k_warp_q8 stores there), 0 outside, as stage_rows reads
-// the stored warped level; every byte XOR flip. Four pixels per thread at a
-// time: their sample positions first, then all sixteen taps in flight, then
+// the stored warped level; every byte XOR flip. Two pixels per thread at a
+// time: their sample positions first, then their eight taps in flight, then
 // the blends.
 __device__ inline void stage_warped(const uint8_t* __restrict__ src, int w, int h,
-                                    const double* hp, int x0, int y0, int nrows, int ndw,
-                                    uint8_t* dst, int ldst, int tid, int nt, uint32_t flip) {
-  constexpr int U = 4;
-  const int total = nrows * ndw * 4;
+                                    const double* hp, int x0, int y0, int nrows,
+                                    const Div& nb, uint8_t* dst, int ldst, int tid, int nt,
+                                    uint32_t flip) {
+  constexpr int U = 2;
+  const int total = nrows * (int)nb.d;
   for (int i0 = tid; i0 < total; i0 += U * nt) {
     Q8Tap t[U];
     bool in[U], ok = true;
+    int at[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + u * nt;
-      const int r = i / (4 * ndw), b = i % (4 * ndw);
+      const int r = quot(i, nb), b = rest(i, r, nb);
       const int gy = y0 + r, gx = x0 + b;
+      at[u] = r * ldst + b;
       in[u] = i < total && gy >= 0 && gy < h && gx >= 0 && gx < w;
       t[u] = warp_tap<true>(hp, w, h, in[u] ? gx : 0, in[u] ? gy : 0, ok);
     }
@@ -309,11 +324,9 @@ __device__ inline void stage_warped(const uint8_t* __restrict__ src, int w, int 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * nt;
-      if (i >= total) break;
-      const int r = i / (4 * ndw), b = i % (4 * ndw);
+      if (i0 + u * nt >= total) break;
       const uint32_t v = in[u] ? blend_q8(p[u], t[u].fx, t[u].fy) : 0u;
-      dst[r * ldst + b] = (uint8_t)(v ^ flip);
+      dst[at[u]] = (uint8_t)(v ^ flip);
     }
   }
 }
@@ -338,6 +351,12 @@ struct SearchShape {
   // sums and the patch rows, the window energies that of the window, and
   // the split totals follow. off_cend: the end of the corner phase's memory.
   int rs, off_reg, off_hsum, off_cend, off_win, off_rowsq, off_tot, off_colE, off_pb;
+  int erun;  // candidate rows per thread in the window energies
+  // dwords of a patch row, a region row and a window row; a window row's
+  // bytes and energy runs; quadrant origins and corner candidates of a row;
+  // candidates of a row; a lane group's threads and a candidate row's strips;
+  // dwords of a padded patch row
+  Div d_patch, d_reg, d_win, d_winb, d_run, d_nxo, d_nc1, d_cand, d_base, d_strip, d_LB, d_split;
 };
 
 // nearest integer of a predicted source coordinate (half up), clamped far
@@ -347,15 +366,6 @@ __device__ inline int round_pred(double s) {
   if (!(q > -1048576.0)) q = -1048576.0;
   if (q > 1048576.0) q = 1048576.0;
   return (int)q;
-}
-
-__device__ inline unsigned long long wave_min_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned long long u = __shfl_xor(v, o);
-    v = u < v ? u : v;
-  }
-  return v;
 }
 
 // Workgroup state shared by the phases of one tile visit.
@@ -432,7 +442,7 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
     if (tid == 0) S.er_sum = 0u;
     // the patch around the known corner
     const int P = c.P, PW = 2 * P + 1;
-    stage_rows(J.ref, w, h, px - P, py - P, PW, (PW + 3) / 4, reg, sh.rs, tid, nt);
+    stage_rows(J.ref, w, h, px - P, py - P, PW, sh.d_patch, reg, sh.rs, tid, nt);
     __syncthreads();
     for (int i = tid; i < PW * NW; i += nt) S.refp[i] = patch_dword(reg, sh.rs, 0, 0, PW, i / NW, i % NW);
   } else {
@@ -440,7 +450,7 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
     // the region lies inside the tile; dword-aligned loads realigned in registers
     const int side = 2 * ext + 1;
     const int rx0 = cx0 - ext, ry0 = cy0 - ext;
-    stage_rows(J.ref, w, h, rx0, ry0, side, (side + 3) / 4, reg, sh.rs, tid, nt);
+    stage_rows(J.ref, w, h, rx0, ry0, side, sh.d_reg, reg, sh.rs, tid, nt);
     if (tid == 0) { S.best_key = 0u; S.er_sum = 0u; }
     __syncthreads();
     const int nc1 = 2 * c.K + 1, ncand = nc1 * nc1;
@@ -454,7 +464,7 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
       const int nxo = 2 * nc1;
       const int nd = (c.r + 3) >> 2;
       for (int i = tid; i < nrow * nxo; i += nt) {
-        const int row = i / nxo, xo = i % nxo;
+        const int row = quot(i, sh.d_nxo), xo = rest(i, row, sh.d_nxo);
         const int a = xo >> 1;
         const int X0 = ext + c.g * (a - c.K) - ((xo & 1) ? 0 : c.r);
         const uint32_t* rp = rdw + (yo + row) * (sh.rs / 4) + (X0 >> 2);
@@ -471,7 +481,7 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
       __syncthreads();
       for (int i = tid; i < 4 * ncand; i += nt) {
         const int ci = i >> 2, q = i & 3;
-        const int a = ci % nc1, b = ci / nc1;
+        const int b = quot(ci, sh.d_nc1), a = rest(ci, b, sh.d_nc1);
         // quadrants in cyclic order TL, TR, BR, BL
         const int xo = 2 * a + ((q == 0 || q == 3) ? 0 : 1);
         const int r0 = c.g * b + ((q <= 1) ? 0 : c.r);   // first row, relative to yo
@@ -558,40 +568,45 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
       uint32_t* pb = reinterpret_cast<uint32_t*>(dyn + sh.off_pb);
       const int d0 = sh.padB >> 2;
       for (int q = tid; q < PW * sh.LB; q += nt) {
-        const int i = q / sh.LB, d = q - i * sh.LB - d0;
+        const int i = quot(q, sh.d_LB), d = rest(q, i, sh.d_LB) - d0;
         pb[q] = (d >= 0 && d < NW) ? patch_dword(reg, sh.rs, pr0, pc0, PW, i, d) : 0u;
       }
       if (sh.split > 1)
         for (int i = tid; i < sh.ncand * sh.ncand; i += nt) tot[i] = 0u;
     }
   };
+  if constexpr (KX != 0)
+    if (sh.split > 1)
+      for (int i = tid; i < sh.ncand * ncp; i += nt) tot[i] = 0u;
   // (without WARP the job has no Hwarp: the launchers check it)
   if (WARP && J.Hwarp) {
     double hp[9];
-    pixel_homography(J.Hwarp, w, h, hp);
-    stage_warped(J.wimg, w, h, hp, wx0, wy0, sh.NR, sh.stage_dw, win, sh.wrow, tid, nt, 0x80u);
+    pixel_homography_sparse(J.Hwarp, w, h, hp);
+    stage_warped(J.wimg, w, h, hp, wx0, wy0, sh.NR, sh.d_winb, win, sh.wrow, tid, nt, 0x80u);
     pack_patch();
   } else {
     // (the patch rows are packed while the window's first loads are in flight)
-    stage_rows_around(J.wimg, w, h, wx0, wy0, sh.NR, sh.stage_dw, win, sh.wrow, tid, nt,
+    stage_rows_around(J.wimg, w, h, wx0, wy0, sh.NR, sh.d_win, win, sh.wrow, tid, nt,
                       0x80808080u, pack_patch);
   }
   __syncthreads();
-  // patch energy (summed over each wave first: one LDS atomic per wave)
-  {
+  // patch energy, by the waves that hold items (summed over each first: one
+  // LDS atomic per wave)
+  auto patch_energy = [&](int first) {
+    if ((first & ~63) >= PW * NW) return;
     uint32_t part = 0;
-    for (int i = tid; i < PW * NW; i += nt)
+    for (int i = first; i < PW * NW; i += nt)
       part = (uint32_t)__builtin_amdgcn_sdot4((int)S.refp[i], (int)S.refp[i], (int)part, false);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if ((tid & 63) == 0 && part) atomicAdd(&S.er_sum, part);
-  }
+    part = (uint32_t)__builtin_amdgcn_readlane(wave_scan_i32((int)part), 63);
+    if ((tid & 63) == 0) atomicAdd(&S.er_sum, part);
+  };
   // matrix-core lane roles: wave (group msp, dx block mnb), lane (r16, cg)
   const int lane = tid & 63, mwave = tid >> 6;
   const int mnb = mwave % sh.NB, msp = mwave / sh.NB;
   const int r16 = lane & 15, cg = lane >> 4;
   v4i acc[MB > 0 ? MB : 1];
   if constexpr (KX == 0) {
+    patch_energy(tid);
     // 3. cross terms on the matrix cores. For patch row i the cross term of
     // every candidate is a product of two small matrices,
     //   X[dy][dx] += sum_x win[i + dy][x] * pat[i][x - dx],
@@ -649,13 +664,13 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
   // hipcc folds e + b*b - a*a on two bytes into one v_dot4_u32_u8 of the
   // packed pair, which adds a*a instead of subtracting it. A run's first
   // dwords may reach a few bytes past the row: those bytes are masked off.)
-  {
+  auto row_energies = [&](int first) {
     constexpr int CH = 8;
     const uint32_t* wdw = reinterpret_cast<const uint32_t*>(win);
     const int rowdw = sh.wrow >> 2;
-    const int nch = (sh.ncand + CH - 1) / CH;
-    for (int it = tid; it < sh.NR * nch; it += nt) {
-      const int yy = it / nch, c0 = (it - yy * nch) * CH;
+    const int nch = (int)sh.d_run.d;
+    for (int it = first; it < sh.NR * nch; it += nt) {
+      const int yy = quot(it, sh.d_run), c0 = rest(it, yy, sh.d_run) * CH;
       const uint32_t* rp = wdw + yy * rowdw;
       uint32_t e = 0;
 #pragma unroll
@@ -688,17 +703,18 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
           if (k0 + q + 1 < cend) out[k0 + q + 1] = v[q];
       }
     }
-  }
-  __syncthreads();
+  };
   // (matrix cores: the window energies overwrite the window)
   uint32_t* colE = reinterpret_cast<uint32_t*>(dyn + sh.off_colE);  // [ncand][ncand]
   // window energies: vertical box sums of the row energies, sliding over
-  // runs of 7 candidate rows per column
-  {
-    const int nch = (sh.ncand + 6) / 7;
-    for (int it = tid; it < sh.ncand * nch; it += nt) {
-      const int dxi = it % sh.ncand, ch = it / sh.ncand;
-      const int y0 = ch * 7, y1 = min(y0 + 7, sh.ncand);
+  // runs of erun candidate rows per column (no longer than it takes to give
+  // the workgroup's threads a run each)
+  auto window_energies = [&]() {
+    const int run = sh.erun;
+    for (int it = tid;; it += nt) {
+      const int ch = quot(it, sh.d_cand), dxi = rest(it, ch, sh.d_cand);
+      const int y0 = ch * run, y1 = min(y0 + run, sh.ncand);
+      if (y0 >= sh.ncand) break;
       uint32_t e = 0;
       for (int i = 0; i < PW; ++i) e += rowsq[(y0 + i) * sh.ncand + dxi];
       colE[y0 * sh.ncand + dxi] = e;
@@ -707,21 +723,16 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
         colE[y * sh.ncand + dxi] = e;
       }
     }
-  }
-  if constexpr (KX != 0)
-    if (sh.split > 1)
-      for (int i = tid; i < sh.ncand * ncp; i += nt) tot[i] = 0u;
-  __syncthreads();
+  };
 
   unsigned long long key = ~0ull;
-  const uint32_t er = S.er_sum;
-  // candidate (dy index j, dx index dxi) with cross term x: its key, if its
-  // patch lies inside the level
-  auto score = [&](int j, int dxi, uint32_t x) {
+  // candidate (dy index j, dx index dxi) with cross term x and window energy e:
+  // its key, if its patch lies inside the level
+  auto score = [&](int j, int dxi, uint32_t x, uint32_t e) {
     const int dx = dxi - R + cdx, dy = j - R + cdy;
     if (px + dx - P < 0 || px + dx + P > w - 1 || py + dy - P < 0 || py + dy + P > h - 1) return;
     // exact modulo 2^32, and the SSD itself is below 2^32
-    const uint32_t ssd = er + colE[j * sh.ncand + dxi] - 2u * x;
+    const uint32_t ssd = S.er_sum + e - 2u * x;
     // ties on the absolute displacement, or on the offset from the
     // predicted position when the window is centred on a prediction
     const int kx = J.Hlit ? dxi - R : dx, ky = J.Hlit ? j - R : dy;
@@ -735,6 +746,10 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
   };
 
   if constexpr (KX == 0) {
+    row_energies(tid);
+    __syncthreads();
+    window_energies();
+    __syncthreads();
     const int dxi = 16 * mnb + r16;
     if (msp == 0 && dxi < sh.ncand) {
 #pragma unroll
@@ -743,22 +758,28 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
         for (int t = 0; t < 4; ++t) {
           const int j = 16 * mb + 4 * cg + t;
           if (mb >= sh.NB || j >= sh.ncand) continue;
-          score(j, dxi, sh.split > 1 ? tot[j * ncp + dxi] : (uint32_t)acc[mb][t]);
+          score(j, dxi, sh.split > 1 ? tot[j * ncp + dxi] : (uint32_t)acc[mb][t],
+                colE[j * sh.ncand + dxi]);
         }
     }
   } else {
+    // the energies from the workgroup's last waves on, beside the first ones'
+    // cross terms
+    const int back = nt - 1 - tid;
+    row_energies(back);
+    patch_energy(back >= 128 ? back - 128 : back + max(nt - 128, 0));
     // 3. cross terms of KX candidates per thread (over a group of patch
     // rows), signed 8-bit dot products of the centred bytes
     const int base_threads = sh.ncand * sh.nstrips;
-    const int grp = tid / base_threads, rem = tid % base_threads;
-    const int j = rem / sh.nstrips, s = rem % sh.nstrips;  // dy index, strip
+    const int grp = quot(tid, sh.d_base), rem = rest(tid, grp, sh.d_base);
+    const int j = quot(rem, sh.d_strip), s = rest(rem, j, sh.d_strip);  // dy index, strip
     uint32_t acc[KX];
 #pragma unroll
     for (int k = 0; k < KX; ++k) acc[k] = 0;
     if (tid < sh.nthreads) {
       const uint32_t* wdw = reinterpret_cast<const uint32_t*>(win);
       const int rowdw = sh.wrow >> 2;
-      const int i0 = grp * PW / sh.split, i1 = (grp + 1) * PW / sh.split;
+      const int i0 = quot(grp * PW, sh.d_split), i1 = quot((grp + 1) * PW, sh.d_split);
       for (int i = i0; i < i1; ++i) {
         const uint32_t* wr = wdw + (j + i) * rowdw + s * (KX / 4);
         uint32_t wv[KX / 4 + NW + 1];
@@ -788,22 +809,35 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
 #pragma unroll
         for (int k = 0; k < KX; ++k) atomicAdd(&tot[j * ncp + s * KX + k], acc[k]);
     }
-    if (sh.split > 1) {
+    __syncthreads();
+    if (sh.split > 1 && sh.erun <= 2) {
+      // a candidate or two per thread, each summing its own window energy
+      for (int i = tid; i < sh.ncand * sh.ncand; i += nt) {
+        const int jj = quot(i, sh.d_cand), dxi = rest(i, jj, sh.d_cand);
+        uint32_t e = 0;
+#pragma unroll 7
+        for (int y = 0; y < PW; ++y) e += rowsq[(jj + y) * sh.ncand + dxi];
+        score(jj, dxi, tot[jj * ncp + dxi], e);
+      }
+    } else {
+      window_energies();
       __syncthreads();
-      if (tid < base_threads)
+      if (sh.split > 1) {
+        for (int i = tid; i < sh.ncand * sh.ncand; i += nt) {
+          const int jj = quot(i, sh.d_cand), dxi = rest(i, jj, sh.d_cand);
+          score(jj, dxi, tot[jj * ncp + dxi], colE[i]);
+        }
+      } else if (tid < base_threads) {
 #pragma unroll
-        for (int k = 0; k < KX; ++k) acc[k] = tot[j * ncp + s * KX + k];
-    }
-    if (tid < base_threads) {
-#pragma unroll
-      for (int k = 0; k < KX; ++k) {
-        const int dxi = s * KX + k;
-        if (dxi < sh.ncand) score(j, dxi, acc[k]);
+        for (int k = 0; k < KX; ++k) {
+          const int dxi = s * KX + k;
+          if (dxi < sh.ncand) score(j, dxi, acc[k], colE[j * sh.ncand + dxi]);
+        }
       }
     }
   }
   // 4. argmin -------------------------------------------------------------------
-  key = wave_min_u64(key);
+  key = ~wave_max_u64(~key);
   if ((tid & 63) == 0) S.wmin[tid >> 6] = key;
   __syncthreads();
   if (tid == 0) {
@@ -1030,13 +1064,33 @@ SearchShape make_shape(int R, const SearchCfg& c, int split, long long ntiles, i
   }
   int b = (sh.nthreads + 63) / 64 * 64;
   if (b < 64) b = 64;
+  // Four waves more than the lane groups where the level leaves SIMDs idle: a
+  // tile is then one chain of latencies and every phase's items are spread
+  // over all the threads (a coarse search of 15 tiles 13.8 -> 10.9 us, of 420
+  // 16.8 -> 15.1; but of 1200 25.8 -> 28.3). The matrix cores' waves each own
+  // a part of the products.
+  if (KX != 0 && ntiles < 1024) b = std::min(b + 256, 1024);
   *block = b;
+  const int nch = std::max(b / sh.ncand, 1);
+  sh.erun = (sh.ncand + nch - 1) / nch;
   // the reference region: side rows of rs bytes, rs covering the realigned
   // dword reads of the quadrant sums (up to 6 bytes past a row's end) and one
   // spare row after the last; the quadrant row sums: 2 (K g + r) rows of
   // 2 (2K + 1) words
   const int ext = c.K * c.g + (c.r > c.P ? c.r : c.P);
   const int side = 2 * ext + 1;
+  sh.d_patch = div_by((PW + 3) / 4);
+  sh.d_reg = div_by((side + 3) / 4);
+  sh.d_win = div_by(sh.stage_dw);
+  sh.d_winb = div_by(4 * sh.stage_dw);
+  sh.d_run = div_by((sh.ncand + 7) / 8);
+  sh.d_nxo = div_by(2 * (2 * c.K + 1));
+  sh.d_nc1 = div_by(2 * c.K + 1);
+  sh.d_cand = div_by(sh.ncand);
+  sh.d_base = div_by(base);
+  sh.d_strip = div_by(std::max(sh.nstrips, 1));
+  sh.d_split = div_by(sh.split);
+  sh.d_LB = div_by(std::max(sh.LB, 1));
   sh.rs = (side + 8 + 3) / 4 * 4;
   const int hsum_words = 2 * (c.K * c.g + c.r) * 2 * (2 * c.K + 1);
   auto a16 = [](int x) { return (x + 15) / 16 * 16; };

@@ -109,4 +109,39 @@ __device__ inline uint32_t load_pair(const uint8_t* p) {
   return reinterpret_cast<const UnalignedU16*>(p)->v;
 }
 
+// inclusive sums over the wave's lanes
+__device__ inline int wave_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// F(v, v of an earlier lane) folded over the wave on the vector ALU; the
+// total in every lane (0 is F's neutral value)
+template <typename F>
+__device__ inline unsigned long long wave_fold_u64(unsigned long long v, F&& f) {
+#define LNR_FOLD(CTRL, ROWS)                                                                    \
+  v = f(v, ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(                          \
+                0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false)                            \
+            << 32) |                                                                            \
+               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false))
+  LNR_FOLD(0x111, 0xf);  // row_shr 1, 2, 4, 8
+  LNR_FOLD(0x112, 0xf);
+  LNR_FOLD(0x114, 0xf);
+  LNR_FOLD(0x118, 0xf);
+  LNR_FOLD(0x142, 0xa);  // row_bcast 15, 31
+  LNR_FOLD(0x143, 0xc);
+#undef LNR_FOLD
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ inline unsigned long long wave_max_u64(unsigned long long v) {
+  return wave_fold_u64(v, [](unsigned long long p, unsigned long long q) { return q > p ? q : p; });
+}
+
 }  // namespace lnr

@@ -94,6 +94,29 @@ def test_backward_warp_edges(lnr, ctx, w, h, fmt):
         assert (np.abs(yw.cpu().numpy() - ywant) <= 1e-4 * (ywant + 1.0)).all(), kind
 
 
+# one tile; a lane group of a wave and less; window energies summed by the
+# candidates' threads and in runs; the last level with extra waves per tile and
+# the first without
+@pytest.mark.parametrize("nx,ny,R", [(1, 1, 0), (1, 1, 7), (2, 1, 1), (3, 2, 10), (5, 3, 8),
+                                     (33, 31, 5), (32, 32, 5)])
+@pytest.mark.parametrize("P", [1, 10])
+def test_search_at_block_edges(lnr, ctx, nx, ny, R, P):
+    rng = np.random.default_rng(nx * 100 + R)
+    w, h = 32 * nx, 32 * ny
+    base = np.kron(rng.integers(0, 256, (h // 8 + 4, w // 8 + 4)), np.ones((8, 8)))
+    a = np.clip(base[3:3 + h, 5:5 + w] + rng.integers(-3, 4, (h, w)), 0, 255).astype(np.uint8)
+    b = np.clip(base[1:1 + h, 2:2 + w] + rng.integers(-3, 4, (h, w)), 0, 255).astype(np.uint8)
+    p, op = lnr.Params(patch_r=P), oracle.params(patch_r=P)
+    t = lambda v: torch.from_numpy(v).cuda()
+    cxy, disp, ssd, flags = (v.cpu().numpy() for v in lnr.stage_search(ctx, t(a), t(b), R, p))
+    cx, cy, has = oracle.corners(a, op)
+    dx, dy, want, valid = oracle.search(a, b, R, cx, cy, has, op)
+    assert np.array_equal(flags & 1, has) and np.array_equal((flags & 2) > 0, valid > 0)
+    v = valid > 0
+    assert np.array_equal(disp[v, 0], dx[v]) and np.array_equal(disp[v, 1], dy[v])
+    assert np.array_equal(ssd[v].view(np.uint32), want[v])
+
+
 # one word / two; the narrow and the wide hypothesis blocks; the last size of
 # one fit block and the first of several; more iterations than blocks take at
 # once, and counts that leave a group short; few matches with repeated draws
