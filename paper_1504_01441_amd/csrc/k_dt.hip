@@ -45,9 +45,10 @@ struct DtArgs {
 // Block 0 also clears zero[0, nzero) and zero64[0, nzero64) and sets ident to
 // the identity (the registration's first launch does this set-up with the
 // tables: histograms, the top level's weeding bits).
-__global__ void k_dt_coef(DtArgs a, double* __restrict__ coef, uint32_t* __restrict__ zero,
-                          int nzero, double* __restrict__ ident,
-                          unsigned long long* __restrict__ zero64, int nzero64) {
+__device__ inline void dt_coef(const DtArgs& a, double* __restrict__ coef,
+                               uint32_t* __restrict__ zero, int nzero,
+                               double* __restrict__ ident,
+                               unsigned long long* __restrict__ zero64, int nzero64) {
   const int i = blockIdx.x + 1, k = threadIdx.x;
   if (blockIdx.x == 0) {
     for (int j = k; j < nzero; j += 256) zero[j] = 0u;
@@ -58,6 +59,20 @@ __global__ void k_dt_coef(DtArgs a, double* __restrict__ coef, uint32_t* __restr
                      sqrt(pow(4.0, (double)a.iters) - 1.0);
   const double ai = exp(-sqrt(2.0) / sig);
   coef[blockIdx.x * 256 + k] = pow(ai, 1.0 + a.ratio * ((double)k / 255.0));
+}
+
+__global__ __launch_bounds__(256) void k_dt_coef(DtArgs a, double* __restrict__ coef,
+                                                 uint32_t* __restrict__ zero, int nzero,
+                                                 double* __restrict__ ident,
+                                                 unsigned long long* __restrict__ zero64,
+                                                 int nzero64) {
+  dt_coef(a, coef, zero, nzero, ident, zero64, nzero64);
+}
+
+// every pair of a batch, one per blockIdx.y
+__global__ __launch_bounds__(256) void k_dt_coef_jobs(DtArgs a, const SetupJob* __restrict__ jobs) {
+  const SetupJob& J = jobs[blockIdx.y];
+  dt_coef(a, J.coef, J.hist, 512, J.ident, J.vb, J.nvb);
 }
 
 struct Rec {  // one pixel of the three maps between passes
@@ -673,15 +688,25 @@ DtShape dt_default_shape(int W, int H) {
   return s;
 }
 
-hipError_t launch_dt_coef(const lnr_params& p, double* coef, uint32_t* zero, int nzero,
-                          double* ident, hipStream_t st, unsigned long long* zero64,
-                          int nzero64) {
+static DtArgs dt_args(const lnr_params& p) {
   DtArgs a;
   a.iters = p.dt_iters;
   a.sigma_s = p.sigma_s;
   a.ratio = p.sigma_s / p.sigma_r;
-  LNR_LAUNCH(k_dt_coef, dim3(a.iters), dim3(256), 0, st, a, coef, zero, nzero, ident, zero64,
-             zero64 ? nzero64 : 0);
+  return a;
+}
+
+hipError_t launch_dt_coef(const lnr_params& p, double* coef, uint32_t* zero, int nzero,
+                          double* ident, hipStream_t st, unsigned long long* zero64,
+                          int nzero64) {
+  LNR_LAUNCH(k_dt_coef, dim3(p.dt_iters), dim3(256), 0, st, dt_args(p), coef, zero, nzero, ident,
+             zero64, zero64 ? nzero64 : 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_dt_coef_jobs(const lnr_params& p, const SetupJob* jobs, int njobs,
+                               hipStream_t st) {
+  LNR_LAUNCH(k_dt_coef_jobs, dim3(p.dt_iters, njobs), dim3(256), 0, st, dt_args(p), jobs);
   return hipGetLastError();
 }
 

@@ -17,20 +17,17 @@ constexpr int kHistRows = 8;  // rows per block, two per wave
 
 constexpr int kCopies = 16, kCopyStride = 257;  // odd stride: copies hit different banks
 
-__global__ __launch_bounds__(256) void k_hist(const uint8_t* __restrict__ y0, int s0,
-                                              const uint8_t* __restrict__ y1, int s1, int W,
-                                              int H, uint32_t* __restrict__ hist) {
+// rows [row0, row0 + kHistRows) of one frame into hist[256]
+__device__ inline void hist_rows(const uint8_t* __restrict__ img, int stride, int W, int H,
+                                 int row0, uint32_t* __restrict__ hist) {
   // neighbouring pixels share values, so lanes spread their LDS atomics over
   // 16 copies of the bins
   __shared__ uint32_t bins[kCopies * kCopyStride];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int i = tid; i < kCopies * kCopyStride; i += 256) bins[i] = 0;
   __syncthreads();
-  const uint8_t* img = blockIdx.y ? y1 : y0;
-  const int stride = blockIdx.y ? s1 : s0;
   uint32_t* mine = bins + (lane & (kCopies - 1)) * kCopyStride;
-  for (int row = blockIdx.x * kHistRows + wave; row < min(H, (blockIdx.x + 1) * kHistRows);
-       row += 4) {
+  for (int row = row0 + wave; row < min(H, row0 + kHistRows); row += 4) {
     // the row as aligned 32-bit words plus unaligned head and tail bytes
     const uint8_t* p = img + (size_t)row * stride;
     const int head = min(W, (int)((4 - ((uintptr_t)p & 3)) & 3));
@@ -56,7 +53,22 @@ __global__ __launch_bounds__(256) void k_hist(const uint8_t* __restrict__ y0, in
   __syncthreads();
   uint32_t s = 0;
   for (int c = 0; c < kCopies; ++c) s += bins[c * kCopyStride + tid];
-  if (s) atomicAdd(&hist[blockIdx.y * 256 + tid], s);
+  if (s) atomicAdd(&hist[tid], s);
+}
+
+// blockIdx.y: the frame
+__global__ __launch_bounds__(256) void k_hist(const uint8_t* __restrict__ y0, int s0,
+                                              const uint8_t* __restrict__ y1, int s1, int W,
+                                              int H, uint32_t* __restrict__ hist) {
+  hist_rows(blockIdx.y ? y1 : y0, blockIdx.y ? s1 : s0, W, H, blockIdx.x * kHistRows,
+            hist + blockIdx.y * 256);
+}
+
+// both frames of every pair of a batch (blockIdx.z), the grid of the tallest
+__global__ __launch_bounds__(256) void k_hist_jobs(const SetupJob* __restrict__ jobs) {
+  const SetupJob& J = jobs[blockIdx.z];
+  const int f = blockIdx.y, row0 = blockIdx.x * kHistRows;
+  if (row0 < J.g.h[0]) hist_rows(J.y[f], J.stride[f], J.g.w[0], J.g.h[0], row0, J.hist + f * 256);
 }
 
 // LUT[v] = round-half-up(255 (cdf[v] - cdf_min) / (n - cdf_min)), cdf_min the
@@ -96,32 +108,19 @@ __device__ void build_lut(const uint32_t* __restrict__ hist, uint8_t* lut) {
   __syncthreads();
 }
 
-struct LevelGeom {
-  int w[kMaxLevels], h[kMaxLevels];
-  long long off[kMaxLevels];
-  int levels;
-};
-
-__global__ __launch_bounds__(256) void k_lut_pyr(const uint8_t* __restrict__ y0, int s0,
-                                                 const uint8_t* __restrict__ y1, int s1,
-                                                 const uint32_t* __restrict__ hist,
-                                                 LevelGeom g, uint8_t* __restrict__ pyr0,
-                                                 uint8_t* __restrict__ pyr1,
-                                                 uint8_t* __restrict__ lut_out,
-                                                 uint8_t* __restrict__ out0,
-                                                 uint8_t* __restrict__ out1,
-                                                 uint8_t* __restrict__ gt0, int hp) {
+// One 64 x 64 block of one frame at (bx, by): level 0 and the levels above from
+// img through its histogram's LUT; cpy, lut_out, gt optional.
+__device__ inline void lut_pyr_block(const uint8_t* __restrict__ img, int stride,
+                                     const uint32_t* __restrict__ hist, const LevelGeom& g,
+                                     int bx, int by, uint8_t* __restrict__ pyr,
+                                     uint8_t* __restrict__ cpy, uint8_t* __restrict__ lut_out,
+                                     uint8_t* __restrict__ gt, int hp) {
   __shared__ uint8_t lut[256];
   __shared__ uint8_t tileA[64 * 64];
   __shared__ uint8_t tileB[32 * 32];
-  const int f = blockIdx.z, tid = threadIdx.x;
-  build_lut(hist + f * 256, lut);
-  if (lut_out && blockIdx.x == 0 && blockIdx.y == 0) lut_out[f * 256 + tid] = lut[tid];
-  const uint8_t* img = f ? y1 : y0;
-  const int stride = f ? s1 : s0;
-  uint8_t* pyr = f ? pyr1 : pyr0;
-  uint8_t* cpy = f ? out1 : out0;  // optional second copy of level 0
-  const int bx = blockIdx.x * 64, by = blockIdx.y * 64;
+  const int tid = threadIdx.x;
+  build_lut(hist, lut);
+  if (lut_out && bx == 0 && by == 0) lut_out[tid] = lut[tid];
   const int W = g.w[0], H = g.h[0];
   // level 0: 64 x 64 block, four 4-byte groups per thread (one 32-bit load
   // and store each where the row allows, all loads in flight first)
@@ -169,7 +168,7 @@ __global__ __launch_bounds__(256) void k_lut_pyr(const uint8_t* __restrict__ y0,
     *reinterpret_cast<uint32_t*>(&tileA[r * 64 + c4]) = packed;
   }
   __syncthreads();
-  if (f == 0 && gt0) store_tile_columns(tileA, bx, by, W, hp, gt0);
+  if (gt) store_tile_columns(tileA, bx, by, W, hp, gt);
   // levels 1.. from the block in LDS; level l of this block covers
   // [bx >> l, (bx >> l) + (64 >> l)) and only pixels inside the level are kept.
   uint8_t* cur = tileA;
@@ -193,6 +192,32 @@ __global__ __launch_bounds__(256) void k_lut_pyr(const uint8_t* __restrict__ y0,
     nxt = t;
     side = ns;
   }
+}
+
+// blockIdx.z: the frame; out0, out1: optional second copies of level 0
+__global__ __launch_bounds__(256) void k_lut_pyr(const uint8_t* __restrict__ y0, int s0,
+                                                 const uint8_t* __restrict__ y1, int s1,
+                                                 const uint32_t* __restrict__ hist,
+                                                 LevelGeom g, uint8_t* __restrict__ pyr0,
+                                                 uint8_t* __restrict__ pyr1,
+                                                 uint8_t* __restrict__ lut_out,
+                                                 uint8_t* __restrict__ out0,
+                                                 uint8_t* __restrict__ out1,
+                                                 uint8_t* __restrict__ gt0, int hp) {
+  const int f = blockIdx.z;
+  lut_pyr_block(f ? y1 : y0, f ? s1 : s0, hist + f * 256, g, blockIdx.x * 64, blockIdx.y * 64,
+                f ? pyr1 : pyr0, f ? out1 : out0, lut_out ? lut_out + f * 256 : nullptr,
+                f ? nullptr : gt0, hp);
+}
+
+// both frames of every pair of a batch (blockIdx.z = 2 pair + frame), the grid
+// of the largest
+__global__ __launch_bounds__(256) void k_lut_pyr_jobs(const SetupJob* __restrict__ jobs) {
+  const SetupJob& J = jobs[blockIdx.z >> 1];
+  const int f = blockIdx.z & 1, bx = blockIdx.x * 64, by = blockIdx.y * 64;
+  if (bx < J.g.w[0] && by < J.g.h[0])
+    lut_pyr_block(J.y[f], J.stride[f], J.hist + f * 256, J.g, bx, by, J.pyr[f], J.out[f], nullptr,
+                  f ? nullptr : J.gt0, J.hp);
 }
 
 // Metering decision (Sec. 2.1) from a 256-bin luma histogram: the pixels
@@ -229,10 +254,13 @@ hipError_t launch_hist(const uint8_t* y0, int s0, const uint8_t* y1, int s1, int
   return hipGetLastError();
 }
 
-hipError_t launch_lut_pyr(const uint8_t* y0, int s0, const uint8_t* y1, int s1,
-                          const uint32_t* hist, const Geometry& geo, uint8_t* pyr0,
-                          uint8_t* pyr1, uint8_t* lut_out, int nframes, hipStream_t st,
-                          uint8_t* out0, uint8_t* out1, uint8_t* gt0) {
+hipError_t launch_hist_jobs(const SetupJob* jobs, int njobs, int hmax, hipStream_t st) {
+  LNR_LAUNCH(k_hist_jobs, dim3((hmax + kHistRows - 1) / kHistRows, 2, njobs), dim3(256), 0, st,
+             jobs);
+  return hipGetLastError();
+}
+
+LevelGeom level_geom(const Geometry& geo) {
   LevelGeom g;
   g.levels = geo.levels;
   for (int l = 0; l < kMaxLevels; ++l) {
@@ -240,9 +268,23 @@ hipError_t launch_lut_pyr(const uint8_t* y0, int s0, const uint8_t* y1, int s1,
     g.h[l] = l < geo.levels ? geo.lv[l].h : 0;
     g.off[l] = l < geo.levels ? (long long)geo.lv[l].pix_off : 0;
   }
+  return g;
+}
+
+hipError_t launch_lut_pyr(const uint8_t* y0, int s0, const uint8_t* y1, int s1,
+                          const uint32_t* hist, const Geometry& geo, uint8_t* pyr0,
+                          uint8_t* pyr1, uint8_t* lut_out, int nframes, hipStream_t st,
+                          uint8_t* out0, uint8_t* out1, uint8_t* gt0) {
   dim3 grid((geo.W + 63) / 64, (geo.H + 63) / 64, nframes);
-  LNR_LAUNCH(k_lut_pyr, grid, dim3(256), 0, st, y0, s0, y1, s1, hist, g, pyr0, pyr1,
-                     lut_out, out0, out1, gt0, dt_guide_stride(geo.H));
+  LNR_LAUNCH(k_lut_pyr, grid, dim3(256), 0, st, y0, s0, y1, s1, hist, level_geom(geo), pyr0, pyr1,
+             lut_out, out0, out1, gt0, dt_guide_stride(geo.H));
+  return hipGetLastError();
+}
+
+hipError_t launch_lut_pyr_jobs(const SetupJob* jobs, int njobs, int wmax, int hmax,
+                               hipStream_t st) {
+  LNR_LAUNCH(k_lut_pyr_jobs, dim3((wmax + 63) / 64, (hmax + 63) / 64, 2 * njobs), dim3(256), 0, st,
+             jobs);
   return hipGetLastError();
 }
 

@@ -1230,11 +1230,11 @@ lnr_status enqueue_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_frame* s
 }
 
 // A level-synchronous batch (plain method, warped-source search): every pair
-// has its own workspace; the set-up (equalisation, pyramids) and the end
-// (propagation, backward warp) of each pair run on the worker streams, and
-// each pyramid level runs for all pairs at once: one warp launch over all
-// their rows, one search launch over all their tiles and one launch per
-// weeding kernel over all their levels (device job tables).
+// has its own workspace; the end of each pair (propagation, backward warp) runs
+// on the worker streams; the set-up (tables, equalisation, pyramids) and each
+// pyramid level run for all pairs at once: one launch per set-up kernel, one
+// warp launch over all their rows, one search launch over all their tiles and
+// one launch per weeding kernel over all their levels (device job tables).
 struct LevelTables {
   size_t o_warp = 0, o_row0 = 0, o_sjob = 0, o_first = 0, o_wjob = 0;  // in the blob
   int njobs = 0, rows = 0, wmax = 0, ntiles = 0, max_tiles = 0;
@@ -1244,6 +1244,8 @@ struct BatchLayout {
   size_t ws_bytes = 0;
   int levels = 0;           // the deepest pyramid
   LevelTables lv[kMaxLevels];
+  size_t o_setup = 0;       // SetupJob of every pair, in the blob
+  int wmax = 0, hmax = 0;   // the largest frame's sides
   std::vector<uint8_t> blob;  // the job tables (device pointers into the workspace)
 };
 
@@ -1260,15 +1262,37 @@ BatchLayout plan_batch(const lnr_frame* refs, int n, const std::vector<PairPlan>
     b.off[i] = b.ws_bytes;
     b.ws_bytes += (plans[i].bytes + 255) & ~(size_t)255;
     b.levels = std::max(b.levels, plans[i].g.levels);
+    b.wmax = std::max(b.wmax, (int)refs[i].width);
+    b.hmax = std::max(b.hmax, (int)refs[i].height);
   }
-  (void)refs;
   return b;
 }
 
 // Fills the job tables for the workspace at ws (after it has been sized).
-void fill_batch_tables(BatchLayout& b, int n, const lnr_params* p, lnr_registration* outs,
-                       const std::vector<PairPlan>& plans, char* ws) {
+void fill_batch_tables(BatchLayout& b, const lnr_frame* refs, const lnr_frame* srcs, int n,
+                       lnr_registration* outs, const std::vector<PairPlan>& plans, char* ws) {
   b.blob.clear();
+  b.o_setup = blob_take(b.blob, sizeof(SetupJob) * (size_t)n);
+  for (int i = 0; i < n; ++i) {
+    const PairPlan& q = plans[i];
+    char* base = ws + b.off[i];
+    SetupJob j;
+    j.y[0] = refs[i].plane[0]; j.stride[0] = refs[i].stride[0];
+    j.y[1] = srcs[i].plane[0]; j.stride[1] = srcs[i].stride[0];
+    j.pyr[0] = reinterpret_cast<uint8_t*>(base + q.o_pref);
+    j.pyr[1] = reinterpret_cast<uint8_t*>(base + q.o_psrc);
+    j.out[0] = outs[i].yeq_ref;
+    j.out[1] = outs[i].yeq_src;
+    j.gt0 = reinterpret_cast<uint8_t*>(base + q.o_gt);
+    j.hp = dt_guide_stride(q.g.H);
+    j.hist = reinterpret_cast<uint32_t*>(base + q.o_hist);
+    j.coef = reinterpret_cast<double*>(base + q.o_coef);
+    j.ident = outs[i].H + 9 * q.g.levels;
+    j.vb = weed_bufs(base, q.wp).vb;
+    j.nvb = level_words(q.g.lv[q.g.levels - 1]);
+    j.g = level_geom(q.g);
+    memcpy(b.blob.data() + b.o_setup + (size_t)i * sizeof(SetupJob), &j, sizeof(j));
+  }
   for (int l = 0; l < b.levels; ++l) {
     std::vector<int> jobs;
     for (int i = 0; i < n; ++i)
@@ -1328,7 +1352,6 @@ void fill_batch_tables(BatchLayout& b, int n, const lnr_params* p, lnr_registrat
     T.rows = row;
     T.ntiles = tile;
   }
-  (void)p;
 }
 
 lnr_status enqueue_batch_levels(lnr_ctx* ctx, const lnr_frame* refs, const lnr_frame* srcs,
@@ -1338,17 +1361,12 @@ lnr_status enqueue_batch_levels(lnr_ctx* ctx, const lnr_frame* refs, const lnr_f
   const auto lists = assign_pairs(refs, n, K);
   char* ws = static_cast<char*>(ctx->ws);
   lnr_status s;
-  // set-up of every pair on the worker streams
-  LNR_HIP(hipEventRecord(ctx->events[K], origin));
-  for (int k = 0; k < K; ++k) {
-    LNR_HIP(hipStreamWaitEvent(ctx->workers[k], ctx->events[K], 0));
-    for (int i : lists[k])
-      if ((s = enqueue_pair_setup(ctx, &refs[i], &srcs[i], p, &outs[i], plans[i], ws + b.off[i],
-                                  ctx->workers[k])) != LNR_OK)
-        return s;
-    LNR_HIP(hipEventRecord(ctx->events[k], ctx->workers[k]));
-    LNR_HIP(hipStreamWaitEvent(origin, ctx->events[k], 0));
-  }
+  // the set-up, all pairs at once (24 launches over the worker streams, three
+  // per pair of a batch of 8, kept the chip waiting for the host)
+  const SetupJob* sj = reinterpret_cast<const SetupJob*>(tab + b.o_setup);
+  LNR_HIP(launch_dt_coef_jobs(*p, sj, n, origin));
+  LNR_HIP(launch_hist_jobs(sj, n, b.hmax, origin));
+  LNR_HIP(launch_lut_pyr_jobs(sj, n, b.wmax, b.hmax, origin));
   // the levels, all pairs at once
   const SearchCfg cfg = search_cfg(*p);
   for (int l = b.levels - 1; l >= 0; --l) {
@@ -1373,14 +1391,23 @@ lnr_status enqueue_batch_levels(lnr_ctx* ctx, const lnr_frame* refs, const lnr_f
     LNR_HIP(launch_weed_jobs(reinterpret_cast<const WeedJob*>(tab + T.o_wjob), T.njobs,
                              T.max_tiles, l, *p, origin));
   }
-  // propagation and backward warp of every pair on the worker streams
+  // propagation and backward warp of every pair on the worker streams, a pair
+  // for each in turn: all of them have work after the first few launches
   LNR_HIP(hipEventRecord(ctx->events[K], origin));
+  size_t longest = 0;
   for (int k = 0; k < K; ++k) {
     LNR_HIP(hipStreamWaitEvent(ctx->workers[k], ctx->events[K], 0));
-    for (int i : lists[k])
+    longest = std::max(longest, lists[k].size());
+  }
+  for (size_t r = 0; r < longest; ++r)
+    for (int k = 0; k < K; ++k) {
+      if (r >= lists[k].size()) continue;
+      const int i = lists[k][r];
       if ((s = enqueue_pair_finish(ctx, &refs[i], &srcs[i], p, &outs[i], plans[i], ws + b.off[i],
                                    ctx->workers[k])) != LNR_OK)
         return s;
+    }
+  for (int k = 0; k < K; ++k) {
     LNR_HIP(hipEventRecord(ctx->events[k], ctx->workers[k]));
     LNR_HIP(hipStreamWaitEvent(origin, ctx->events[k], 0));
   }
@@ -1435,7 +1462,7 @@ lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_fra
   // workspace, which must not move after they are written)
   auto upload_eager_tables = [&]() -> lnr_status {
     if ((s = ensure_ws(ctx, ws_need(K), st)) != LNR_OK) return s;
-    fill_batch_tables(lay, n, p, outs, plans, static_cast<char*>(ctx->ws));
+    fill_batch_tables(lay, refs, srcs, n, outs, plans, static_cast<char*>(ctx->ws));
     LNR_HIP(hipStreamSynchronize(st));  // an earlier eager batch may still read them
     if (ctx->tables_size < lay.blob.size()) {
       if (ctx->tables) LNR_HIP(hipFree(ctx->tables));
@@ -1530,7 +1557,7 @@ lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_fra
   if (!exec) {
     void* tab = nullptr;
     if (levels) {
-      fill_batch_tables(lay, n, p, outs, plans, static_cast<char*>(ctx->ws));
+      fill_batch_tables(lay, refs, srcs, n, outs, plans, static_cast<char*>(ctx->ws));
       LNR_HIP(hipMalloc(&tab, lay.blob.size()));
       const hipError_t ec = hipMemcpy(tab, lay.blob.data(), lay.blob.size(),
                                       hipMemcpyHostToDevice);

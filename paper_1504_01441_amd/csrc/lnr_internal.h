@@ -61,6 +61,34 @@ struct SearchCfg {
 };
 
 // ---- equalisation + pyramid (k_equalize.hip)
+struct LevelGeom {
+  int w[kMaxLevels], h[kMaxLevels];
+  long long off[kMaxLevels];
+  int levels;
+};
+// The set-up of one pair of a batch: its frames' luma (reference first), the
+// histograms [2][256], pyramids, second copies of level 0 and column-major
+// guide of launch_lut_pyr; the coefficient tables, the identity and the
+// weeding bits of launch_dt_coef.
+struct SetupJob {
+  const uint8_t* y[2];
+  uint8_t* pyr[2];
+  uint8_t* out[2];
+  uint8_t* gt0;
+  uint32_t* hist;
+  double* coef;
+  double* ident;
+  unsigned long long* vb;
+  int stride[2];
+  int hp, nvb;
+  LevelGeom g;
+};
+LevelGeom level_geom(const Geometry& geo);
+// njobs pairs' (device table) histograms, then their pyramids, one launch each;
+// wmax, hmax: the largest frame's sides
+hipError_t launch_hist_jobs(const SetupJob* jobs, int njobs, int hmax, hipStream_t st);
+hipError_t launch_lut_pyr_jobs(const SetupJob* jobs, int njobs, int wmax, int hmax,
+                               hipStream_t st);
 hipError_t launch_hist(const uint8_t* y0, int s0, const uint8_t* y1, int s1, int W, int H,
                        uint32_t* hist /*[nframes][256]*/, int nframes, hipStream_t st);
 // the metering decision from a luma histogram: out[0] = stops, out[1] = the
@@ -268,6 +296,10 @@ __device__ inline void store_tile_columns(const uint8_t* tile, int bx, int by, i
 hipError_t launch_dt_coef(const lnr_params& p, double* coef, uint32_t* zero, int nzero,
                           double* ident, hipStream_t st, unsigned long long* zero64 = nullptr,
                           int nzero64 = 0);
+
+// the same for njobs pairs of a batch (device table; one parameter set)
+hipError_t launch_dt_coef_jobs(const lnr_params& p, const SetupJob* jobs, int njobs,
+                               hipStream_t st);
 
 // ---- backward warp (k_warp.hip)
 // Chroma of a 4:2:0 frame: U at u[(y/2) su + (x/2) cs], V likewise (I420: two
