@@ -28,6 +28,7 @@
 //  k_cnn_wgrad    weight and bias gradients of every layer, per block of samples
 //  k_cnn_adamw    sums the per-block gradients, applies AdamW (fp32) and
 //                 refreshes the bf16 layouts
+#include "lnr_device.h"
 #include "lnr_internal.h"
 
 namespace lnr {
@@ -77,6 +78,17 @@ __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h <<
 
 __device__ inline f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+// relu(v + bias) of four channels as bf16 (hardware conversion, the rounding of
+// f2bf; no NaN is left after the maximum), one 8-byte store
+__device__ inline void st4_relu(uint16_t* p, const f32x4& v, const f32x4& bias) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+  const f32x2 lo = {fmaxf(v[0] + bias[0], 0.f), fmaxf(v[1] + bias[1], 0.f)};
+  const f32x2 hi = {fmaxf(v[2] + bias[2], 0.f), fmaxf(v[3] + bias[3], 0.f)};
+  const h2 a = __builtin_convertvector(lo, h2), b = __builtin_convertvector(hi, h2);
+  *reinterpret_cast<uint2*>(p) =
+      make_uint2(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b));
 }
 __device__ inline bf16x4 ld4(const uint16_t* p) { return *reinterpret_cast<const bf16x4*>(p); }
 
@@ -178,11 +190,15 @@ __global__ __launch_bounds__(256) void k_cnn_input(const uint8_t* __restrict__ r
 // position tiles per wave, the 32 -> 32 layers (3x3, pad 1, stride S, NHWC
 // bf16 in / out, W [co][tap][ci]) one position tile per wave, and the last
 // layer's two channel halves on parts 0 and 1. Every output element sums its
-// MFMA products in (tap, channel half) order.
-// In LDS a position's 32 channels take kPS elements (80 bytes) and a weight
-// row [tap][ci] kWS elements (592 bytes): the padding spreads the 16 rows of
-// an MFMA operand over the banks (unpadded, activation reads conflict ~6-way
-// and weight reads 4-way).
+// MFMA products in (tap, channel half) order. The weights are the products'
+// left operand: a lane then receives four neighbouring channels of a position,
+// which are converted in pairs and stored in 8 bytes (with the activations on
+// the left it holds one channel of four positions, 2-byte stores).
+// (Their LDS layouts: act_at below.)
+//
+// The backward's LDS: a position's 32 channels take kPS elements (80 bytes)
+// and a weight row kWS (592 bytes), which spreads the 16 rows of an operand
+// over half of the bank pairs (unpadded: one or two of them).
 constexpr int kPS = 40;
 constexpr int kWS = 9 * CH + 8;
 
@@ -206,75 +222,141 @@ __device__ inline void load_rows(const uint16_t* __restrict__ src, uint16_t* dst
   }
 }
 
-__device__ void conv1_fwd_part(const uint16_t* in, const uint16_t* W1p, const float* bias,
-                               uint16_t* out, int lane, int part) {
+// The forward's LDS layouts. An operand read takes the 8-byte units of one
+// channel group from 16 rows (positions, or output channels), 16 lanes at a
+// time; unpadded rows of 64 or 576 bytes would put them in one or two of the
+// 16 pairs of banks. So unit c (channels 4c .. 4c + 3) of a row is held at c
+// XOR a number that counts through the rows of an operand, and where a layer's
+// operand takes every other position, neighbouring positions change places on
+// every other of its image rows: no conflicts on any operand. (Rows padded to
+// 80 and 592 bytes: half of the LDS cycles were conflicts.)
+// Element offset of unit c at position pos of the activations of layer A (0:
+// a4, not read as an operand; 1: a1, 16 x 16, stride 2; 2: a2, 8 x 8, stride 1;
+// 3: a3, 8 x 8, stride 2):
+template <int A>
+__device__ inline int act_at(int pos, int c) {
+  if constexpr (A == 1) return (((pos ^ ((pos >> 5) & 1)) << 3) + (c ^ ((pos >> 1) & 7))) * 4;
+  if constexpr (A == 2) return ((pos << 3) + (c ^ ((pos >> 1) & 7))) * 4;
+  if constexpr (A == 3)
+    return (((pos ^ ((pos >> 5) & 1)) << 3) + (c ^ (((pos >> 1) & 3) | ((pos >> 2) & 4)))) * 4;
+  return ((pos << 3) + c) * 4;
+}
+constexpr int kK1S = kK1 + 4;  // W1's rows: an odd number of units
+
+// W2 .. W4, `rows` rows [co][9 tap][32 ci], into LDS: unit c of a tap at c XOR
+// (co / 2) % 8
+__device__ inline void load_weights(const uint16_t* __restrict__ src, uint16_t* dst, int rows,
+                                    int tid, int nt) {
+  constexpr int N = 9 * CH / 8;  // 16-byte loads (two units) per row
+  const int total = rows * N;
+  for (int i0 = tid; i0 < total; i0 += 8 * nt) {
+    uint4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      v[u] = reinterpret_cast<const uint4*>(src)[min(i0 + u * nt, total - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * nt;
+      if (i >= total) break;
+      const int row = i / N, c = 2 * (i % N), sw = (row >> 1) & 7;
+      uint2* d = reinterpret_cast<uint2*>(dst + row * 9 * CH);
+      d[c ^ sw] = make_uint2(v[u].x, v[u].y);
+      d[(c + 1) ^ sw] = make_uint2(v[u].z, v[u].w);
+    }
+  }
+}
+
+// Lane constants of a wave's operand reads, as byte offsets into the
+// workgroup's memory, formed once: with the bounds tests and the layouts'
+// arithmetic in every product's read, the vector ALU, not the matrix cores or
+// the LDS, took most of the time. Positions outside a layer read zeros.
+struct FwdOffsets {
+  int c1[3];                 // conv1: the tap of step ks, in the wave's first row
+  int c2[9], c3[9];          // unit g of each tap; the other half's is at XOR 32
+  int wt;                    // unit g of weight row r; the other half's at XOR 32
+};
+
+template <int HIN, int HOUT, int S, int A>
+__device__ inline void tap_offsets(int (&o)[9], int base, int zero, int m, int g) {
+  const int oy = m / HOUT, ox = m % HOUT;
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) {
+    const int iy = oy * S + tap / 3 - 1, ix = ox * S + tap % 3 - 1;
+    const bool ok = iy >= 0 && iy < HIN && ix >= 0 && ix < HIN;
+    o[tap] = ok ? base + 2 * act_at<A>(iy * HIN + ix, g) : zero;
+    asm volatile("" : "+v"(o[tap]));  // (held, not formed again for every sample)
+  }
+}
+
+__device__ inline bf16x4 lds4(const uint8_t* sm, int off) {
+  return *reinterpret_cast<const bf16x4*>(sm + off);
+}
+
+// x in LDS: 18 x 18 positions of 4 channels, zeros around the 16 x 16
+constexpr int kXW = 18, kXElems = kXW * kXW * C1;
+
+__device__ inline void conv1_fwd_part(const uint8_t* sm, const FwdOffsets& f, const uint16_t* W1p,
+                                      const float* bias, uint16_t* out, int lane, int part) {
   // K = (tap, ci) = tap * 4 + ci over three steps of 16: step ks covers taps
   // 4 ks .. 4 ks + 3, lane group g one tap's four channels (one 8-byte load)
   const int r = lane & 15, g = lane >> 4;
-  const int mt0 = 4 * part;
-  const bf16x4 zero = {0, 0, 0, 0};
   f32x4 acc[4][2];
 #pragma unroll
   for (int u = 0; u < 4; ++u) acc[u][0] = acc[u][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ks = 0; ks < 3; ++ks) {
-    const int tap = 4 * ks + g;
-    const bf16x4 b0 = ld4(W1p + r * kK1 + ks * 16 + g * 4);
-    const bf16x4 b1 = ld4(W1p + (16 + r) * kK1 + ks * 16 + g * 4);
+    const bf16x4 b0 = ld4(W1p + r * kK1S + ks * 16 + g * 4);
+    const bf16x4 b1 = ld4(W1p + (16 + r) * kK1S + ks * 16 + g * 4);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int m = (mt0 + u) * 16 + r, oy = m >> 4, ox = m & 15;
-      const int iy = oy + tap / 3 - 1, ix = ox + tap % 3 - 1;
-      const bool ok = tap < 9 && iy >= 0 && iy < 16 && ix >= 0 && ix < 16;
-      const bf16x4 a = ok ? ld4(in + (iy * 16 + ix) * C1) : zero;
-      acc[u][0] = mfma(a, b0, acc[u][0]);
-      acc[u][1] = mfma(a, b1, acc[u][1]);
+      const bf16x4 a = lds4(sm, f.c1[ks] + u * kXW * C1 * 2);
+      acc[u][0] = mfma(b0, a, acc[u][0]);
+      acc[u][1] = mfma(b1, a, acc[u][1]);
     }
+    __builtin_amdgcn_sched_barrier(0);  // (all steps' operands at once: spills)
   }
+  const f32x4 c0 = *reinterpret_cast<const f32x4*>(bias + 4 * g);
+  const f32x4 c1 = *reinterpret_cast<const f32x4*>(bias + 16 + 4 * g);
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int p = (mt0 + u) * 16 + g * 4 + j;
-      out[p * kPS + r] = f2bf(fmaxf(acc[u][0][j] + bias[r], 0.f));
-      out[p * kPS + 16 + r] = f2bf(fmaxf(acc[u][1][j] + bias[16 + r], 0.f));
-    }
+  for (int u = 0; u < 4; ++u) {
+    // act_at<1> of position (4 part + u) 16 + r: u decides the exchange
+    const int p = r ^ (u >> 1), at = ((p << 3) + (g ^ (r >> 1))) * 4;
+    uint16_t* o = out + (4 * part + u) * 16 * CH;
+    st4_relu(o + at, acc[u][0], c0);
+    st4_relu(o + (at ^ 16), acc[u][1], c1);
+  }
 }
 
-template <int HIN, int HOUT, int S>
-__device__ void conv_fwd_part(const uint16_t* in, const uint16_t* W, const float* bias,
-                              uint16_t* out, int lane, int part) {
+// MT == 4: position tile `part`, both channel halves; MT == 1: channel half
+// `part` of the single position tile (parts 2, 3 idle). o: the taps' offsets;
+// wt: the layer's first weight row's.
+template <int MT, int B>
+__device__ inline void conv_fwd_part(const uint8_t* sm, const int (&o)[9], int wt,
+                                     const float* bias, uint16_t* out, int lane, int part) {
   const int r = lane & 15, g = lane >> 4;
-  constexpr int MT = HOUT * HOUT / 16;
-  static_assert(MT == 4 || MT == 1, "position tiles per sample");
-  // MT == 4: position tile `part`, both channel halves; MT == 1: channel half
-  // `part` of the single position tile (parts 2, 3 idle)
+  constexpr int NT = MT == 4 ? 2 : 1;
   if (MT == 1 && part >= 2) return;
-  const int mt = MT == 4 ? part : 0;
-  const int n0 = MT == 4 ? 0 : part, n1 = MT == 4 ? 2 : part + 1;
-  const bf16x4 zero = {0, 0, 0, 0};
-  f32x4 acc[2] = {(f32x4){0.f, 0.f, 0.f, 0.f}, (f32x4){0.f, 0.f, 0.f, 0.f}};
-  const int m = mt * 16 + r, oy = m / HOUT, ox = m % HOUT;
+  const int n0 = MT == 4 ? 0 : part;
+  f32x4 acc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  const int w = wt + n0 * 16 * 9 * CH * 2;
 #pragma unroll
   for (int tap = 0; tap < 9; ++tap) {
-    const int iy = oy * S + tap / 3 - 1, ix = ox * S + tap % 3 - 1;
-    const bool ok = iy >= 0 && iy < HIN && ix >= 0 && ix < HIN;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      const int ci = half * 16 + g * 4;
-      const bf16x4 a = ok ? ld4(in + (iy * HIN + ix) * kPS + ci) : zero;
-      for (int nt = n0; nt < n1; ++nt) {
-        const bf16x4 b = ld4(W + (nt * 16 + r) * kWS + tap * CH + ci);
-        acc[nt - n0] = mfma(a, b, acc[nt - n0]);
-      }
-    }
-  }
-  for (int nt = n0; nt < n1; ++nt)
+      const bf16x4 a = lds4(sm, o[tap] ^ (32 * half));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int p = mt * 16 + g * 4 + j;
-      out[p * kPS + nt * 16 + r] = f2bf(fmaxf(acc[nt - n0][j] + bias[nt * 16 + r], 0.f));
+      for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = mfma(lds4(sm, (w ^ (32 * half)) + (nt * 16 * 9 + tap) * CH * 2), a, acc[nt]);
     }
+    if (tap % 3 == 2) __builtin_amdgcn_sched_barrier(0);  // (all taps' operands at once: spills)
+  }
+  const int m = (MT == 4 ? part : 0) * 16 + r;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+    st4_relu(out + act_at<B>(m, (n0 + nt) * 4 + g), acc[nt],
+             *reinterpret_cast<const f32x4*>(bias + (n0 + nt) * 16 + 4 * g));
 }
 
 struct ProposalOut {
@@ -289,25 +371,39 @@ struct ProposalOut {
   int ntiles;
 };
 
-// LDS: packed weights (W1p, then W2..W4 with padded rows) and biases, shared
+// LDS: packed weights (W1p with padded rows, then W2..W4) and biases, shared
 // by the workgroup's waves; then per sample in flight a 256-position and a
 // 64-position activation buffer (x -> a1 -> a2 -> a3 -> a4 ping-pong). The
 // head's weights are read from global memory.
-constexpr int kFwdLdsWeights = (kW1p + 3 * CH * kWS) * 2 + 4 * CH * 4;
-constexpr int kFwdBufA = 256 * kPS, kFwdBufB = 64 * kPS;  // elements
+constexpr int kFwdLdsWeights = (CH * kK1S + 3 * kWp) * 2 + 4 * CH * 4;
+constexpr int kFwdBufA = 256 * CH, kFwdBufB = 64 * CH;  // elements
 constexpr int kFwdLdsSample = (kFwdBufA + kFwdBufB) * 2;
-constexpr int fwd_lds(int spb) { return kFwdLdsWeights + spb * kFwdLdsSample; }
+constexpr int kFwdZero = 512;  // bytes of zeros, read for positions outside a layer
+constexpr int fwd_lds(int spb) { return kFwdLdsWeights + spb * kFwdLdsSample + kFwdZero; }
+static_assert(kFwdLdsWeights % 64 == 0 && kFwdLdsSample % 64 == 0 && kFwdBufA % 32 == 0,
+              "XOR 32 stays in a position's 64 bytes");
+static_assert(3 * kXW * C1 * 2 + 40 <= kFwdZero, "conv1 reads its four rows of zeros");
 static_assert(fwd_lds(kFwdMany) <= 160 * 1024, "forward workgroup LDS");
 
 // a1 .. a4 as stored for training: position * 32 + channel, 8 channels (one
-// 16-byte access) at a time
+// 16-byte store) at a time
+template <int A>
 __device__ inline void store_acts(const uint16_t* buf, uint16_t* __restrict__ out, int npos,
                                   int gt, int nt) {
-  for (int i = gt; i < npos * 4; i += nt)
-    reinterpret_cast<uint4*>(out)[i] =
-        *reinterpret_cast<const uint4*>(buf + (i >> 2) * kPS + (i & 3) * 8);
+  for (int i = gt; i < npos * 4; i += nt) {
+    const uint2 lo = *reinterpret_cast<const uint2*>(buf + act_at<A>(i >> 2, 2 * (i & 3)));
+    const uint2 hi = *reinterpret_cast<const uint2*>(buf + act_at<A>(i >> 2, 2 * (i & 3) + 1));
+    reinterpret_cast<uint4*>(out)[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+  }
 }
 
+// Bound by the LDS reads (an activation and two weight operands for two matrix
+// products: 18 us for 4860 samples; the products alone 13) and by the waits
+// between the layers, whose waves run in step. 4860 samples take 35 us; 55
+// with seven barriers per sample, the input staged and the head run by
+// themselves, 2-byte activation stores and conflicts on half of the LDS cycles.
+// (Traced, step by step: 61 us; stores, input and head 48; layouts 42; lane
+// constants 41.)
 template <bool TRAIN, int SPB>
 __global__ __launch_bounds__(SPB * kFwdGroupWaves * kWave) void k_cnn_fwd(
     const uint16_t* __restrict__ pk, const float* __restrict__ P, const uint16_t* __restrict__ x,
@@ -315,94 +411,149 @@ __global__ __launch_bounds__(SPB * kFwdGroupWaves * kWave) void k_cnn_fwd(
   extern __shared__ __align__(16) uint8_t sm[];
   if (po.count) n = *po.count;
   uint16_t* sW1 = reinterpret_cast<uint16_t*>(sm);
-  uint16_t* sW = sW1 + kW1p;  // [3][32 co][kWS]: [9 tap][32 ci] + padding
-  float* sb = reinterpret_cast<float*>(sW + 3 * CH * kWS);  // [4][32]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = wave / kFwdGroupWaves, part = wave % kFwdGroupWaves;
+  uint16_t* sW = sW1 + CH * kK1S;  // [3][32 co][9 tap][32 ci]
+  float* sb = reinterpret_cast<float*>(sW + 3 * kWp);  // [4][32]
+  const int tid = threadIdx.x;
+  int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // a group's parts are rotated, so that the parts that are idle in the last
+  // layer or run the head are on different SIMDs
+  const int grp = wave / kFwdGroupWaves, part = (wave + grp) % kFwdGroupWaves;
   const int gt = part * kWave + lane;  // thread index within the sample's group
   constexpr int GT = kFwdGroupWaves * kWave;
   {
-    load_rows<kK1, kK1>(pk, sW1, CH, tid, SPB * GT);
-    load_rows<9 * CH, kWS>(pk + kW1p, sW, 3 * CH, tid, SPB * GT);
+    for (int i = tid; i < CH * kK1 / 4; i += SPB * GT)
+      reinterpret_cast<uint2*>(sW1)[i / (kK1 / 4) * (kK1S / 4) + i % (kK1 / 4)] =
+          reinterpret_cast<const uint2*>(pk)[i];
+    load_weights(pk + kW1p, sW, 3 * CH, tid, SPB * GT);
     for (int i = tid; i < 4 * CH; i += blockDim.x) sb[i] = P[kOffB[i / CH] + i % CH];
   }
   uint16_t* bufA = reinterpret_cast<uint16_t*>(sm + kFwdLdsWeights + grp * kFwdLdsSample);
   uint16_t* bufB = bufA + kFwdBufA;
-  // every group runs the same number of rounds (the barriers are block-wide);
-  // a group past the last sample idles through its round
-  for (int s0 = blockIdx.x * SPB; s0 < n; s0 += gridDim.x * SPB) {
-    const int s = s0 + grp;
-    const bool act = s < n;
-    __syncthreads();  // weights loaded / previous round's buffers free
-    if (act) {
-      // x: NCHW [4][16][16] -> NHWC [16][16][4] in bufB
-      const uint16_t* xs = x + (size_t)s * kIn;
-      for (int i = gt; i < 256; i += GT)
+  uint16_t* bufX = bufB + kXElems;  // a4, past the network input in bufB
+  static_assert(kXElems + 16 * CH <= kFwdBufB, "a4 beside x");
+  const int oA = kFwdLdsWeights + grp * kFwdLdsSample, oB = oA + kFwdBufA * 2;
+  const int oZ = kFwdLdsWeights + SPB * kFwdLdsSample;
+  if (tid < kFwdZero / 4) reinterpret_cast<uint32_t*>(sm + oZ)[tid] = 0u;
+  FwdOffsets fo;
+  {
+    const int r = lane & 15, g = lane >> 4;
 #pragma unroll
-        for (int c = 0; c < C1; ++c) bufB[C1 * i + c] = xs[c * 256 + i];
+    for (int ks = 0; ks < 3; ++ks) {
+      const int tap = 4 * ks + g;
+      fo.c1[ks] = tap < 9 ? oB + ((4 * part + tap / 3) * kXW + r + tap % 3) * C1 * 2 : oZ;
+      asm volatile("" : "+v"(fo.c1[ks]));
     }
-    __syncthreads();
+    tap_offsets<16, 8, 2, 1>(fo.c2, oA, oZ, part * 16 + r, g);
+    tap_offsets<8, 8, 1, 2>(fo.c3, oB, oZ, part * 16 + r, g);
+    fo.wt = CH * kK1S * 2 + (r * 9 * CH + 4 * (g ^ ((r >> 1) & 7))) * 2;
+    static_assert(CH * kK1S * 2 % 64 == 0, "XOR 32 stays in a tap's 64 bytes");
+  }
+  // x: NCHW [4][16][16] -> NHWC in bufB with its border, two positions per
+  // thread of parts 2 and 3 (x may be aligned to its elements only)
+  const int xq = 2 * (gt - GT / 2);
+  auto fetch = [&](int s, uint32_t (&v)[C1]) {
+#pragma unroll
+    for (int c = 0; c < C1; ++c)
+      v[c] = part >= 2 && s < n
+                 ? reinterpret_cast<const UnalignedU32*>(x + (size_t)s * kIn + c * 256 + xq)->v
+                 : 0u;
+  };
+  auto put = [&](const uint32_t (&v)[C1]) {
+    if (part < 2) return;
+    uint2* d = reinterpret_cast<uint2*>(bufB);  // one position each
+    const int q = (xq / 16 + 1) * kXW + xq % 16 + 1;
+    d[q] = make_uint2((v[0] & 0xffffu) | (v[1] << 16), (v[2] & 0xffffu) | (v[3] << 16));
+    d[q + 1] = make_uint2((v[0] >> 16) | (v[1] & 0xffff0000u), (v[2] >> 16) | (v[3] & 0xffff0000u));
+    // the border (the second layer's output lay there): rows 0 and 17, then
+    // both sides of the rows between
+    const int e = xq / 2;
+    if (e < 2 * kXW) d[e < kXW ? e : (kXW - 1) * kXW + e - kXW] = make_uint2(0u, 0u);
+    else if (e < 2 * kXW + 32)
+      d[((e - 2 * kXW) / 2 + 1) * kXW + ((e & 1) ? kXW - 1 : 0)] = make_uint2(0u, 0u);
+  };
+  // the head of sample s, whose a4 is complete, by the wave of part 0
+  auto head = [&](int s) {
+    if (TRAIN) store_acts<0>(bufX, acts + (size_t)s * kActN + kActA4, 16, gt, GT);
+    if (part != 0) return;
+    // head (fp32): f = p * 32 + c, eight features per lane
+    float o[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int f = lane * 8 + k;
+      const float a = bf2f(bufX[f]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) o[j] += P[kOffWh + j * 512 + f] * a;
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) o[j] += __shfl_xor(o[j], off);
+    if (lane != 0) return;
+    const float o0 = o[0] + P[kOffBh], o1 = o[1] + P[kOffBh + 1], o2 = o[2] + P[kOffBh + 2];
+    if (out) {
+      out[(size_t)s * 3] = o0;
+      out[(size_t)s * 3 + 1] = o1;
+      out[(size_t)s * 3 + 2] = o2;
+    }
+    if (po.centre) {
+      // window centre: prediction rounded half up, kept inside the search range
+      int cx = (int)floorf(8.f * o0 + 0.5f), cy = (int)floorf(8.f * o1 + 0.5f);
+      cx = min(max(cx, -po.clampc), po.clampc);
+      cy = min(max(cy, -po.clampc), po.clampc);
+      const int t = po.tiles ? po.tiles[s] : s;
+      const int fb = o2 >= po.conf_logit ? 0 : 1;
+      po.centre[2 * t] = cx;
+      po.centre[2 * t + 1] = cy;
+      po.fallback[t] = (uint8_t)fb;
+      if (po.lists) po.lists[fb * po.ntiles + atomicAdd(&po.counts[fb], 1)] = t;
+    }
+  };
+  // every group runs the same number of rounds (the barriers are block-wide);
+  // a group past the last sample idles through its round. The next sample's
+  // input is fetched during a round and written beside the last layer, and the
+  // head runs beside the next sample's first layer: four barriers per round.
+  const int step = gridDim.x * SPB;
+  int s = blockIdx.x * SPB + grp;
+  uint32_t xv[C1];
+  fetch(s, xv);
+  put(xv);
+  int prev = -1;  // the sample whose head is due
+  for (int s0 = blockIdx.x * SPB; s0 < n; s0 += step, s += step) {
+    const bool act = s < n;
+    asm volatile("" : "+v"(lane));  // (the stores' and the head's addresses: formed again)
+    uint16_t* as = acts + (size_t)s * kActN;
+    __syncthreads();  // weights and x in place, the previous round's a4 too
+    if (prev >= 0) head(prev);
     if (act) {
       if (TRAIN)
-        for (int i = gt; i < kIn; i += GT) acts[(size_t)s * kActN + kActX + i] = bufB[i];
-      conv1_fwd_part(bufB, sW1, sb, bufA, lane, part);  // a1 -> bufA
+        for (int i = gt; i < kIn; i += GT)
+          as[kActX + i] = bufB[((i >> 6) * kXW + kXW + 1) * C1 + (i & 63)];
+      conv1_fwd_part(sm, fo, sW1, sb, bufA, lane, part);  // a1 -> bufA
     }
-    __syncthreads();
-    if (act) conv_fwd_part<16, 8, 2>(bufA, sW, sb + CH, bufB, lane, part);  // a2 -> bufB
+    fetch(s + step, xv);
     __syncthreads();
     if (act) {
-      if (TRAIN) {  // stored unpadded: position * 32 + channel
-        uint16_t* a = acts + (size_t)s * kActN;
-        store_acts(bufA, a + kActA1, 256, gt, GT);
-        store_acts(bufB, a + kActA2, 64, gt, GT);
-      }
+      if (TRAIN) store_acts<1>(bufA, as + kActA1, 256, gt, GT);
+      conv_fwd_part<4, 2>(sm, fo.c2, fo.wt, sb + CH, bufB, lane, part);  // a2 -> bufB
     }
-    __syncthreads();  // a1 copied out before a3 overwrites it
-    if (act) conv_fwd_part<8, 8, 1>(bufB, sW + CH * kWS, sb + 2 * CH, bufA, lane, part);  // a3 -> bufA
     __syncthreads();
-    if (act) conv_fwd_part<8, 4, 2>(bufA, sW + 2 * CH * kWS, sb + 3 * CH, bufB, lane, part);  // a4 -> bufB
+    if (act) {
+      if (TRAIN) store_acts<2>(bufB, as + kActA2, 64, gt, GT);
+      conv_fwd_part<4, 3>(sm, fo.c3, fo.wt + 2 * kWp, sb + 2 * CH, bufA, lane, part);  // a3 -> bufA
+    }
     __syncthreads();
-    if (act && TRAIN) {
-      uint16_t* a = acts + (size_t)s * kActN;
-      store_acts(bufA, a + kActA3, 64, gt, GT);
-      store_acts(bufB, a + kActA4, 16, gt, GT);
+    if (act) {
+      if (TRAIN) store_acts<3>(bufA, as + kActA3, 64, gt, GT);
+      int c4[9];  // (formed here: kept too, they would spill)
+      tap_offsets<8, 4, 2, 3>(c4, oA, oZ, lane & 15, lane >> 4);
+      conv_fwd_part<1, 0>(sm, c4, fo.wt + 4 * kWp, sb + 3 * CH, bufX, lane, part);  // a4
     }
-    if (act && part == 0) {
-      // head (fp32): f = p * 32 + c, eight features per lane
-      float o[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int f = lane * 8 + k;
-        const float a = bf2f(bufB[(f >> 5) * kPS + (f & 31)]);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) o[j] += P[kOffWh + j * 512 + f] * a;
-      }
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) o[j] += __shfl_xor(o[j], off);
-      if (lane == 0) {
-        const float o0 = o[0] + P[kOffBh], o1 = o[1] + P[kOffBh + 1], o2 = o[2] + P[kOffBh + 2];
-        if (out) {
-          out[(size_t)s * 3] = o0;
-          out[(size_t)s * 3 + 1] = o1;
-          out[(size_t)s * 3 + 2] = o2;
-        }
-        if (po.centre) {
-          // window centre: prediction rounded half up, kept inside the search range
-          int cx = (int)floorf(8.f * o0 + 0.5f), cy = (int)floorf(8.f * o1 + 0.5f);
-          cx = min(max(cx, -po.clampc), po.clampc);
-          cy = min(max(cy, -po.clampc), po.clampc);
-          const int t = po.tiles ? po.tiles[s] : s;
-          const int fb = o2 >= po.conf_logit ? 0 : 1;
-          po.centre[2 * t] = cx;
-          po.centre[2 * t + 1] = cy;
-          po.fallback[t] = (uint8_t)fb;
-          if (po.lists) po.lists[fb * po.ntiles + atomicAdd(&po.counts[fb], 1)] = t;
-        }
-      }
-    }
+    put(xv);
+    prev = act ? s : -1;
   }
+  __syncthreads();
+  if (prev >= 0) head(prev);
 }
 
 // da_in = transposed conv of dz (LDS, [HOUT^2] rows of kPS) with W (WT, ci

@@ -117,6 +117,24 @@ def test_search_at_block_edges(lnr, ctx, nx, ny, R, P):
     assert np.array_equal(ssd[v].view(np.uint32), want[v])
 
 
+# the last one-sample workgroups and the first four-sample ones; rounds that
+# leave 3, 2 and 1 of a workgroup's samples, a last round of few workgroups; an
+# input aligned to its elements only. A sample's result does not depend on its
+# place: the one-sample workgroups', which the oracle checks, give the same bits
+@pytest.mark.parametrize("n", [256, 257, 1023, 1030, 2053])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_forward_rounds(lnr, ctx, n, shift):
+    P = synth.proposal_params(12, head_scale=4.0)
+    lnr.proposal_set(ctx, torch.from_numpy(P))
+    xb = _bf16_bits(_inputs(60 + n, n)).cuda()
+    buf = torch.empty(xb.numel() + shift, dtype=xb.dtype, device="cuda")
+    buf[shift:] = xb.reshape(-1)
+    got = lnr.proposal_forward(ctx, buf[shift:].view(xb.shape))
+    want = torch.cat([lnr.proposal_forward(ctx, xb[i:i + 200].contiguous())
+                      for i in range(0, n, 200)])
+    assert torch.equal(got, want)
+
+
 # one word / two; the narrow and the wide hypothesis blocks; the last size of
 # one fit block and the first of several; more iterations than blocks take at
 # once, and counts that leave a group short; few matches with repeated draws
