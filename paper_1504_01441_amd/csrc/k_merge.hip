@@ -14,12 +14,12 @@
 //             the Laplacian's rows are read once, and take the left and right
 //             neighbours from the adjacent lanes.
 //  k_reduce:  REDUCE ([1 4 6 4 1]/16 separable, clamped, even samples) of
-//             every weight and image plane of one level, through LDS.
+//             every weight and image plane of one level, in registers.
 //  k_blend:   from the top level down, R_l = sum_k W_k,l (G_k,l - E(G_k,l+1))
-//             + E(R_l+1), E the EXPAND rule, on 64x16 tiles whose coarse
-//             neighbourhoods are staged (and row-expanded) in LDS; level 0
-//             goes to the output. Small levels use k_blend_px instead (one
+//             + E(R_l+1), E the EXPAND rule, on 64x32 tiles whose coarse
+//             neighbourhoods are staged in LDS; level 0 goes to the output. Small levels use k_blend_px instead (one
 //             thread per pixel and channel, samples read directly).
+#include "lnr_device.h"
 #include "lnr_internal.h"
 
 namespace lnr {
@@ -81,7 +81,8 @@ __global__ __launch_bounds__(256) void k_ssim(const float* __restrict__ a, SsimM
     for (int i = 0; i < NR; ++i) {  // every load in flight before the sums
       // (32-bit byte offsets, since a plane has at most 2^26 pixels: 64-bit
       // addresses of all the loads would cost a block per CU)
-      const uint32_t o = 4u * ((uint32_t)min(max(oy - R + i, 0), H - 1) * (uint32_t)W + (uint32_t)gx);
+      const uint32_t o =
+          4u * ((uint32_t)min(max(oy - R + i, 0), H - 1) * (uint32_t)W + (uint32_t)gx);
       pa[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a) + o);
       pb[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + o);
     }
@@ -182,6 +183,22 @@ __device__ inline double raw_weight(int ch, double gu, double gl, double gr, dou
   return wt + 1e-12;
 }
 
+// the value of the lane before (kWaveShr1) or after, on the vector ALU; the
+// wave's first or last lane gets 0
+constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;
+template <int CTRL>
+__device__ inline double from_lane(double v) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false),
+      __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false));
+}
+
+template <int CTRL>
+__device__ inline float from_lane(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
 constexpr int kWeightRows = 8;
 constexpr int kWeightCols = 62;  // output columns per wave (lanes 1..62)
 
@@ -192,7 +209,9 @@ constexpr int kWeightCols = 62;  // output columns per wave (lanes 1..62)
 // neighbours); the left and right neighbours' grey values come from the
 // adjacent lanes by shuffle. The samples of the next row are loaded before
 // the current row's weights are formed and stored, so one row's loads are
-// always in flight.
+// always in flight. Bound by its instructions (295 per wave and row, 40 of the
+// 48 us of two 5 MP frames); 52 us with the neighbours' grey values through
+// the LDS unit and a division per weight.
 template <int NMAX>
 __global__ __launch_bounds__(256) void k_weights(FramePtrs f, int n, int ch, int W, int H,
                                                  int ref, float two_se2) {
@@ -202,7 +221,6 @@ __global__ __launch_bounds__(256) void k_weights(FramePtrs f, int n, int ch, int
   const int x = (bx * 4 + wave) * kWeightCols + lane - 1;
   const int xc = min(max(x, 0), W - 1);
   const bool writes = lane >= 1 && lane <= kWeightCols && x < W;
-  const int lsrc = lane > 0 ? lane - 1 : 0, rsrc = lane < 63 ? lane + 1 : 63;
   const int y0 = by * kWeightRows, y1 = min(y0 + kWeightRows, H);
   const size_t plane = (size_t)W * H;
   auto ld = [&](const float* I, size_t o, float& r, float& g, float& b) {
@@ -261,7 +279,7 @@ __global__ __launch_bounds__(256) void k_weights(FramePtrs f, int n, int ch, int
       }
       const bool warped = k != ref;
       const double gd = grey_of(ch, Dr[k], Dg[k], Db[k]);
-      const double gl = __shfl(gc[k], lsrc), gr = __shfl(gc[k], rsrc);
+      const double gl = from_lane<kWaveShr1>(gc[k]), gr = from_lane<kWaveShl1>(gc[k]);
       wk[k] = (float)raw_weight(ch, gu[k], gl, gr, gd, gc[k], cr[k], cg[k], cb[k], warped, S[k],
                                 two_se2);
       sum += (double)wk[k];
@@ -271,9 +289,12 @@ __global__ __launch_bounds__(256) void k_weights(FramePtrs f, int n, int ch, int
     }
     if (writes) {
 #pragma unroll
-      for (int k = 0; k < NMAX; ++k) {
+      for (int k = 0; k < NMAX; k += 2) {  // two at a time share the reciprocal
         if (k >= n) continue;
-        f.wout[k][o] = (float)((double)wk[k] / sum);
+        double q0, q1;
+        recip_quotients((double)wk[k], k + 1 < n ? (double)wk[k + 1] : 0.0, sum, q0, q1);
+        f.wout[k][o] = (float)q0;
+        if (k + 1 < n) f.wout[k + 1][o] = (float)q1;
       }
     }
   }
@@ -331,46 +352,67 @@ struct MapPtrs {
   float* out[kMaxMaps];
 };
 
-constexpr int kRedTW = 128, kRedTH = 8;
+constexpr int kRedCols = 62;  // output columns per wave (lanes 1..62)
 
+// A wave forms ROWS output rows of 62 columns of one plane: a lane loads the
+// two source columns of its output in every source row, all of them in flight
+// before the first sum, and takes the neighbours' from the adjacent lanes.
+// Bound by memory at level 0 of a large frame. The staged tile this replaces
+// spent 38 of its 40 us (eight planes of two 5 MP frames) on instructions, 150
+// per output, most of them index arithmetic; with two rows in flight at a time
+// instead of all it was as slow, by latency. 40 -> 38 us at
+// that level, 14.2 -> 12.3 at the next, 6.3 -> 5.5.
+template <int ROWS>
 __global__ __launch_bounds__(256) void k_reduce(MapPtrs m, int w, int h, int w2, int h2) {
-  __shared__ float src[2 * kRedTH + 3][2 * kRedTW + 3];
-  __shared__ float hb[2 * kRedTH + 3][kRedTW];
-  const float kf[5] = {1.f / 16, 4.f / 16, 6.f / 16, 4.f / 16, 1.f / 16};
-  const float* in = m.in[blockIdx.z];
-  float* out = m.out[blockIdx.z];
-  const int ox = blockIdx.x * kRedTW, oy = blockIdx.y * kRedTH;
-  constexpr int rows = 2 * kRedTH + 3, cols = 2 * kRedTW + 3;
-  constexpr int per = (rows * cols + 255) / 256;
-  float v[per];
+  const float* __restrict__ in = m.in[blockIdx.z];
+  float* __restrict__ out = m.out[blockIdx.z];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int X0 = blockIdx.x * kRedCols - 1, X = X0 + lane;
+  const int oy0 = (blockIdx.y * 4 + wave) * ROWS;
+  if (oy0 >= h2) return;
+  constexpr int N = 2 * ROWS + 3;
+  float a[N], b[N];
+  // (32-bit byte offsets: a plane has at most 2^26 pixels)
+  const char* p = reinterpret_cast<const char*>(in);
+  auto row_at = [&](int i) {
+    return 4u * ((uint32_t)min(max(2 * oy0 - 2 + i, 0), h - 1) * (uint32_t)w);
+  };
+  if (X0 >= 0 && 2 * (X0 + 63) + 1 < w) {
+    struct __attribute__((packed, aligned(4))) Pair {
+      float a, b;
+    };
 #pragma unroll
-  for (int q = 0; q < per; ++q) {  // all loads in flight before the LDS stores
-    const int i = threadIdx.x + 256 * q;
-    const int yy = i / cols, xx = i % cols;
-    const int gy = min(max(2 * oy - 2 + yy, 0), h - 1), gx = min(max(2 * ox - 2 + xx, 0), w - 1);
-    v[q] = i < rows * cols ? in[(size_t)gy * w + gx] : 0.f;
-  }
+    for (int i = 0; i < N; ++i) {
+      const Pair v = *reinterpret_cast<const Pair*>(p + (row_at(i) + 8u * (uint32_t)X));
+      a[i] = v.a;
+      b[i] = v.b;
+    }
+  } else {
+    const uint32_t c0 = 4u * (uint32_t)min(max(2 * X, 0), w - 1);
+    const uint32_t c1 = 4u * (uint32_t)min(max(2 * X + 1, 0), w - 1);
 #pragma unroll
-  for (int q = 0; q < per; ++q) {
-    const int i = threadIdx.x + 256 * q;
-    if (i < rows * cols) src[i / cols][i % cols] = v[q];
+    for (int i = 0; i < N; ++i) {
+      a[i] = *reinterpret_cast<const float*>(p + (row_at(i) + c0));
+      b[i] = *reinterpret_cast<const float*>(p + (row_at(i) + c1));
+    }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < rows * kRedTW; i += 256) {
-    const int yy = i / kRedTW, xx = i % kRedTW;
-    float s = 0.f;
-    for (int k = 0; k < 5; ++k) s += kf[k] * src[yy][2 * xx + k];
-    hb[yy][xx] = s;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < kRedTH * kRedTW; i += 256) {
-    const int yy = i / kRedTW, xx = i % kRedTW;
-    const int gy = oy + yy, gx = ox + xx;
-    if (gy >= h2 || gx >= w2) continue;
-    float s = 0.f;
-    for (int k = 0; k < 5; ++k) s += kf[k] * hb[2 * yy + k][xx];
-    out[(size_t)gy * w2 + gx] = s;
-  }
+  // [1 4 6 4 1] / 16 in that order (every product but the middle one is exact)
+  auto taps = [](float v0, float v1, float v2, float v3, float v4) {
+    float s = fmaf(0.25f, v1, 0.0625f * v0);
+    s += 0.375f * v2;
+    return fmaf(0.0625f, v4, fmaf(0.25f, v3, s));
+  };
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    a[i] = taps(from_lane<kWaveShr1>(a[i]), from_lane<kWaveShr1>(b[i]), a[i], b[i],
+                from_lane<kWaveShl1>(a[i]));
+  if (lane < 1 || lane > kRedCols || X >= w2) return;
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j)
+    if (oy0 + j < h2)
+      out[(uint32_t)(oy0 + j) * (uint32_t)w2 + (uint32_t)X] =
+          taps(a[2 * j], a[2 * j + 1], a[2 * j + 2], a[2 * j + 3], a[2 * j + 4]);
 }
 
 struct BlendPtrs {
@@ -381,177 +423,154 @@ struct BlendPtrs {
   float* out[3];             // collapsed result at level l
 };
 
-constexpr int kBW = 64, kBH = 16;                 // fine output tile
+constexpr int kBW = 64, kBH = 32;                 // fine output tile
 constexpr size_t kBlendPxMax = 1 << 18;           // levels up to this size: k_blend_px
 constexpr int kCW = kBW / 2 + 2, kCH = kBH / 2 + 2;  // coarse tile with its EXPAND halo
+constexpr int kCT = kCW * kCH;
 
-// One 64 x 16 tile of level l, channels [c0, c0 + cg):
+// EXPAND (clamped coarse indices, rows first, then columns): even samples 2i
+// (c[i-1] + 6 c[i] + c[i+1]) / 8, odd ones 2i + 1 (c[i] + c[i+1]) / 2.
+__device__ inline float ex_even(float a, float m, float p) {
+  return fmaf(0.75f, m, 0.125f * (a + p));
+}
+__device__ inline float ex_odd(float m, float p) { return 0.5f * (m + p); }
+
+// the four fine columns from the even one of staged column i + 1 on (row + i
+// is 8-byte aligned)
+__device__ inline float4 ex_row4(const float* row) {
+  const float2 u = *reinterpret_cast<const float2*>(row);
+  const float2 v = *reinterpret_cast<const float2*>(row + 2);
+  return make_float4(ex_even(u.x, u.y, v.x), ex_odd(u.y, v.x), ex_even(u.y, v.x, v.y),
+                     ex_odd(v.x, v.y));
+}
+
+// two fine rows of four columns: t at the coarse row and column before
+__device__ inline void expand_tile8(const float* t, float4& e, float4& o) {
+  const float4 a = ex_row4(t), m = ex_row4(t + kCW), p = ex_row4(t + 2 * kCW);
+  e = make_float4(ex_even(a.x, m.x, p.x), ex_even(a.y, m.y, p.y), ex_even(a.z, m.z, p.z),
+                  ex_even(a.w, m.w, p.w));
+  o = make_float4(ex_odd(m.x, p.x), ex_odd(m.y, p.y), ex_odd(m.z, p.z), ex_odd(m.w, p.w));
+}
+
+// four floats of a row that is aligned to its elements only
+struct __attribute__((packed, aligned(4))) Float4 {
+  float x, y, z, w;
+};
+__device__ inline float4 load4(const float* p, int valid) {  // the first `valid` of them
+  if (valid >= 4) {
+    const Float4 v = *reinterpret_cast<const Float4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  return make_float4(p[0], valid > 1 ? p[1] : 0.f, valid > 2 ? p[2] : 0.f, 0.f);
+}
+__device__ inline void store4(float* p, const float4& v, int valid) {
+  if (valid >= 4) {
+    *reinterpret_cast<Float4*>(p) = Float4{v.x, v.y, v.z, v.w};
+    return;
+  }
+  p[0] = v.x;
+  if (valid > 1) p[1] = v.y;
+  if (valid > 2) p[2] = v.z;
+}
+__device__ inline void blend4(float4& acc, const float4& w, const float4& g, const float4& e) {
+  acc.x = fmaf(w.x, g.x - e.x, acc.x);
+  acc.y = fmaf(w.y, g.y - e.y, acc.y);
+  acc.z = fmaf(w.z, g.z - e.z, acc.z);
+  acc.w = fmaf(w.w, g.w - e.w, acc.w);
+}
+
+// One 64 x 32 tile of a level below the top, channels [c0, c0 + cg):
 //   R_l = sum_k W_k (G_k - E(G_k,l+1)) + E(R_l+1).
-// EXPAND (even 2i: (c[i-1] + 6 c[i] + c[i+1]) / 8, odd 2i+1: (c[i] + c[i+1]) / 2,
-// clamped coarse indices; rows first, then columns) reads the coarse planes
-// from LDS tiles (kCH x kCW, clamped at load) loaded once per block; each
-// thread expands the coarse rows it needs in registers. Each thread owns one
-// column of the tile (4 rows), or four pixels of a row, and reads each weight
-// once.
-// EXPAND at fine column 2 (li + cx0) + (xeven ? 0 : 1) of one staged row
-__device__ inline float ex_row(const float* row, int li, bool xeven) {
-  return xeven ? (row[li - 1] + 6.f * row[li] + row[li + 1]) / 8.f
-               : (row[li] + row[li + 1]) / 2.f;
-}
-
-__device__ inline float expand_tile(const float* t, int li, bool xeven, int lj, bool yeven) {
-  const float m = ex_row(t + lj * kCW, li, xeven), p = ex_row(t + (lj + 1) * kCW, li, xeven);
-  if (yeven) {
-    const float a = ex_row(t + (lj - 1) * kCW, li, xeven);
-    return (a + 6.f * m + p) / 8.f;
-  }
-  return (m + p) / 2.f;
-}
-
-// the four fine columns from the even one of coarse index li (li, li + 1)
-__device__ inline float4 ex_row4(const float* row, int li) {
-  const float a = row[li - 1], m = row[li], p = row[li + 1], q = row[li + 2];
-  return make_float4((a + 6.f * m + p) / 8.f, (m + p) / 2.f, (m + 6.f * p + q) / 8.f,
-                     (p + q) / 2.f);
-}
-
-__device__ inline float4 expand_tile4(const float* t, int li, int lj, bool yeven) {
-  const float4 m = ex_row4(t + lj * kCW, li), p = ex_row4(t + (lj + 1) * kCW, li);
-  if (yeven) {
-    const float4 a = ex_row4(t + (lj - 1) * kCW, li);
-    return make_float4((a.x + 6.f * m.x + p.x) / 8.f, (a.y + 6.f * m.y + p.y) / 8.f,
-                       (a.z + 6.f * m.z + p.z) / 8.f, (a.w + 6.f * m.w + p.w) / 8.f);
-  }
-  return make_float4((m.x + p.x) / 2.f, (m.y + p.y) / 2.f, (m.z + p.z) / 2.f, (m.w + p.w) / 2.f);
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_blend(BlendPtrs b, int n, int c0, int cg, int w, int h,
-                                               int cw, int chh, int top, int vec) {
-  extern __shared__ float sm[];
+// EXPAND reads the coarse planes from LDS tiles (kCH x kCW, clamped at load)
+// loaded once per block, a thread's places in them found once; a thread owns
+// two rows of four pixels, which share their expanded coarse rows, and reads
+// each weight once. With one row per thread and the staging's places found
+// for every plane by divisions the kernel was bound by its instructions, 345
+// per pixel (44 of the 51 us of two 5 MP frames' level 0);
+// now 46 us there, by memory, 17.7 -> 14 at the next level.
+__global__ __launch_bounds__(256) void k_blend(BlendPtrs b, int n, int c0, int cg, int w, int h,
+                                               int cw, int chh) {
+  extern __shared__ __align__(16) float sm[];  // plane m = cc (n + 1) + k, k = n: R
   const int tid = threadIdx.x;
   int bx, by;
   xcd_block(gridDim.x, gridDim.y, bx, by);
   const int ox = bx * kBW, oy = by * kBH;
-  const int cx0 = (ox >> 1) - 1, cy0 = (oy >> 1) - 1;
-  const int nm = top ? 0 : (n + 1) * cg;  // plane m = cc (n + 1) + k, k = n: R
-  float* ct = sm;                         // [nm][kCH][kCW] coarse tiles
-  if (!top) {
-    const int ntot = nm * kCH * kCW;
-    for (int i0 = tid; i0 < ntot; i0 += 12 * 256) {  // twelve loads in flight per thread
-      float v[12];
+  {
+    constexpr int U = (kCT + 255) / 256;
+    uint32_t off[U];
 #pragma unroll
-      for (int u = 0; u < 12; ++u) {
-        const int i = i0 + 256 * u;
-        v[u] = 0.f;
-        if (i < ntot) {
-          const int m = i / (kCH * kCW), r = (i / kCW) % kCH, q = i % kCW;
-          const int cc = m / (n + 1), k = m % (n + 1);
-          const float* src = k < n ? b.gc[k][c0 + cc] : b.rc[c0 + cc];
-          const int gy = min(max(cy0 + r, 0), chh - 1), gx = min(max(cx0 + q, 0), cw - 1);
-          v[u] = src[(size_t)gy * cw + gx];
+    for (int u = 0; u < U; ++u) {
+      const int i = tid + 256 * u, r = i / kCW, q = i % kCW;
+      const int gy = min(max((oy >> 1) - 1 + r, 0), chh - 1);
+      const int gx = min(max((ox >> 1) - 1 + q, 0), cw - 1);
+      off[u] = (uint32_t)gy * (uint32_t)cw + (uint32_t)gx;  // (in bounds past the tile too)
+    }
+    for (int cc = 0; cc < cg; ++cc)
+      for (int k0 = 0; k0 <= n; k0 += 4) {  // four planes' loads in flight
+        float v[4][U];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int k = k0 + j;
+          if (k > n) break;
+          const float* __restrict__ src = k < n ? b.gc[k][c0 + cc] : b.rc[c0 + cc];
+#pragma unroll
+          for (int u = 0; u < U; ++u) v[j][u] = src[off[u]];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (k0 + j > n) break;
+          float* ct = sm + (cc * (n + 1) + k0 + j) * kCT;
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (tid + 256 * u < kCT) ct[tid + 256 * u] = v[j][u];
         }
       }
-#pragma unroll
-      for (int u = 0; u < 12; ++u)
-        if (i0 + 256 * u < ntot) ct[i0 + 256 * u] = v[u];
-    }
     __syncthreads();
   }
-  if (vec) {
-    // rows of 16-byte aligned planes, width a multiple of 4: a thread owns four
-    // consecutive pixels of one row (float4 loads and stores)
-    const int xq = 4 * (tid & 15), y = oy + (tid >> 4);
-    const int x = ox + xq;
-    if (x >= w || y >= h) return;
-    const size_t o = (size_t)y * w + x;
-    const int li = (x >> 1) - cx0, lj = (y >> 1) - cy0;  // local coarse indices
-    const bool even = (y & 1) == 0;
-    float4 acc[3];
+  const int xq = 4 * (tid & 15), yq = 2 * (tid >> 4);
+  const int x = ox + xq, y = oy + yq;
+  if (x >= w || y >= h) return;
+  const int valid = w - x;
+  const uint32_t o0 = (uint32_t)y * (uint32_t)w + (uint32_t)x;
+  const uint32_t o1 = y + 1 < h ? o0 + (uint32_t)w : o0;  // (the last row again, not stored)
+  const float* t = sm + (yq >> 1) * kCW + (xq >> 1);
+  float4 acc[3][2];
 #pragma unroll
-    for (int cc = 0; cc < 3; ++cc) acc[cc] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k = 0; k < n; ++k) {
-      const float4 wv = *reinterpret_cast<const float4*>(b.w[k] + o);
-      float4 gv[3];
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc)
-        gv[cc] = cc < cg ? *reinterpret_cast<const float4*>(b.g[k][c0 + cc] + o)
-                         : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) {
-        if (cc >= cg) break;
-        const float4 e = top ? make_float4(0.f, 0.f, 0.f, 0.f)
-                             : expand_tile4(ct + (cc * (n + 1) + k) * kCH * kCW, li, lj, even);
-        acc[cc].x += wv.x * (gv[cc].x - e.x);
-        acc[cc].y += wv.y * (gv[cc].y - e.y);
-        acc[cc].z += wv.z * (gv[cc].z - e.z);
-        acc[cc].w += wv.w * (gv[cc].w - e.w);
-      }
-    }
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) {
-      if (cc >= cg) break;
-      float4 v = acc[cc];
-      if (!top) {
-        const float4 e = expand_tile4(ct + (cc * (n + 1) + n) * kCH * kCW, li, lj, even);
-        v.x += e.x; v.y += e.y; v.z += e.z; v.w += e.w;
-      }
-      *reinterpret_cast<float4*>(b.out[c0 + cc] + o) = v;
-    }
-    return;
-  }
-  // thread = one column of the tile (lanes are consecutive pixels), 4 rows
-  const int fx = tid & 63, fy0 = tid >> 6;
-  const int x = ox + fx;
-  if (x >= w) return;
-  const int li = (x >> 1) - cx0;
-  const bool xeven = (x & 1) == 0;
-  float acc[3][4];
-  for (int cc = 0; cc < cg; ++cc)
-    for (int q = 0; q < 4; ++q) acc[cc][q] = 0.f;
+  for (int cc = 0; cc < 3; ++cc) acc[cc][0] = acc[cc][1] = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int k = 0; k < n; ++k) {
-    // this frame's weights and image values first (16 loads in flight)
-    float wv[4], gv[3][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int y = oy + fy0 + 4 * q;
-      wv[q] = y < h ? b.w[k][(size_t)y * w + x] : 0.f;
-    }
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int y = oy + fy0 + 4 * q;
-        gv[cc][q] = cc < cg && y < h ? b.g[k][c0 + cc][(size_t)y * w + x] : 0.f;
-      }
+    const float4 w0 = load4(b.w[k] + o0, valid), w1 = load4(b.w[k] + o1, valid);
+    float4 g0[3], g1[3];
 #pragma unroll
     for (int cc = 0; cc < 3; ++cc) {
       if (cc >= cg) break;
-      const float* t = ct + (cc * (n + 1) + k) * kCH * kCW;
+      g0[cc] = load4(b.g[k][c0 + cc] + o0, valid);
+      g1[cc] = load4(b.g[k][c0 + cc] + o1, valid);
+    }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int y = oy + fy0 + 4 * q;
-        if (y >= h) break;
-        const float e = top ? 0.f : expand_tile(t, li, xeven, (y >> 1) - cy0, (y & 1) == 0);
-        acc[cc][q] += wv[q] * (gv[cc][q] - e);
-      }
+    for (int cc = 0; cc < 3; ++cc) {
+      if (cc >= cg) break;
+      float4 e0, e1;
+      expand_tile8(t + (cc * (n + 1) + k) * kCT, e0, e1);
+      blend4(acc[cc][0], w0, g0[cc], e0);
+      blend4(acc[cc][1], w1, g1[cc], e1);
     }
   }
-  for (int cc = 0; cc < cg; ++cc) {
-    const float* t = ct + (cc * (n + 1) + n) * kCH * kCW;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int y = oy + fy0 + 4 * q;
-      if (y >= h) break;
-      const float v =
-          top ? acc[cc][q] : acc[cc][q] + expand_tile(t, li, xeven, (y >> 1) - cy0, (y & 1) == 0);
-      b.out[c0 + cc][(size_t)y * w + x] = v;
-    }
+  for (int cc = 0; cc < 3; ++cc) {
+    if (cc >= cg) break;
+    float4 e0, e1;
+    expand_tile8(t + (cc * (n + 1) + n) * kCT, e0, e1);
+    const float4 u = acc[cc][0], v = acc[cc][1];
+    float* out = b.out[c0 + cc];
+    store4(out + o0, make_float4(u.x + e0.x, u.y + e0.y, u.z + e0.z, u.w + e0.w), valid);
+    if (y + 1 < h)
+      store4(out + o1, make_float4(v.x + e1.x, v.y + e1.y, v.z + e1.z, v.w + e1.w), valid);
   }
 }
 
 // A pixel of EXPAND(c) at (x, y) of the finer level: rows of the coarse plane
-// (cw x chh, clamped indices) expanded along x first, then along y, with the
-// arithmetic of k_blend's LDS path.
+// (cw x chh, clamped indices) expanded along x first, then along y, as k_blend
+// does from its staged tiles.
 __device__ inline float expand_px(const float* __restrict__ c, int cw, int chh, int x, int y) {
   const int i = x >> 1, j = y >> 1;
   const int xa = max(i - 1, 0), xm = min(i, cw - 1), xp = min(i + 1, cw - 1);
@@ -560,9 +579,9 @@ __device__ inline float expand_px(const float* __restrict__ c, int cw, int chh, 
   for (int q = 0; q < 3; ++q) {
     const float* row = c + (size_t)min(max(j - 1 + q, 0), chh - 1) * cw;
     const float a = row[xa], m = row[xm], p = row[xp];
-    rv[q] = (x & 1) == 0 ? (a + 6.f * m + p) / 8.f : (m + p) / 2.f;
+    rv[q] = (x & 1) == 0 ? ex_even(a, m, p) : ex_odd(m, p);
   }
-  return (y & 1) == 0 ? (rv[0] + 6.f * rv[1] + rv[2]) / 8.f : (rv[1] + rv[2]) / 2.f;
+  return (y & 1) == 0 ? ex_even(rv[0], rv[1], rv[2]) : ex_odd(rv[1], rv[2]);
 }
 
 // Small levels: one thread per pixel and channel (blockIdx.y), every sample
@@ -691,8 +710,15 @@ hipError_t launch_merge(int n, int ch, int W, int H, const float* const* imgs,
       mp.in[z] = plane_ptr(z, l - 1);
       mp.out[z] = plane_ptr(z, l);
     }
-    dim3 g((lw[l] + kRedTW - 1) / kRedTW, (lh[l] + kRedTH - 1) / kRedTH, maps);
-    LNR_LAUNCH(k_reduce, g, dim3(256), 0, st, mp, lw[l - 1], lh[l - 1], lw[l], lh[l]);
+    // eight rows per wave read 19 source rows; two (7 rows) where the level would
+    // leave the chip idle
+    const bool tall = (size_t)lw[l] * lh[l] * maps >= (1u << 20);
+    const int rows = tall ? 8 : 2;
+    const dim3 g((lw[l] + kRedCols - 1) / kRedCols, (lh[l] + 4 * rows - 1) / (4 * rows), maps);
+    if (tall)
+      LNR_LAUNCH(k_reduce<8>, g, dim3(256), 0, st, mp, lw[l - 1], lh[l - 1], lw[l], lh[l]);
+    else
+      LNR_LAUNCH(k_reduce<2>, g, dim3(256), 0, st, mp, lw[l - 1], lh[l - 1], lw[l], lh[l]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // blend + collapse, top level first
@@ -714,31 +740,16 @@ hipError_t launch_merge(int n, int ch, int W, int H, const float* const* imgs,
     const size_t per_plane = (size_t)kCH * kCW * sizeof(float);
     int cg = ch;  // channels per launch, so that the coarse tiles fit in 64 KB of LDS
     while (cg > 1 && (size_t)(n + 1) * cg * per_plane > 64 * 1024) --cg;
-    if ((size_t)(n + 1) * per_plane > 64 * 1024) {  // stacks of more than 15 frames
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blend),
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)((n + 1) * per_plane));
-      if (e != hipSuccess) return e;
-    }
     if ((size_t)lw[l] * lh[l] <= kBlendPxMax) {
       LNR_LAUNCH(k_blend_px, dim3((lw[l] * lh[l] + 255) / 256, ch), dim3(256), 0, st, bp, n,
                  lw[l], lh[l], cw, chh, top);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       continue;
     }
-    for (int c0 = 0; c0 < ch; c0 += cg) {
+    for (int c0 = 0; c0 < ch; c0 += cg) {  // (a top level is below kBlendPxMax)
       const int g = min(cg, ch - c0);
-      const size_t lds = top ? 0 : (size_t)(n + 1) * g * per_plane;
-      // float4 path: width a multiple of 4 and every plane 16-byte aligned
-      bool vec = lw[l] % 4 == 0;
-      auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-      for (int k = 0; k < n && vec; ++k) {
-        vec = vec && al(bp.w[k]);
-        for (int c = c0; c < c0 + g; ++c) vec = vec && al(bp.g[k][c]);
-      }
-      for (int c = c0; c < c0 + g; ++c) vec = vec && al(bp.out[c]);
       LNR_LAUNCH(k_blend, dim3((lw[l] + kBW - 1) / kBW, (lh[l] + kBH - 1) / kBH), dim3(256),
-                 lds, st, bp, n, c0, g, lw[l], lh[l], cw, chh, top, vec ? 1 : 0);
+                 (size_t)(n + 1) * g * per_plane, st, bp, n, c0, g, lw[l], lh[l], cw, chh);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }

@@ -135,6 +135,29 @@ def test_forward_rounds(lnr, ctx, n, shift):
     assert torch.equal(got, want)
 
 
+# levels of staged tiles (more than 2^18 pixels) with ragged tiles and rows of 1,
+# 2 and 3 pixels past the last four, of odd heights, and of one strip; the
+# reduction's border strips and short row groups; stacks whose channels take
+# more than one launch
+@pytest.mark.parametrize("n,ch,w,h", [(2, 3, 513, 515), (2, 1, 4098, 67), (3, 3, 70, 4003),
+                                      (2, 3, 1027, 512), (9, 3, 520, 509)])
+def test_merge_at_tile_edges(lnr, ctx, n, ch, w, h):
+    rng = np.random.default_rng(n * 1000 + w)
+    step = np.ones((5, 5))
+    plane = lambda: np.clip(np.kron(rng.uniform(0, 1, (h // 5 + 1, w // 5 + 1)), step)[:h, :w]
+                            * 0.8 + rng.uniform(0, 0.2, (h, w)), 0, 1).astype(np.float32)
+    imgs = [np.stack([plane() for _ in range(ch)]) for _ in range(n)]
+    base = plane()
+    yeqs = [np.clip(base + rng.uniform(-0.05, 0.05, (h, w)), 0, 1).astype(np.float32)
+            for _ in range(n)]
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    got = lnr.stage_merge(ctx, [t(i) for i in imgs], [t(y) for y in yeqs], 0, lnr.Params())
+    want = oracle.merge([i.astype(np.float64) for i in imgs], [y.astype(np.float64) for y in yeqs],
+                        0, oracle.params())
+    # the bound of the FP32 stages
+    assert (np.abs(got.cpu().numpy() - want) <= 1e-4 * (np.abs(want) + 1.0)).all()
+
+
 # one word / two; the narrow and the wide hypothesis blocks; the last size of
 # one fit block and the first of several; more iterations than blocks take at
 # once, and counts that leave a group short; few matches with repeated draws
