@@ -17,8 +17,9 @@
 //             every weight and image plane of one level, in registers.
 //  k_blend:   from the top level down, R_l = sum_k W_k,l (G_k,l - E(G_k,l+1))
 //             + E(R_l+1), E the EXPAND rule, on 64x32 tiles whose coarse
-//             neighbourhoods are staged in LDS; level 0 goes to the output. Small levels use k_blend_px instead (one
-//             thread per pixel and channel, samples read directly).
+//             neighbourhoods are staged in LDS; level 0 goes to the output. Small
+//             levels use k_blend_px instead (one thread per pixel and channel,
+//             samples read directly).
 #include "lnr_device.h"
 #include "lnr_internal.h"
 
