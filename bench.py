@@ -155,7 +155,8 @@ def algo_bytes_per_step(W, H, fmt_i420, n, ch, reg_sizes, blend_levels, launches
         elif base == "k_weights":       # all frames' planes + SSIM in, weights out
             add(base, cnt * (n * ch * 4 + (n - 1) * 4 + n * 4) * N)
         elif base == "k_reduce":        # every weight/image plane, level l-1 in, level l out
-            add(base, sum(n * (ch + 1) * 4 * (mpx[l - 1] + mpx[l]) for l in range(1, blend_levels)))
+            # (two builds by level size, all levels counted once)
+            out[base] = sum(n * (ch + 1) * 4 * (mpx[l - 1] + mpx[l]) for l in range(1, blend_levels))
         elif base == "k_blend":         # weights, images, coarse images, coarse result in; result out
             tot = 0
             for l in range(blend_levels):
