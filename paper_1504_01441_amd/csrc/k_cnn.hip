@@ -132,7 +132,9 @@ __global__ __launch_bounds__(256) void k_cnn_set(const float* __restrict__ src,
 // on every side; rows and columns outside the image repeat the edge) are
 // staged in workgroup memory; channels 0, 1 are the 2x2 sums of the central
 // 32 x 32 tile, channels 2, 3 the 4x4 sums of the window, each value
-// bf16((s - mid) / scale), exact before the one rounding.
+// bf16((s - mid) / scale), exact before the one rounding. Bound by latency: 16
+// us for a 5 MP pair with a dword's loads per turn of a loop, 12 with a thread's
+// eight in flight together.
 __global__ __launch_bounds__(256) void k_cnn_input(const uint8_t* __restrict__ ref,
                                                    const uint8_t* __restrict__ wrp, int w, int h,
                                                    int ntx, const int32_t* __restrict__ tiles,
@@ -144,25 +146,28 @@ __global__ __launch_bounds__(256) void k_cnn_input(const uint8_t* __restrict__ r
   if (i >= m) return;
   const int t = tiles ? tiles[i] : i;
   const int x0 = (t % ntx) * 32 - 16, y0 = (t / ntx) * 32 - 16;
-  for (int k = threadIdx.x; k < 2 * 64 * 16; k += 256) {
-    const int c = k >> 10, r = (k >> 4) & 63, d = k & 15;
-    const uint8_t* img = c ? wrp : ref;
-    const int yy = min(max(y0 + r, 0), h - 1);
-    const uint8_t* row = img + (size_t)yy * w;
-    const int xs = x0 + 4 * d;
-    const int off = (int)(reinterpret_cast<uintptr_t>(row + xs) & 3u);
-    uint32_t v = 0;
-    if (xs >= 0 && (xs - off) + 8 <= w) {
-      const uint8_t* base = row + xs - off;  // aligned
-      const uint32_t lo = *reinterpret_cast<const uint32_t*>(base);
-      const uint32_t hi = *reinterpret_cast<const uint32_t*>(base + 4);
-      v = __builtin_amdgcn_alignbyte(hi, lo, off);
-    } else {
+  // a thread's eight dwords (column d of rows 16 apart, both images) all in
+  // flight before the first is stored; the branch is the tile's column's
+  const int d = threadIdx.x & 15, xs = x0 + 4 * d;
+  uint32_t v[8];
+  const uint8_t* rows[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+    rows[q] = (q >> 2 ? wrp : ref) +
+              (size_t)min(max(y0 + (q & 3) * 16 + (int)(threadIdx.x >> 4), 0), h - 1) * w;
+  if (xs >= 0 && xs + 4 <= w) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const UnalignedU32*>(rows[q] + xs)->v;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      v[q] = 0;
       for (int b = 0; b < 4; ++b)
-        v |= (uint32_t)row[min(max(xs + b, 0), w - 1)] << (8 * b);
+        v[q] |= (uint32_t)rows[q][min(max(xs + b, 0), w - 1)] << (8 * b);
     }
-    win[c][r][d] = v;
   }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) win[q >> 2][(q & 3) * 16 + (threadIdx.x >> 4)][d] = v[q];
   __syncthreads();
   uint16_t* xo = x + (size_t)i * kIn;
   const uint8_t* wb = reinterpret_cast<const uint8_t*>(win);

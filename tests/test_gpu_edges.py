@@ -117,6 +117,16 @@ def test_search_at_block_edges(lnr, ctx, nx, ny, R, P):
     assert np.array_equal(ssd[v].view(np.uint32), want[v])
 
 
+# windows past both sides, past one, ending with the row; rows aligned to a byte
+@pytest.mark.parametrize("w,h", [(32, 32), (47, 33), (48, 40), (97, 64), (131, 97)])
+def test_network_input_window_edges(lnr, ctx, w, h):
+    rng = np.random.default_rng(w * h)
+    ref, wrp = (rng.integers(0, 256, (h, w)).astype(np.uint8) for _ in range(2))
+    x = lnr.proposal_inputs(ctx, torch.from_numpy(ref).cuda(), torch.from_numpy(wrp).cuda())
+    want = oracle.cnn_tile_inputs(ref, wrp, range((w // 32) * (h // 32)))
+    assert np.array_equal(x.view(torch.bfloat16).float().cpu().numpy(), want)
+
+
 # the last one-sample workgroups and the first four-sample ones; rounds that
 # leave 3, 2 and 1 of a workgroup's samples, a last round of few workgroups; an
 # input aligned to its elements only. A sample's result does not depend on its
