@@ -814,9 +814,13 @@ __device__ void search_tile(const SearchJob& J, int tile, int gidx, const Search
       // a candidate or two per thread, each summing its own window energy
       for (int i = tid; i < sh.ncand * sh.ncand; i += nt) {
         const int jj = quot(i, sh.d_cand), dxi = rest(i, jj, sh.d_cand);
+        const uint32_t* rq = rowsq + jj * sh.ncand + dxi;
         uint32_t e = 0;
-#pragma unroll 7
-        for (int y = 0; y < PW; ++y) e += rowsq[(jj + y) * sh.ncand + dxi];
+        int y = 0;
+        for (; y + 7 <= PW; y += 7)  // seven reads in flight
+#pragma unroll
+          for (int q = 0; q < 7; ++q) e += rq[(y + q) * sh.ncand];
+        for (; y < PW; ++y) e += rq[y * sh.ncand];
         score(jj, dxi, tot[jj * ncp + dxi], e);
       }
     } else {
