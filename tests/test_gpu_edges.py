@@ -226,3 +226,24 @@ def test_flow_at_line_edges(lnr, ctx, w, h):
         err = np.abs(got.cpu().numpy().astype(np.float64) - want)
         assert (err <= 1e-4 * (np.abs(want) + 1.0))[mask].all()
     assert (np.abs(nt.cpu().numpy() - n) <= 1e-4 * (np.abs(n) + 1.0)).all()
+
+
+# a negative n_min defines the flow everywhere as P~ / N~: infinite where the
+# weight underflowed to 0 before the displacement did, undefined where both did
+def test_flow_where_the_weight_underflows(lnr, ctx):
+    w, h = 1600, 32
+    flags = np.zeros(w // 32, np.uint8)
+    flags[0] = 7
+    cxy = np.stack([np.arange(w // 32) * 32 + 16, np.full(w // 32, 16)], 1).astype(np.int32)
+    disp = np.tile(np.array([16, -16], np.int32), (w // 32, 1))
+    t = lambda a: torch.from_numpy(a).cuda()
+    flow, nt = (v.cpu().numpy() for v in lnr.stage_flow(
+        ctx, t(cxy), t(disp), t(flags), torch.zeros(h, w, dtype=torch.uint8, device="cuda"),
+        lnr.Params(sigma_s=8.0, n_min=-1.0)))
+    assert (np.abs(flow[0][nt > 1e-30] - 16) < 1e-3).all()
+    zero = nt == 0
+    inf = np.isposinf(flow[0])
+    # 16 N~ leaves the floats four powers of two after N~ does, at 0.82 per pixel
+    assert inf[zero].sum() >= h and not inf[~zero].any()
+    assert np.array_equal(inf, np.isneginf(flow[1]))
+    assert np.isnan(flow[:, zero & ~inf]).all()
