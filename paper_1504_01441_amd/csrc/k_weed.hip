@@ -216,9 +216,12 @@ __device__ inline unsigned long long wave_or_u64(unsigned long long v) {
 
 // dynamic LDS of k_hyp: the words, the union and the inlier bits of IPB
 // hypotheses (8 bytes a word each), then the prefix counts
-inline size_t hyp_lds(int words, int ipb) {
+constexpr size_t hyp_lds(int words, int ipb) {
   return (size_t)words * 8 * (2 + ipb) + ((size_t)words + 1) * 4;
 }
+// what a workgroup can take, less k_hyp's own shared variables
+constexpr size_t kHypLdsMax = 160 * 1024 - 1024;
+static_assert(hyp_lds(kMaxWords, 4) <= kHypLdsMax, "the wide form takes every level");
 
 // The kernels below take one level of one pair (JOBS false: the job is the
 // kernel argument) or a table of jobs, one per blockIdx.z (batches).
@@ -227,8 +230,11 @@ inline size_t hyp_lds(int words, int ipb) {
 // 256 tiles take four per 512 threads (every CU a block at the default 1024
 // iterations, half the tests per wave); the smallest levels, and batches,
 // whose jobs fill the chip anyway, eight (a full wave of eight-lane solves)
-// per 256.
-inline bool hyp_wide(int ntiles, int njobs) { return ntiles > 256 && njobs < 4; }
+// per 256, unless the inlier words of eight do not fit a workgroup's memory
+// (more than 1938 words: 124,032 tiles).
+inline bool hyp_wide(int ntiles, int words, int njobs) {
+  return (ntiles > 256 && njobs < 4) || hyp_lds(words, 8) > kHypLdsMax;
+}
 
 // A coarse level (15 to 1200 tiles) is bound by the first wave's instruction
 // count, one every four or five cycles: eight-lane solves, draws in parallel,
@@ -774,7 +780,7 @@ hipError_t launch_weed(const WeedJob& one, const WeedJob* jobs, int njobs, int n
                        const WeedArgs& a, hipStream_t st) {
   const int words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
   if (words > kMaxWords || a.iters > kMaxIters) return hipErrorInvalidValue;
-  const bool wide = hyp_wide(ntiles, njobs);
+  const bool wide = hyp_wide(ntiles, words, njobs);
   hipError_t e = wide ? launch_hyp<JOBS, 4, 512>(one, jobs, njobs, words, a, st)
                       : launch_hyp<JOBS, 8, 256>(one, jobs, njobs, words, a, st);
   if (e != hipSuccess) return e;

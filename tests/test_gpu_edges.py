@@ -247,3 +247,63 @@ def test_flow_where_the_weight_underflows(lnr, ctx):
     assert inf[zero].sum() >= h and not inf[~zero].any()
     assert np.array_equal(inf, np.isneginf(flow[1]))
     assert np.isnan(flow[:, zero & ~inf]).all()
+
+
+def _weeding_case(nx, ny, tile, keep, seed):
+    """Matches of one level: a smooth motion with rounding, a third of them
+    random, `keep` of the tiles valid: (w, h, cx, cy, dx, dy, valid)."""
+    rng = np.random.default_rng(seed)
+    w, h = nx * tile, ny * tile
+    gy, gx = np.mgrid[0:ny, 0:nx]
+    cx = (gx * tile + tile // 2 + rng.integers(-2, 3, gx.shape)).ravel().astype(np.int32)
+    cy = (gy * tile + tile // 2 + rng.integers(-2, 3, gx.shape)).ravel().astype(np.int32)
+    dx = (np.rint(0.002 * (cx - w / 2) - 3) + rng.integers(-1, 2, cx.shape)).astype(np.int32)
+    dy = (np.rint(0.003 * (cy - h / 2) + 2) + rng.integers(-1, 2, cx.shape)).astype(np.int32)
+    far = rng.random(cx.shape) < 0.3
+    dx[far], dy[far] = rng.integers(-16, 17, far.sum()), rng.integers(-16, 17, far.sum())
+    return w, h, cx, cy, dx, dy, (rng.random(cx.shape) < keep).astype(np.uint8)
+
+
+def _weeding_parity(lnr, ctx, case, iters):
+    w, h, cx, cy, dx, dy, valid = case
+    p, op = lnr.Params(weed_iters=iters), oracle.params(weed_iters=iters)
+    M, n, bc, bi = oracle.weed(cx, cy, dx, dy, valid, w, h, 1, op)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    flags, H, counts = lnr.stage_weed_fit(
+        ctx, t(np.stack([cx, cy], 1)), t(np.stack([dx, dy], 1)),
+        t((valid * 3).astype(np.uint8)), w, h, 1, torch.eye(3, dtype=torch.float64).reshape(9), p)
+    f, c = flags.cpu().numpy(), counts.cpu().numpy()
+    assert np.array_equal((f & 4) > 0, M > 0)
+    assert c[0] == valid.sum() and c[2] == bc and c[3] == bi
+    sel = (f & 8) > 0
+    assert c[1] == sel.sum() == (bc if bc > oracle.weed_delta(int(valid.sum()), op) else 0)
+    want, _ = oracle.fit_level(cx, cy, dx, dy, sel.astype(np.uint8), w, h, np.eye(3))
+    assert np.array_equal(H.cpu().numpy().reshape(3, 3), want)
+
+
+# the largest level: 2304 tile words
+@pytest.mark.parametrize("iters", [37, 1100])
+def test_weeding_of_the_largest_level(lnr, ctx, iters):
+    _weeding_parity(lnr, ctx, _weeding_case(384, 384, 16, 0.8, iters), iters)
+
+
+# batches of pairs whose level 0 has the most tile words that eight hypotheses
+# per block can hold (1938, from four pairs on) and more: the single calls'
+# results, which take four per block
+@pytest.mark.parametrize("n,H", [(2, 5184), (4, 5168), (4, 5184)])
+def test_batch_with_a_level_of_many_tiles(lnr, ctx, n, H):
+    rng = np.random.default_rng(n)
+    p = lnr.Params(tile=16, patch_r=3, quad_r=3, corner_step=1, radius0=2, radius_coarse=2,
+                   weed_iters=50, dt_iters=1)
+    frames = []
+    for w, h in [(6144, H)] + [(320, 200)] * (n - 1):
+        y = rng.integers(0, 256, (h, w), dtype=np.uint8)
+        frames.append((lnr.Frame.from_numpy(y), lnr.Frame.from_numpy(np.roll(y, (1, -1), (0, 1)))))
+    refs, srcs = [f[0] for f in frames], [f[1] for f in frames]
+    outs = lnr.register_batch(ctx, refs, srcs, p)
+    for r, s, got in zip(refs, srcs, outs):
+        want = lnr.register_pair(ctx, r, s, p)
+        torch.cuda.synchronize()
+        for k in ("corner_xy", "disp", "ssd", "flags", "counts", "H", "flow", "image"):
+            a, b = getattr(got, k), getattr(want, k)
+            assert torch.equal(a, b), k
