@@ -275,11 +275,13 @@ int pinned_search_shape(const lnr_ctx* ctx, int w, int h, int R) {
   return it == ctx->search_split.end() ? 0 : it->second;
 }
 
+size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
+
 struct Plan {
   size_t off = 0;
   size_t take(size_t bytes) {
     const size_t o = off;
-    off += (bytes + 255) & ~(size_t)255;
+    off += round256(bytes);
     return o;
   }
 };
@@ -343,16 +345,28 @@ struct WeedPlan {
   size_t nmatch, key, G, part, psum, vb;
 };
 
-WeedPlan plan_weed(Plan& pl, int ntiles, int iters) {
+size_t weed_words(int ntiles) { return ntiles > 0 ? (size_t)(ntiles + 63) / 64 : 1; }
+
+// The keys and partial sums, which live from one weeding kernel to the next
+// only: a registration puts them where its propagation maps will be, so that
+// its workspace does not grow by them.
+size_t weed_passing_bytes(int ntiles, int iters) {
+  const size_t fit_blocks = (weed_words(ntiles) + kFitWords - 1) / kFitWords;
+  return round256(sizeof(unsigned long long) * (size_t)weed_blocks(iters, 4)) +
+         sizeof(long long) * 24 * fit_blocks;
+}
+
+// passing: the offset of weed_passing_bytes
+WeedPlan plan_weed(Plan& pl, int ntiles, int iters, size_t passing) {
   WeedPlan w;
-  const size_t words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
+  const size_t words = weed_words(ntiles);
   const size_t blocks = (size_t)weed_blocks(iters, 4);
   w.nmatch = pl.take(sizeof(int32_t));
-  w.key = pl.take(sizeof(unsigned long long) * blocks);
   w.G = pl.take(sizeof(double) * 8 * blocks);
   w.part = pl.take(sizeof(unsigned long long) * words * blocks);
-  w.psum = pl.take(sizeof(long long) * 24 * ((words + kFitWords - 1) / kFitWords));
   w.vb = pl.take(sizeof(unsigned long long) * words);
+  w.key = passing;
+  w.psum = passing + round256(sizeof(unsigned long long) * blocks);
   return w;
 }
 
@@ -403,8 +417,9 @@ PairPlan plan_pair(int W, int H, const lnr_params* p) {
   q.o_pref = pl.take(q.g.pyr_bytes);
   q.o_psrc = pl.take(q.g.pyr_bytes);
   q.o_warp = pl.take(N);
-  q.wp = plan_weed(pl, q.g.lv[0].ntx * q.g.lv[0].nty, p->weed_iters);
-  q.o_maps = pl.take(dt_maps_bytes(W, H));
+  const int nt = q.g.lv[0].ntx * q.g.lv[0].nty;
+  q.o_maps = pl.take(std::max(dt_maps_bytes(W, H), weed_passing_bytes(nt, p->weed_iters)));
+  q.wp = plan_weed(pl, nt, p->weed_iters, q.o_maps);
   q.o_gt = pl.take(dt_guide_t_bytes(W, H));
   q.o_coef = pl.take((size_t)p->dt_iters * 256 * sizeof(double));
   const size_t nt0 = (size_t)q.g.lv[0].ntx * q.g.lv[0].nty;
@@ -791,7 +806,6 @@ lnr_status lnr_register_pair_noalloc(lnr_ctx* ctx, const lnr_frame* ref, const l
 
 namespace {
 lnr_status ensure_workers(lnr_ctx* ctx, int K);
-size_t round256(size_t b);
 }  // namespace
 
 extern "C" {
@@ -1064,7 +1078,8 @@ lnr_status lnr_stage_weed_fit(lnr_ctx* ctx, const int32_t* corner_xy, const int3
     return fail(ctx, LNR_E_ARG, "bad weed/fit arguments");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, LNR_E_HIP, "hipSetDevice");
   Plan pl;
-  const WeedPlan wp = plan_weed(pl, ntiles, p->weed_iters);
+  const size_t passing = pl.take(weed_passing_bytes(ntiles, p->weed_iters));
+  const WeedPlan wp = plan_weed(pl, ntiles, p->weed_iters, passing);
   if ((s = ensure_ws(ctx, pl.off, (hipStream_t)stream)) != LNR_OK) return s;
   const WeedBufs wb = weed_bufs(static_cast<char*>(ctx->ws), wp);
   LNR_HIP(launch_weed_fit(corner_xy, disp, flags, ntiles, w, h, level, *p, H_prev, H_out, counts,
@@ -1183,8 +1198,6 @@ lnr_status ensure_workers(lnr_ctx* ctx, int K) {
   if (!ctx->capture) LNR_HIP(hipStreamCreateWithFlags(&ctx->capture, hipStreamNonBlocking));
   return LNR_OK;
 }
-
-size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Longest-processing-time assignment of pairs (by pixel count) to K streams.
 std::vector<std::vector<int>> assign_pairs(const lnr_frame* refs, int n, int K) {

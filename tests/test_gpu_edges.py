@@ -307,3 +307,20 @@ def test_batch_with_a_level_of_many_tiles(lnr, ctx, n, H):
         for k in ("corner_xy", "disp", "ssd", "flags", "counts", "H", "flow", "image"):
             a, b = getattr(got, k), getattr(want, k)
             assert torch.equal(a, b), k
+
+
+# the fixed scratch filled to its last byte: one weeding iteration, whose
+# buffers are the smallest part of a plan, in a frame that leaves no room
+def test_noalloc_at_the_scratch_limit(lnr, ctx):
+    w, h = 1021, 5912
+    p = lnr.Params(tile=16, patch_r=3, quad_r=3, corner_step=1, radius0=2, radius_coarse=2,
+                   weed_iters=1, dt_iters=3)
+    rng = np.random.default_rng(w)
+    y = np.kron(rng.integers(0, 256, (h // 4, w // 4 + 1)), np.ones((4, 4)))[:, :w].astype(np.uint8)
+    ref, src = lnr.Frame.from_numpy(y), lnr.Frame.from_numpy(np.roll(y, (1, -1), (0, 1)))
+    got = lnr.Registration.alloc(w, h, lnr.LNR_Y8, p)
+    lnr.register_pair_noalloc(ctx, ref, src, p, out=got)
+    want = lnr.register_pair(ctx, ref, src, p)
+    torch.cuda.synchronize()
+    for k in ("corner_xy", "disp", "ssd", "flags", "H", "flow", "image"):
+        assert torch.equal(getattr(got, k), getattr(want, k)), k
