@@ -288,15 +288,18 @@ lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_fra
                               int32_t n, const lnr_params* p, lnr_registration* outs,
                               int32_t flags, void* stream);
 /* Time every domain-transform kernel shape that covers w x h (Sec. 2.4 pass;
- * results do not depend on the shape) and use the fastest for that size from
- * then on. shape_out[5] (optional): rows per thread, row block, rows per
- * column segment, columns per block, segments per column. Synchronises. */
+ * results do not depend on the shape), those of lnr_flow_shapes and the ones
+ * with the column shape used by default at this height, and use the fastest
+ * for that size from then on. shape_out[5] (optional): rows per thread, row
+ * block, rows per column segment, columns per block, segments per column.
+ * Synchronises. */
 lnr_status lnr_autotune_flow(lnr_ctx* ctx, int32_t w, int32_t h, const lnr_params* p,
                              int32_t* shape_out, void* stream);
 /* Use one propagation kernel shape (five values, in the order of
  * lnr_autotune_flow's shape_out) for w x h from now on, in place of the
  * default or tuned one: for reproducible configurations. LNR_E_UNSUPPORTED
- * unless it is one of the shapes lnr_flow_shapes lists for w x h. */
+ * unless it is one of the shapes lnr_flow_shapes lists for w x h or one that
+ * lnr_autotune_flow can report for it. */
 lnr_status lnr_set_flow_shape(lnr_ctx* ctx, int32_t w, int32_t h, const int32_t* shape);
 /* The propagation shapes that cover w x h (host only): writes up to max of
  * them to shapes[5 * i ...] (may be null) and returns how many there are. */

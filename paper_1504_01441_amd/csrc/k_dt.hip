@@ -24,7 +24,7 @@
 //          row that holds no sample stays exactly zero through it, so that
 //          pass writes only a row flag for it, and the first column pass
 //          reads the records of flagged rows only (the rest are zeros).
-//  k_dt_col: one workgroup per strip of 4 or 8 columns over the full height, as
+//  k_dt_col: one workgroup per strip of 2 to 8 columns over the full height, as
 //          128 or 256 segments per column held in registers; the records are read
 //          and written once per pass. The last pass writes F (and N~) instead.
 #include <algorithm>
@@ -639,45 +639,58 @@ hipError_t row_pass(const DtShape& s, bool first, Rec* maps, const uint8_t* guid
 hipError_t col_pass(const DtShape& s, bool last, Rec* maps, const uint8_t* gt, int W, int H,
                     const double* cf, float* flow, float* ntilde, double nmin,
                     const uint8_t* rowflag, hipStream_t st) {
-  // The shape's rows per segment are the most it may take; the fewest that
-  // cover the height leave no segment idle (5 MP's 1944 rows fill 122 of 128
-  // segments of 16, but 1440 would fill 90: of 12, all 120).
-  const int need = (H + s.nseg - 1) / s.nseg, l = min(s.l, (need + 3) / 4 * 4);
-  // (the shapes of two columns by 256 segments run as blocks of four: runs of
-  // 48 bytes instead of 24 per row, 3000 x 4000: 85 -> 72 us, last 139 -> 103)
-#define COL(L, NC, NS, BLOCK)                                                                \
-  if (l == L && s.ncol == NC && s.nseg == NS)                                                 \
-    return launch_col<L, BLOCK, NS>(last, maps, gt, W, H, cf, flow, ntilde, nmin, rowflag, st);
-  COL(4, 8, 128, 8) COL(8, 8, 128, 8)
-  COL(4, 4, 128, 4) COL(8, 4, 128, 4) COL(12, 4, 128, 4) COL(16, 4, 128, 4) COL(20, 4, 128, 4)
-  COL(24, 4, 128, 4)
-  COL(4, 2, 256, 4) COL(8, 2, 256, 4) COL(12, 2, 256, 4) COL(16, 2, 256, 4) COL(20, 2, 256, 4)
-  COL(24, 2, 256, 4)
+#define COL(L, NC, NS)                                                                       \
+  if (s.l == L && s.ncol == NC && s.nseg == NS)                                               \
+    return launch_col<L, NC, NS>(last, maps, gt, W, H, cf, flow, ntilde, nmin, rowflag, st);
+  // the listed shapes
+  COL(8, 8, 128) COL(8, 4, 128) COL(16, 4, 128) COL(8, 2, 256) COL(24, 4, 128)
+  COL(16, 2, 256) COL(24, 2, 256)
+  // the other defaults
+  COL(4, 8, 128) COL(12, 4, 128) COL(20, 4, 128) COL(16, 4, 256) COL(20, 4, 256)
+  COL(24, 4, 256)
 #undef COL
   return hipErrorInvalidValue;
 }
+
+bool same_col(const DtShape& a, const DtShape& b) {
+  return a.l == b.l && a.ncol == b.ncol && a.nseg == b.nseg;
+}
 }  // namespace
 
+// A listed row shape with a listed column shape or with the height's default.
 bool dt_shape_valid(const DtShape& s, int W, int H) {
-  bool row = false, col = false;
+  bool row = false, col = same_col(s, dt_default_shape(W, H));
   for (const DtShape& r : kRowShapes) row |= r.seg == s.seg && r.nt == s.nt;
-  for (const DtShape& c : kColShapes) col |= c.l == s.l && c.ncol == s.ncol && c.nseg == s.nseg;
+  for (const DtShape& c : kColShapes) col |= same_col(c, s);
   return row && col && W <= s.seg * s.nt && H <= s.l * s.nseg;
 }
 
-// Every instantiated (row, column) pair that covers W x H.
-int dt_shape_candidates(int W, int H, DtShape* out, int max) {
+// Every listed (row, column) pair that covers W x H, then (tuner) the row
+// shapes with the height's default column shape where that is not listed.
+int dt_shape_candidates(int W, int H, DtShape* out, int max, bool tuner) {
   int n = 0;
+  auto add = [&](const DtShape& r, const DtShape& c) {
+    const DtShape s{r.seg, r.nt, c.l, c.ncol, c.nseg};
+    if (dt_shape_valid(s, W, H) && n < max) out[n++] = s;
+  };
   for (const DtShape& r : kRowShapes)
-    for (const DtShape& c : kColShapes) {
-      const DtShape s{r.seg, r.nt, c.l, c.ncol, c.nseg};
-      if (dt_shape_valid(s, W, H) && n < max) out[n++] = s;
-    }
+    for (const DtShape& c : kColShapes) add(r, c);
+  if (!tuner) return n;
+  const DtShape def = dt_default_shape(W, H);
+  for (const DtShape& c : kColShapes)
+    if (same_col(c, def)) return n;
+  for (const DtShape& r : kRowShapes) add(r, def);
   return n;
 }
 
-// The default table: the fewest rows / segments per thread that cover the
-// image (double-precision segments stay within 256 VGPRs).
+// The default: the fewest pixels per thread that cover a row, and segments of
+// the fewest rows (whole guide words) that cover the height, which leaves no
+// segment idle (1440 rows would fill 90 of 128 segments of 16: of 12, all
+// 120). Heights of more than 128 segments of 24 rows take 256 of them in
+// blocks of four columns, not two: runs of 48 bytes per row instead of 24
+// (3000 x 4000: 85 -> 72 us, last 139 -> 103). The column kernels' launch
+// bound holds them to 128 registers, which segments of 24 rows exceed by 24 to
+// 28 bytes of scratch per lane.
 DtShape dt_default_shape(int W, int H) {
   DtShape s;
   if (W <= 1024) { s.seg = 4; s.nt = 256; }
@@ -685,11 +698,9 @@ DtShape dt_default_shape(int W, int H) {
   else if (W <= 3072) { s.seg = 12; s.nt = 256; }
   else if (W <= 4096) { s.seg = 8; s.nt = 512; }
   else { s.seg = 12; s.nt = 512; }
-  if (H <= 1024) { s.l = 8; s.ncol = 8; s.nseg = 128; }
-  else if (H <= 2048) { s.l = 16; s.ncol = 4; s.nseg = 128; }
-  else if (H <= 3072) { s.l = 24; s.ncol = 4; s.nseg = 128; }
-  else if (H <= 4096) { s.l = 16; s.ncol = 2; s.nseg = 256; }
-  else { s.l = 24; s.ncol = 2; s.nseg = 256; }
+  s.nseg = H <= 3072 ? 128 : 256;
+  s.ncol = H <= 1024 ? 8 : 4;
+  s.l = ((H + s.nseg - 1) / s.nseg + 3) / 4 * 4;
   return s;
 }
 

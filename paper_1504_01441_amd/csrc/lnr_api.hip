@@ -1614,14 +1614,14 @@ lnr_status lnr_set_flow_shape(lnr_ctx* ctx, int32_t w, int32_t h, const int32_t*
   DtShape s;
   s.seg = shape[0]; s.nt = shape[1]; s.l = shape[2]; s.ncol = shape[3]; s.nseg = shape[4];
   if (!dt_shape_valid(s, w, h))
-    return fail(ctx, LNR_E_UNSUPPORTED, "not an instantiated propagation shape covering w x h");
+    return fail(ctx, LNR_E_UNSUPPORTED, "not a propagation shape of lnr_flow_shapes or the tuner for w x h");
   ctx->dt_shapes[std::make_pair((int)w, (int)h)] = s;
   return LNR_OK;
 }
 
 int32_t lnr_flow_shapes(int32_t w, int32_t h, int32_t* shapes, int32_t max) {
   DtShape c[64];
-  const int n = dt_shape_candidates(w, h, c, 64);
+  const int n = dt_shape_candidates(w, h, c, 64, false);
   for (int i = 0; i < n && i < max && shapes; ++i) {
     shapes[5 * i] = c[i].seg; shapes[5 * i + 1] = c[i].nt; shapes[5 * i + 2] = c[i].l;
     shapes[5 * i + 3] = c[i].ncol; shapes[5 * i + 4] = c[i].nseg;
@@ -1653,7 +1653,7 @@ lnr_status lnr_autotune_flow(lnr_ctx* ctx, int32_t w, int32_t h, const lnr_param
   // matches time them exactly
   LNR_HIP(hipMemsetAsync(b, 0, pl.off, st));
   DtShape cand[64];
-  const int nc = dt_shape_candidates(w, h, cand, 64);
+  const int nc = dt_shape_candidates(w, h, cand, 64, true);
   hipEvent_t t0 = nullptr, t1 = nullptr;
   LNR_HIP(hipEventCreate(&t0));
   LNR_HIP(hipEventCreate(&t1));

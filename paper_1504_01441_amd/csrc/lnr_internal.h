@@ -241,15 +241,15 @@ hipError_t launch_weed_fit(const int32_t* corner_xy, const int32_t* disp, uint8_
 
 // ---- domain-transform propagation (k_dt.hip)
 // Kernel shapes: rows of SEG pixels per thread in NT-thread blocks; columns as
-// NCOL columns x NSEG segments of L rows per block. Only the instantiated
-// combinations are valid (dt_shape_valid).
+// NCOL columns x NSEG segments of L rows per block. Only the listed
+// combinations and the default of the size are valid (dt_shape_valid).
 struct DtShape {
   int seg, nt;         // row kernel
   int l, ncol, nseg;   // column kernel
 };
 DtShape dt_default_shape(int W, int H);
 bool dt_shape_valid(const DtShape& s, int W, int H);
-int dt_shape_candidates(int W, int H, DtShape* out, int max);
+int dt_shape_candidates(int W, int H, DtShape* out, int max, bool tuner);
 // The propagation's working maps: one 12-byte record per pixel (the three
 // maps), so that a column pass reads whole runs of neighbouring columns.
 // The propagation maps (12 bytes per pixel) and, 256-byte aligned after

@@ -324,3 +324,63 @@ def test_noalloc_at_the_scratch_limit(lnr, ctx):
     torch.cuda.synchronize()
     for k in ("corner_xy", "disp", "ssd", "flags", "H", "flow", "image"):
         assert torch.equal(getattr(got, k), getattr(want, k)), k
+
+
+def _flow_case(w, h, seed):
+    """Corners of every tile, displacements, the kept ones, and a guide."""
+    rng = np.random.default_rng(seed)
+    guide = np.clip(np.cumsum(rng.integers(-9, 10, (h, w)), 1) + 128, 0, 255).astype(np.uint8)
+    gy, gx = np.mgrid[0:h // 32, 0:w // 32]
+    cx = (gx * 32 + 16 + rng.integers(-16, 16, gx.shape)).ravel().astype(np.int32)
+    cy = (gy * 32 + 16 + rng.integers(-16, 16, gx.shape)).ravel().astype(np.int32)
+    dx, dy = (rng.integers(-16, 17, cx.shape).astype(np.int32) for _ in range(2))
+    return cx, cy, dx, dy, (rng.random(cx.shape) < 0.7).astype(np.uint8), guide
+
+
+# the default column shapes from the first to the last height that takes them:
+# segments of 12, 20 and 24 rows (test_flow_at_line_edges has the others)
+@pytest.mark.parametrize("w,h", [(40, 1025), (37, 1536), (33, 2049), (34, 2560), (35, 2561),
+                                 (33, 4097), (36, 5121), (33, 6144)])
+def test_flow_default_column_shapes(lnr, ctx, w, h):
+    p, op = lnr.Params(), oracle.params()
+    cx, cy, dx, dy, keep, guide = _flow_case(w, h, w + h)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    flow, nt = lnr.stage_flow(ctx, t(np.stack([cx, cy], 1)), t(np.stack([dx, dy], 1)),
+                              t(keep * 7), t(guide), p)
+    u, v, n = oracle.sparse_to_dense(cx, cy, dx, dy, keep, guide, op)
+    mask = n > 2e-30
+    for got, want in ((flow[0], u), (flow[1], v)):  # the FP32 stages' bound, 1e-4 relative
+        err = np.abs(got.cpu().numpy().astype(np.float64) - want)
+        assert (err <= 1e-4 * (np.abs(want) + 1.0))[mask].all()
+    assert (np.abs(nt.cpu().numpy() - n) <= 1e-4 * (np.abs(n) + 1.0)).all()
+
+
+# a pinned shape's rows per segment are the rows that run, whatever the height
+# needs: where a segment ends shows in the last bits of the flow, so that other
+# rows give other bits (within the bound), and the same pin gives the same
+def test_pinned_flow_shapes_are_the_ones_that_run(lnr):
+    c = lnr.Context(0)
+    w, h = 640, 480
+    rng = np.random.default_rng(3)
+    y = np.kron(rng.integers(0, 256, (h // 8, w // 8)), np.ones((8, 8)))
+    y = np.clip(y + rng.integers(-3, 4, (h, w)), 0, 255).astype(np.uint8)
+    ref, src = lnr.Frame.from_numpy(y), lnr.Frame.from_numpy(np.roll(y, (2, -3), (0, 1)))
+    p = lnr.Params(radius0=8)
+
+    def run(shape):
+        lnr.set_flow_shape(c, w, h, shape)
+        return lnr.register_pair(c, ref, src, p).ntilde.cpu().numpy()
+
+    got = {rows: run((4, 256, rows, 4, 128)) for rows in (8, 16, 24)}
+    for a, b in ((8, 16), (8, 24), (16, 24)):
+        assert not np.array_equal(got[a], got[b])
+        assert (np.abs(got[a] - got[b]) <= 1e-4 * (np.abs(got[a]) + 1.0)).all()
+    assert np.array_equal(got[16], run((4, 256, 16, 4, 128)))
+    # what the tuner reports can be pinned, also where the default is not listed
+    for size in ((w, h), (700, 1080)):
+        shape = lnr.autotune_flow(c, *size, p)
+        assert shape[0] * shape[1] >= size[0] and shape[2] * shape[4] >= size[1]
+        lnr.set_flow_shape(c, *size, shape)
+    with pytest.raises(lnr.LnrError):
+        lnr.set_flow_shape(c, w, h, (4, 256, 12, 4, 128))  # the default of another height
+    c.close()
