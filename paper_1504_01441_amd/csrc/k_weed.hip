@@ -24,6 +24,8 @@
 //         and composes H_l = H_{l+1} o G. One block up to kFitWords words;
 //         larger levels spread the tiles over blocks and k_solve finishes.
 // The kernels are ordered by the stream; no block waits for another.
+#include <algorithm>
+
 #include "lnr_device.h"
 #include "lnr_internal.h"
 
@@ -214,26 +216,43 @@ __device__ inline unsigned long long wave_or_u64(unsigned long long v) {
   return wave_fold_u64(v, [](unsigned long long p, unsigned long long q) { return p | q; });
 }
 
-// dynamic LDS of k_hyp: the words, the union and the inlier bits of IPB
-// hypotheses (8 bytes a word each), then the prefix counts
-constexpr size_t hyp_lds(int words, int ipb) {
-  return (size_t)words * 8 * (2 + ipb) + ((size_t)words + 1) * 4;
+// dynamic LDS of k_hyp: the words, the union and the inlier bits of ipb
+// hypotheses (8 bytes a word each), the prefix counts; where more than ipb are
+// solved together, their coefficients and usability
+constexpr size_t hyp_lds(int words, int ipb, int per) {
+  return (size_t)words * 8 * (2 + ipb) + ((size_t)words + 1) * 4 +
+         (per > ipb ? (size_t)per * (64 + 4) : 0);
 }
 // what a workgroup can take, less k_hyp's own shared variables
 constexpr size_t kHypLdsMax = 160 * 1024 - 1024;
-static_assert(hyp_lds(kMaxWords, 4) <= kHypLdsMax, "the wide form takes every level");
+static_assert(hyp_lds(kMaxWords, 4, 64) <= kHypLdsMax, "the wide form takes every level");
 
 // The kernels below take one level of one pair (JOBS false: the job is the
 // kernel argument) or a table of jobs, one per blockIdx.z (batches).
 //
-// Hypotheses per k_hyp block and its threads: a pair's levels of more than
-// 256 tiles take four per 512 threads (every CU a block at the default 1024
-// iterations, half the tests per wave); the smallest levels, and batches,
-// whose jobs fill the chip anyway, eight (a full wave of eight-lane solves)
-// per 256, unless the inlier words of eight do not fit a workgroup's memory
-// (more than 1938 words: 124,032 tiles).
-inline bool hyp_wide(int ntiles, int words, int njobs) {
-  return (ntiles > 256 && njobs < 4) || hyp_lds(words, 8) > kHypLdsMax;
+// How k_hyp splits a level's iterations: hypotheses that a block tests
+// together (ipb) and its threads, hypotheses that it solves together (per) and
+// blocks. A pair's levels of more than 256 tiles test four per 512 threads
+// (every CU a block at the default 1024 iterations, half the tests per wave);
+// the smallest levels, and batches, whose jobs fill the chip anyway, eight (a
+// full wave of eight-lane solves) per 256, unless the inlier words of eight do
+// not fit a workgroup's memory (more than 1938 words: 124,032 tiles). More
+// iterations than the blocks take so are solved by as many of a block's waves
+// as it needs, eight hypotheses each, before they are tested: with every solve
+// on the first wave 65,536 iterations took 274 us at 300 tiles and 735 at
+// 4860 (all of a level's weeding), so 130 and 586.
+struct HypForm {
+  bool wide;
+  int per, blocks;
+};
+inline HypForm hyp_form(int iters, int ntiles, int words, int njobs) {
+  const int share = (iters + kWeedBlocks - 1) / kWeedBlocks;
+  const int narrow = std::min(std::max((share + 7) / 8 * 8, 8), 32);
+  HypForm f;
+  f.wide = (ntiles > 256 && njobs < 4) || hyp_lds(words, 8, narrow) > kHypLdsMax;
+  f.per = f.wide ? std::min((share + 3) / 4 * 4, 64) : narrow;
+  f.blocks = weed_blocks(iters, f.per);
+  return f;
 }
 
 // A coarse level (15 to 1200 tiles) is bound by the first wave's instruction
@@ -241,9 +260,13 @@ inline bool hyp_wide(int ntiles, int words, int njobs) {
 // tests without branches. 8.0 us at 300 tiles and 9 at 15; one system per
 // lane and a launch of its own for the tests took 8.6 + 4.2 us. At 4860
 // tiles the tests are the work: 17 us against 9.2 + 12.8.
-template <bool JOBS, int IPB, int NT>
-__global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, const WeedJob* __restrict__ jobs,
-                                            WeedArgs a) {
+// MANY: `solved` hypotheses are solved together, else IPB (a kernel of its own:
+// the usual one takes 0.3 us less without the turns).
+template <bool JOBS, int IPB, int NT, bool MANY>
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
+                                                               const WeedJob* __restrict__ jobs,
+                                                               WeedArgs a, int solved) {
+  const int per = MANY ? solved : IPB;
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
   const unsigned long long* __restrict__ vbg = J.b.vb;
   const int32_t* __restrict__ cxy = J.cxy;
@@ -252,20 +275,24 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, cons
   const int ox = J.w / 2, oy = J.h / 2;
   constexpr int NW = NT / 64;
   extern __shared__ __align__(16) unsigned long long dyn[];
-  unsigned long long* vb = dyn;                    // valid-tile bits, tile order
+  __shared__ __align__(16) double few_gs[MANY ? 1 : IPB][8];
+  __shared__ int few_usable[MANY ? 1 : IPB];
+  double (*gs)[8] = MANY ? reinterpret_cast<double (*)[8]>(dyn) : few_gs;  // [per]
+  unsigned long long* vb = dyn + (MANY ? 8 * per : 0);  // valid-tile bits, tile order
   unsigned long long* uni = vb + nwords;           // union of the accepted inliers
   unsigned long long* inl = uni + nwords;          // [nwords][IPB] inlier bits
   int* wpre = reinterpret_cast<int*>(inl + (size_t)nwords * IPB);  // valid tiles before a word
-  __shared__ __align__(16) double gs[IPB][8];
-  __shared__ int usable[IPB];   // 0: no, 1: yes, 2: yes, tested with plain divisions
+  // [per] 0: not usable, 1: usable, 2: usable, tested with plain divisions
+  int* usable = MANY ? wpre + nwords + 1 : few_usable;
   __shared__ int wc[IPB][NW];
+  __shared__ int matches;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // this thread's first tile, in flight with the words
   int4 mine = make_int4(0, 0, 0, 0);
   if (ntiles > 0) mine = tile_match(cxy, disp, min(tid, ntiles - 1), ox, oy);
-  // The first wave prepares, solves and counts by itself; the others only
-  // test, between the two barriers of a group.
-  int N = 0, delta = 0;           // first wave
+  // The first wave prepares, solves (up to eight hypotheses) and counts by
+  // itself; the others only test, between the two barriers of a group.
+  int N = 0, delta = 0;           // (N: the solving waves; delta: the first)
   unsigned long long best = 0ull;  // this block's best key (first wave)
   double bg = 0.0;                 // its coefficient `lane` (lanes 0..7)
   const unsigned long long seed = a.seed ^ ((unsigned long long)(uint32_t)a.level << 56);
@@ -316,16 +343,20 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, cons
     N = __builtin_amdgcn_readlane(incl, 63);
     delta = weed_delta(N, a);
     if (blockIdx.x == 0 && lane == 0) *J.b.nmatch = N;
+    if (MANY && lane == 0) matches = N;
   }
-  const int groups = (a.iters + IPB - 1) / IPB;
-  for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const int it0 = grp * IPB;
-    if (wave == 0) {
+  if (MANY) {  // more waves solve: the words are theirs too
+    __syncthreads();
+    N = matches;
+  }
+  const int turn = (int)gridDim.x * per;
+  for (int r0 = blockIdx.x * per; r0 < a.iters; r0 += turn) {
+    if (MANY ? 8 * wave < per : wave == 0) {
       // eight lanes per hypothesis: each draws one index of the first eight
       // and sets up row (lane & 7) of the system, the x or y equation of
       // match row / 2
-      const int q = min(lane >> 3, IPB - 1), row = lane & 7;
-      const int it = it0 + q;
+      const int q = min(8 * wave + (lane >> 3), per - 1), row = lane & 7;
+      const int it = r0 + q;
       const unsigned long long base = seed + (unsigned long long)it * 16ull;
       auto draw = [&](int t) {
         return (int)__umulhi((uint32_t)(splitmix64(base + (unsigned long long)t) >> 32),
@@ -374,7 +405,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, cons
       double g[8];
       const bool solved = solve8_rows(A, g);
       good = good && solved;
-      if (row == 0 && (lane >> 3) < IPB) {
+      if (row == 0 && 8 * wave + (lane >> 3) < per) {
         // not usable: too few matches, degenerate draw or fit
         usable[q] = good ? (needs_plain(g) ? 2 : 1) : 0;
 #pragma unroll
@@ -382,58 +413,75 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one, cons
       }
     }
     __syncthreads();
-    // every tile against the group's hypotheses
-    bool plain = false;
+    for (int it0 = r0; it0 < min(r0 + per, a.iters); it0 += IPB) {
+      // every tile against the next IPB hypotheses
+      const double (*g)[8] = gs + (it0 - r0);
+      const int* use = usable + (it0 - r0);
+      bool plain = false;
 #pragma unroll
-    for (int q = 0; q < IPB; ++q) plain = plain || usable[q] == 2;
-    int cnt = 0;  // lane q: hypothesis q
-    for (int t0 = 0; t0 < nwords * 64; t0 += NT) {
-      const int t = t0 + tid, word = t >> 6;
-      if (word >= nwords) break;  // whole waves
-      const bool valid = (vb[word] >> lane) & 1ull;
-      const int4 m = t0 == 0 ? mine : tile_match(cxy, disp, min(t, ntiles - 1), ox, oy);
-      unsigned long long keep = 0ull;
+      for (int q = 0; q < IPB; ++q) plain = plain || use[q] == 2;
+      // four hypotheses stay in registers over the tiles (read again for every
+      // tile they keep the LDS unit busier than the tests the vector ALU)
+      double r[4][8];
+      if constexpr (IPB == 4)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) r[q][i] = g[q][i];
+      int cnt = 0;  // lane q: hypothesis q
+      for (int t0 = 0; t0 < nwords * 64; t0 += NT) {
+        const int t = t0 + tid, word = t >> 6;
+        if (word >= nwords) break;  // whole waves
+        const bool valid = (vb[word] >> lane) & 1ull;
+        const int4 m = t0 == 0 ? mine : tile_match(cxy, disp, min(t, ntiles - 1), ox, oy);
+        unsigned long long keep = 0ull;
 #pragma unroll 4
-      for (int q = 0; q < IPB; ++q) {
-        const unsigned long long b = __ballot(valid && is_inlier<false>(gs[q], m, a.eps2));
-        if (lane == q) keep = b;
-      }
-      if (plain)
         for (int q = 0; q < IPB; ++q) {
-          if (usable[q] != 2) continue;
-          const unsigned long long b = __ballot(valid && is_inlier<true>(gs[q], m, a.eps2));
+          const unsigned long long b =
+              __ballot(valid && is_inlier<false>(IPB == 4 ? r[q & 3] : g[q], m, a.eps2));
           if (lane == q) keep = b;
         }
-      cnt += __popcll(keep);
-      if (lane < IPB) inl[(size_t)word * IPB + lane] = keep;
-    }
-    if (lane < IPB) wc[lane][wave] = cnt;
-    __syncthreads();
-    if (wave == 0) {
-      // lane q counts hypothesis q
-      int c = 0;
-      unsigned long long key = 0ull;
-      if (lane < IPB && usable[lane]) {
+        if (plain)
+          for (int q = 0; q < IPB; ++q) {
+            if (use[q] != 2) continue;
+            const unsigned long long b = __ballot(valid && is_inlier<true>(g[q], m, a.eps2));
+            if (lane == q) keep = b;
+          }
+        cnt += __popcll(keep);
+        if (lane < IPB) inl[(size_t)word * IPB + lane] = keep;
+      }
+      if (lane < IPB) wc[lane][wave] = cnt;
+      __syncthreads();
+      if (wave == 0) {
+        // lane q counts hypothesis q
+        int c = 0;
+        unsigned long long key = 0ull;
+        if (lane < IPB && use[lane]) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) c += wc[lane][w];
-        key = ((unsigned long long)(uint32_t)c << 32) |
-              (unsigned long long)(~(uint32_t)(it0 + lane));
-      }
-      const unsigned int acc = (unsigned int)__ballot(c > delta);  // accepted
-      const unsigned long long top = wave_max_u64(key);
-      if (top > best) {
-        best = top;
-        const int q = (int)(~(uint32_t)top) - it0;
-        if (lane < 8) bg = gs[q][lane];
-      }
-      if (acc)
-        for (int w = lane; w < nwords; w += 64) {
-          unsigned long long v = uni[w];
-          for (unsigned int r = acc; r; r &= r - 1)
-            v |= inl[(size_t)w * IPB + __builtin_ctz(r)];
-          uni[w] = v;
+          for (int w = 0; w < NW; ++w) c += wc[lane][w];
+          key = ((unsigned long long)(uint32_t)c << 32) |
+                (unsigned long long)(~(uint32_t)(it0 + lane));
         }
+        const unsigned int acc = (unsigned int)__ballot(c > delta);  // accepted
+        const unsigned long long top = wave_max_u64(key);
+        if (top > best) {
+          best = top;
+          const int q = (int)(~(uint32_t)top) - it0;
+          if (lane < 8) bg = g[q][lane];
+        }
+        if (acc)
+          for (int w = lane; w < nwords; w += 64) {
+            unsigned long long v = uni[w];
+            for (unsigned int r = acc; r; r &= r - 1)
+              v |= inl[(size_t)w * IPB + __builtin_ctz(r)];
+            uni[w] = v;
+          }
+      }
+      // (the first wave is done with the counts, the bits and the hypotheses
+      // before they are written again)
+      if (MANY && (it0 + IPB < r0 + per || r0 + turn < a.iters)) __syncthreads();
     }
+    if (!MANY) break;  // (fewer groups than blocks otherwise)
   }
   if (wave != 0) return;
   if (lane < 8) J.b.G[(size_t)blockIdx.x * 8 + lane] = bg;
@@ -572,7 +620,7 @@ __device__ inline void solve_level(const WeedJob& J, const double* tot, int msel
 }
 
 // Block x owns tile words [x wpb, (x + 1) wpb): the union M over the blocks
-// of k_hyp (hypothesis groups of ipb iterations), flags 4 (in M) and 8 (in
+// of k_hyp (per iterations a turn), flags 4 (in M) and 8 (in
 // the fit) of its tiles and their least-squares terms; the level's only block
 // then solves, several leave their sums to k_solve. One block is enough for
 // kFitOne words (2048 tiles, four per thread); beyond, its one CU is the
@@ -582,7 +630,7 @@ __device__ inline void solve_level(const WeedJob& J, const double* tot, int msel
 template <bool JOBS>
 __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
                                                      const WeedJob* __restrict__ jobs,
-                                                     WeedArgs a, int ipb, int nhyp, int wpb) {
+                                                     WeedArgs a, int per, int nhyp, int wpb) {
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
   const int ntiles = J.ntiles, words = J.words;
   const int w0 = blockIdx.x * wpb, w1 = min(words, w0 + wpb);
@@ -642,7 +690,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
   bkey = wave_max_u64(bkey);
   const int bc = bkey ? (int)(bkey >> 32) : -1;
   const int bi = bkey ? (int)(~(uint32_t)(bkey & 0xffffffffull)) : -1;
-  const int bb = bkey ? bi / ipb % nhyp : 0;  // the block that solved iteration bi
+  const int bb = bkey ? bi / per % nhyp : 0;  // the block that solved iteration bi
   const bool fit = bc > delta;
   if (blockIdx.x == 0 && tid == 0) {
     J.counts[0] = N;
@@ -760,18 +808,18 @@ WeedArgs weed_args(const lnr_params& p, int level) {
 namespace {
 // k_hyp, k_fit and, for a level of more than one k_fit block, k_solve over
 // njobs jobs of at most ntiles tiles.
-template <bool JOBS, int IPB, int NT>
+template <bool JOBS, int IPB, int NT, bool MANY>
 hipError_t launch_hyp(const WeedJob& one, const WeedJob* jobs, int njobs, int words,
-                      const WeedArgs& a, hipStream_t st) {
-  const size_t lds = hyp_lds(words, IPB);
+                      const WeedArgs& a, const HypForm& f, hipStream_t st) {
+  const size_t lds = hyp_lds(words, IPB, f.per);
   if (lds > 64 * 1024) {
     const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hyp<JOBS, IPB, NT>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hyp<JOBS, IPB, NT, MANY>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  LNR_LAUNCH((k_hyp<JOBS, IPB, NT>), dim3(weed_blocks(a.iters, IPB), 1, njobs), dim3(NT), lds, st,
-             one, jobs, a);
+  LNR_LAUNCH((k_hyp<JOBS, IPB, NT, MANY>), dim3(f.blocks, 1, njobs), dim3(NT), lds, st, one, jobs,
+             a, f.per);
   return hipGetLastError();
 }
 
@@ -780,14 +828,18 @@ hipError_t launch_weed(const WeedJob& one, const WeedJob* jobs, int njobs, int n
                        const WeedArgs& a, hipStream_t st) {
   const int words = ntiles > 0 ? (ntiles + 63) / 64 : 1;
   if (words > kMaxWords || a.iters > kMaxIters) return hipErrorInvalidValue;
-  const bool wide = hyp_wide(ntiles, words, njobs);
-  hipError_t e = wide ? launch_hyp<JOBS, 4, 512>(one, jobs, njobs, words, a, st)
-                      : launch_hyp<JOBS, 8, 256>(one, jobs, njobs, words, a, st);
+  const HypForm f = hyp_form(a.iters, ntiles, words, njobs);
+  const bool many = f.per > (f.wide ? 4 : 8);
+  hipError_t e =
+      f.wide ? many ? launch_hyp<JOBS, 4, 512, true>(one, jobs, njobs, words, a, f, st)
+                    : launch_hyp<JOBS, 4, 512, false>(one, jobs, njobs, words, a, f, st)
+             : many ? launch_hyp<JOBS, 8, 256, true>(one, jobs, njobs, words, a, f, st)
+                    : launch_hyp<JOBS, 8, 256, false>(one, jobs, njobs, words, a, f, st);
   if (e != hipSuccess) return e;
   const int wpb = words <= kFitOne ? kFitOne : kFitWords;
   const int blocks = (words + wpb - 1) / wpb;
   LNR_LAUNCH(k_fit<JOBS>, dim3(blocks, 1, njobs), dim3(kFitThreads), 0, st, one, jobs, a,
-             wide ? 4 : 8, weed_blocks(a.iters, wide ? 4 : 8), wpb);
+             f.per, f.blocks, wpb);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (blocks > 1) {
     LNR_LAUNCH(k_solve<JOBS>, dim3(1, 1, njobs), dim3(64), 0, st, one, jobs, wpb);

@@ -384,3 +384,13 @@ def test_pinned_flow_shapes_are_the_ones_that_run(lnr):
     with pytest.raises(lnr.LnrError):
         lnr.set_flow_shape(c, w, h, (4, 256, 12, 4, 128))  # the default of another height
     c.close()
+
+
+# iterations beyond one group per block: the last and first counts that one
+# wave, two, a part of one and all waves of a block solve, and a second turn of
+# the blocks; narrow blocks (up to 256 tiles), then wide ones
+@pytest.mark.parametrize("nx,ny,iters", [
+    (12, 9, 2048), (12, 9, 2049), (12, 9, 8192), (12, 9, 8193), (5, 3, 20000),
+    (20, 15, 1025), (20, 15, 2049), (20, 15, 16384), (20, 15, 16389), (70, 61, 16389)])
+def test_weeding_of_many_iterations(lnr, ctx, nx, ny, iters):
+    _weeding_parity(lnr, ctx, _weeding_case(nx, ny, 32, 0.8, iters + nx), iters)
