@@ -543,16 +543,23 @@ __global__ __launch_bounds__(NCOL * NSEG, 4) void k_dt_col(Rec* __restrict__ map
       const bool ok = (double)a2[j] > nmin;
       double fu, fv;  // (float operands: far from the double range's ends)
       recip_quotients((double)a0[j], (double)a1[j], (double)a2[j], fu, fv);
-      // (a negative nmin lets N~ = 0 through, which the reciprocal does not
-      // take: x / 0 is x times its infinity)
-      const float inf = copysignf(INFINITY, a2[j]);
-      const float qu = a2[j] != 0.f ? (float)fu : a0[j] * inf;
-      const float qv = a2[j] != 0.f ? (float)fv : a1[j] * inf;
-      flow[o] = ok ? qu : 0.f;
-      flow[plane + o] = ok ? qv : 0.f;
+      flow[o] = ok ? (float)fu : 0.f;
+      flow[plane + o] = ok ? (float)fv : 0.f;
       if (ntilde) ntilde[o] = a2[j];
     } else {
       maps[o] = Rec{a0[j], a1[j], a2[j]};
+    }
+  }
+  if (LAST && nmin < 0.0) {  // N~ = 0 counts, which the reciprocal does not take
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const int y = rs + j;
+      if (y >= H) break;
+      const size_t o = (size_t)y * W + col;
+      if (a2[j] == 0.f) {
+        flow[o] = a0[j] / a2[j];
+        flow[plane + o] = a1[j] / a2[j];
+      }
     }
   }
 }
