@@ -14,7 +14,9 @@
 //         precision, a row per lane; wave ballots over the tiles give each
 //         hypothesis' count and inlier bits, so that the block knows by
 //         itself which of its hypotheses are accepted (count above delta),
-//         the union of their inliers and its best hypothesis.
+//         the union of their inliers and its best hypothesis. A few
+//         iterations over many tiles: a block per chunk of the tiles as well,
+//         which leaves every hypothesis' inlier bits and its chunk's count.
 // k_fit:  M, the union of the blocks' unions (any split of the iterations
 //         gives the same M, as the paper notes), and the best consensus of
 //         all blocks (most inliers, lowest iteration), whose inliers are
@@ -230,6 +232,7 @@ static_assert(hyp_lds(kMaxWords, 4, 64) <= kHypLdsMax, "the wide form takes ever
 // The kernels below take one level of one pair (JOBS false: the job is the
 // kernel argument) or a table of jobs, one per blockIdx.z (batches).
 //
+
 // How k_hyp splits a level's iterations: hypotheses that a block tests
 // together (ipb) and its threads, hypotheses that it solves together (per) and
 // blocks. A pair's levels of more than 256 tiles test four per 512 threads
@@ -240,15 +243,30 @@ static_assert(hyp_lds(kMaxWords, 4, 64) <= kHypLdsMax, "the wide form takes ever
 // iterations than the blocks take so are solved by as many of a block's waves
 // as it needs, eight hypotheses each, before they are tested: with every solve
 // on the first wave 65,536 iterations took 274 us at 300 tiles and 735 at
-// 4860 (all of a level's weeding), so 130 and 586.
+// 4860 (all of a level's weeding), so 130 and 586. Iterations that leave half of
+// the CUs without a block are tested by several blocks per group, each on a
+// chunk of the tiles, where the level is large enough for that to pay for the
+// chunks' counts: from 49 words on, above 256 hypotheses from 129 on (one
+// iteration over 46,500 tiles 98 us in one block, 28 in chunks; 256 over 3136
+// tiles 28.0 and 25.6; 512 over 4860 tiles 31 and 34, over 11,625 44 and 38).
 struct HypForm {
   bool wide;
-  int per, blocks;
+  int per, blocks, chunks;
 };
 inline HypForm hyp_form(int iters, int ntiles, int words, int njobs) {
+  HypForm f;
+  const int groups = (iters + 3) / 4;
+  f.chunks = 1;
+  if (iters <= kSplitIters && words > (iters <= kWeedBlocks ? 48 : 128) && groups * njobs <= 128)
+    f.chunks = std::min({256 / (groups * njobs), words / kSplitWords, kSplitChunks});
+  if (f.chunks > 1) {
+    f.wide = true;
+    f.per = 4;
+    f.blocks = groups;
+    return f;
+  }
   const int share = (iters + kWeedBlocks - 1) / kWeedBlocks;
   const int narrow = std::min(std::max((share + 7) / 8 * 8, 8), 32);
-  HypForm f;
   f.wide = (ntiles > 256 && njobs < 4) || hyp_lds(words, 8, narrow) > kHypLdsMax;
   f.per = f.wide ? std::min((share + 3) / 4 * 4, 64) : narrow;
   f.blocks = weed_blocks(iters, f.per);
@@ -260,12 +278,15 @@ inline HypForm hyp_form(int iters, int ntiles, int words, int njobs) {
 // tests without branches. 8.0 us at 300 tiles and 9 at 15; one system per
 // lane and a launch of its own for the tests took 8.6 + 4.2 us. At 4860
 // tiles the tests are the work: 17 us against 9.2 + 12.8.
-// MANY: `solved` hypotheses are solved together, else IPB (a kernel of its own:
-// the usual one takes 0.3 us less without the turns).
-template <bool JOBS, int IPB, int NT, bool MANY>
+// kManyHyp: `solved` hypotheses are solved together, else IPB (a kernel of its
+// own: the usual one takes 0.3 us less without the turns). kSplitHyp: the tiles
+// of chunk blockIdx.y only.
+enum HypMode { kUsualHyp, kManyHyp, kSplitHyp };
+template <bool JOBS, int IPB, int NT, HypMode MODE>
 __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
                                                                const WeedJob* __restrict__ jobs,
                                                                WeedArgs a, int solved) {
+  constexpr bool MANY = MODE == kManyHyp, SPLIT = MODE == kSplitHyp;
   const int per = MANY ? solved : IPB;
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
   const unsigned long long* __restrict__ vbg = J.b.vb;
@@ -281,15 +302,20 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
   unsigned long long* vb = dyn + (MANY ? 8 * per : 0);  // valid-tile bits, tile order
   unsigned long long* uni = vb + nwords;           // union of the accepted inliers
   unsigned long long* inl = uni + nwords;          // [nwords][IPB] inlier bits
-  int* wpre = reinterpret_cast<int*>(inl + (size_t)nwords * IPB);  // valid tiles before a word
+  // valid tiles before a word
+  int* wpre = reinterpret_cast<int*>(inl + (SPLIT ? 0 : (size_t)nwords * IPB));
   // [per] 0: not usable, 1: usable, 2: usable, tested with plain divisions
   int* usable = MANY ? wpre + nwords + 1 : few_usable;
   __shared__ int wc[IPB][NW];
   __shared__ int matches;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the tested words
+  const int wpc = SPLIT ? split_words(nwords, gridDim.y) : nwords;
+  const int w0 = SPLIT ? blockIdx.y * wpc : 0, w1 = SPLIT ? min(nwords, w0 + wpc) : nwords;
+  if (SPLIT && w0 >= nwords) return;  // (a level has at least one word)
   // this thread's first tile, in flight with the words
   int4 mine = make_int4(0, 0, 0, 0);
-  if (ntiles > 0) mine = tile_match(cxy, disp, min(tid, ntiles - 1), ox, oy);
+  if (ntiles > 0) mine = tile_match(cxy, disp, min(w0 * 64 + tid, ntiles - 1), ox, oy);
   // The first wave prepares, solves (up to eight hypotheses) and counts by
   // itself; the others only test, between the two barriers of a group.
   int N = 0, delta = 0;           // (N: the solving waves; delta: the first)
@@ -342,20 +368,23 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
     wave_lds_order();
     N = __builtin_amdgcn_readlane(incl, 63);
     delta = weed_delta(N, a);
-    if (blockIdx.x == 0 && lane == 0) *J.b.nmatch = N;
+    if (blockIdx.x == 0 && w0 == 0 && lane == 0) *J.b.nmatch = N;
     if (MANY && lane == 0) matches = N;
   }
   if (MANY) {  // more waves solve: the words are theirs too
     __syncthreads();
     N = matches;
   }
+  // (one turn but for kManyHyp; a straight line compiles to tests unrolled
+  // further, 0.5 us per launch of a batch's)
   const int turn = (int)gridDim.x * per;
   for (int r0 = blockIdx.x * per; r0 < a.iters; r0 += turn) {
     if (MANY ? 8 * wave < per : wave == 0) {
       // eight lanes per hypothesis: each draws one index of the first eight
       // and sets up row (lane & 7) of the system, the x or y equation of
       // match row / 2
-      const int q = min(8 * wave + (lane >> 3), per - 1), row = lane & 7;
+      const int q0 = MANY ? 8 * wave : 0;
+      const int q = min(q0 + (lane >> 3), per - 1), row = lane & 7;
       const int it = r0 + q;
       const unsigned long long base = seed + (unsigned long long)it * 16ull;
       auto draw = [&](int t) {
@@ -405,7 +434,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
       double g[8];
       const bool solved = solve8_rows(A, g);
       good = good && solved;
-      if (row == 0 && 8 * wave + (lane >> 3) < per) {
+      if (row == 0 && q0 + (lane >> 3) < per) {
         // not usable: too few matches, degenerate draw or fit
         usable[q] = good ? (needs_plain(g) ? 2 : 1) : 0;
 #pragma unroll
@@ -413,32 +442,33 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
       }
     }
     __syncthreads();
-    for (int it0 = r0; it0 < min(r0 + per, a.iters); it0 += IPB) {
+    for (int it0 = r0;; it0 += IPB) {
       // every tile against the next IPB hypotheses
-      const double (*g)[8] = gs + (it0 - r0);
-      const int* use = usable + (it0 - r0);
+      const double (*g)[8] = MANY ? gs + (it0 - r0) : gs;
+      const int* use = MANY ? usable + (it0 - r0) : usable;
       bool plain = false;
 #pragma unroll
       for (int q = 0; q < IPB; ++q) plain = plain || use[q] == 2;
-      // four hypotheses stay in registers over the tiles (read again for every
-      // tile they keep the LDS unit busier than the tests the vector ALU)
+      // four hypotheses of many stay in registers over the tiles (read again for
+      // every tile they keep the LDS unit busier than the tests the vector ALU)
+      constexpr bool HELD = MANY && IPB == 4;
       double r[4][8];
-      if constexpr (IPB == 4)
+      if constexpr (HELD)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
           for (int i = 0; i < 8; ++i) r[q][i] = g[q][i];
       int cnt = 0;  // lane q: hypothesis q
-      for (int t0 = 0; t0 < nwords * 64; t0 += NT) {
+      for (int t0 = w0 * 64; t0 < w1 * 64; t0 += NT) {
         const int t = t0 + tid, word = t >> 6;
-        if (word >= nwords) break;  // whole waves
+        if (word >= w1) break;  // whole waves
         const bool valid = (vb[word] >> lane) & 1ull;
-        const int4 m = t0 == 0 ? mine : tile_match(cxy, disp, min(t, ntiles - 1), ox, oy);
+        const int4 m = t0 == w0 * 64 ? mine : tile_match(cxy, disp, min(t, ntiles - 1), ox, oy);
         unsigned long long keep = 0ull;
 #pragma unroll 4
         for (int q = 0; q < IPB; ++q) {
           const unsigned long long b =
-              __ballot(valid && is_inlier<false>(IPB == 4 ? r[q & 3] : g[q], m, a.eps2));
+              __ballot(valid && is_inlier<false>(HELD ? r[q & 3] : g[q], m, a.eps2));
           if (lane == q) keep = b;
         }
         if (plain)
@@ -448,7 +478,12 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
             if (lane == q) keep = b;
           }
         cnt += __popcll(keep);
-        if (lane < IPB) inl[(size_t)word * IPB + lane] = keep;
+        if constexpr (SPLIT) {
+          if (lane < IPB && it0 + lane < a.iters)
+            J.b.part[(size_t)word * a.iters + it0 + lane] = keep;
+        } else {
+          if (lane < IPB) inl[(size_t)word * IPB + lane] = keep;
+        }
       }
       if (lane < IPB) wc[lane][wave] = cnt;
       __syncthreads();
@@ -461,6 +496,13 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
           for (int w = 0; w < NW; ++w) c += wc[lane][w];
           key = ((unsigned long long)(uint32_t)c << 32) |
                 (unsigned long long)(~(uint32_t)(it0 + lane));
+        }
+        if constexpr (SPLIT) {  // k_fit adds up the chunks' counts
+          if (lane < IPB && it0 + lane < a.iters)
+            J.b.key[(size_t)blockIdx.y * a.iters + it0 + lane] = key;
+          if (w0 == 0 && lane < IPB * 8 && it0 + (lane >> 3) < a.iters)
+            J.b.G[(size_t)it0 * 8 + lane] = g[lane >> 3][lane & 7];
+          return;
         }
         const unsigned int acc = (unsigned int)__ballot(c > delta);  // accepted
         const unsigned long long top = wave_max_u64(key);
@@ -479,11 +521,13 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_hyp(WeedJob one,
       }
       // (the first wave is done with the counts, the bits and the hypotheses
       // before they are written again)
-      if (MANY && (it0 + IPB < r0 + per || r0 + turn < a.iters)) __syncthreads();
+      if (!MANY) break;
+      const bool more = it0 + IPB < min(r0 + per, a.iters);
+      if (more || r0 + turn < a.iters) __syncthreads();
+      if (!more) break;
     }
-    if (!MANY) break;  // (fewer groups than blocks otherwise)
   }
-  if (wave != 0) return;
+  if (wave != 0 || SPLIT) return;
   if (lane < 8) J.b.G[(size_t)blockIdx.x * 8 + lane] = bg;
   if (lane == 0) J.b.key[blockIdx.x] = best;
   if ((int)(best >> 32) > delta)  // an accepted hypothesis: k_fit reads them
@@ -619,18 +663,20 @@ __device__ inline void solve_level(const WeedJob& J, const double* tot, int msel
   if (lane == 0) J.counts[1] = msel;
 }
 
-// Block x owns tile words [x wpb, (x + 1) wpb): the union M over the blocks
-// of k_hyp (per iterations a turn), flags 4 (in M) and 8 (in
-// the fit) of its tiles and their least-squares terms; the level's only block
+// Block x owns tile words [x wpb, (x + 1) wpb): the union M over the nhyp blocks
+// of k_hyp (per iterations a turn; in chunks: over the hypotheses, whose keys
+// are the chunks' with the counts added up), flags 4 (in M) and 8 (in the fit)
+// of its tiles and their least-squares terms; the level's only block
 // then solves, several leave their sums to k_solve. One block is enough for
 // kFitOne words (2048 tiles, four per thread); beyond, its one CU is the
 // limit (4860 tiles: 20 us in one block, 7.5 us in five and 5.6 for k_solve).
 // 7.6 us at 300 tiles, where a union over all the iterations' inlier rows and
 // a one-lane solve in a launch of its own took 10.1 + 6.6.
-template <bool JOBS>
+template <bool JOBS, int SLOTS>
 __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
                                                      const WeedJob* __restrict__ jobs,
-                                                     WeedArgs a, int per, int nhyp, int wpb) {
+                                                     WeedArgs a, int per, int nhyp, int chunks,
+                                                     int wpb) {
   const WeedJob J = JOBS ? jobs[blockIdx.z] : one;
   const int ntiles = J.ntiles, words = J.words;
   const int w0 = blockIdx.x * wpb, w1 = min(words, w0 + wpb);
@@ -639,8 +685,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
   const int32_t* __restrict__ disp = J.disp;
   uint8_t* __restrict__ flags = J.flags;
   constexpr int NW = kFitThreads / 64;
-  __shared__ __align__(16) double Gs[kWeedBlocks * 8];
+  __shared__ __align__(16) double Gs[SLOTS * 8];
   __shared__ unsigned long long M[kFitOne];
+  __shared__ uint32_t csum[NW][SLOTS];
   __shared__ long long part[NW][kSums];
   __shared__ double tot[kSums];
   __shared__ int msel;
@@ -656,8 +703,8 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
     m0 = tile_match(cxy, disp, tc0, ox, oy);
   }
   const int N = *J.b.nmatch;
-  constexpr int NK = kWeedBlocks / 64;  // hypothesis blocks per lane
-  static_assert(kWeedBlocks * 8 == 4 * kFitThreads, "four coefficients per thread");
+  constexpr int NK = SLOTS / 64;             // hypothesis blocks per lane
+  constexpr int NC = SLOTS * 8 / kFitThreads;  // coefficients per thread
   unsigned long long key[NK];
 #pragma unroll
   for (int u = 0; u < NK; ++u) {
@@ -665,9 +712,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
     key[u] = J.b.key[min(b, nhyp - 1)];
     if (b >= nhyp) key[u] = 0ull;
   }
-  double gr[4];
+  double gr[NC];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) gr[u] = J.b.G[min(tid + u * kFitThreads, nhyp * 8 - 1)];
+  for (int u = 0; u < NC; ++u) gr[u] = J.b.G[min(tid + u * kFitThreads, nhyp * 8 - 1)];
   // word wd's unions, a block per lane
   unsigned long long pr[NK];
   auto fetch = [&](int wd) {
@@ -682,6 +729,33 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
     hp = J.Hprev[e];
 #pragma unroll
     for (int i = 0; i < 3; ++i) hb[i] = J.Hbase[e / 3 * 3 + i];
+  }
+  if (chunks > 1) {
+    // a wave adds up every NW-th chunk's counts, all of them in flight
+    const int wpc = split_words(words, chunks), used = (words + wpc - 1) / wpc;
+    constexpr int PW = kSplitChunks / NW;
+#pragma unroll
+    for (int u = 0; u < NK; ++u) {
+      if (64 * u >= nhyp) break;
+      unsigned long long k[PW];
+#pragma unroll
+      for (int i = 0; i < PW; ++i)
+        k[i] = J.b.key[(size_t)min(wave + i * NW, used - 1) * nhyp + min(lane + 64 * u, nhyp - 1)];
+      uint32_t c = 0;
+#pragma unroll
+      for (int i = 0; i < PW; ++i) c += wave + i * NW < used ? (uint32_t)(k[i] >> 32) : 0u;
+      csum[wave][64 * u + lane] = c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NK; ++u) {
+      if (64 * u >= nhyp) break;
+      uint32_t c = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) c += csum[w][64 * u + lane];
+      if (lane + 64 * u < nhyp)
+        key[u] = (unsigned long long)c << 32 | (key[u] & 0xffffffffull);
+    }
   }
   const int delta = weed_delta(N, a);
   unsigned long long bkey = key[0];
@@ -708,7 +782,7 @@ __global__ __launch_bounds__(kFitThreads) void k_fit(WeedJob one,
     if (lane == 0) M[wd - w0] = v;
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) Gs[tid + u * kFitThreads] = gr[u];
+  for (int u = 0; u < NC; ++u) Gs[tid + u * kFitThreads] = gr[u];
   __syncthreads();
   double g[8];  // the best hypothesis
 #pragma unroll
@@ -808,18 +882,18 @@ WeedArgs weed_args(const lnr_params& p, int level) {
 namespace {
 // k_hyp, k_fit and, for a level of more than one k_fit block, k_solve over
 // njobs jobs of at most ntiles tiles.
-template <bool JOBS, int IPB, int NT, bool MANY>
+template <bool JOBS, int IPB, int NT, HypMode MODE>
 hipError_t launch_hyp(const WeedJob& one, const WeedJob* jobs, int njobs, int words,
                       const WeedArgs& a, const HypForm& f, hipStream_t st) {
-  const size_t lds = hyp_lds(words, IPB, f.per);
+  const size_t lds = hyp_lds(words, MODE == kSplitHyp ? 0 : IPB, MODE == kManyHyp ? f.per : 0);
   if (lds > 64 * 1024) {
     const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hyp<JOBS, IPB, NT, MANY>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hyp<JOBS, IPB, NT, MODE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  LNR_LAUNCH((k_hyp<JOBS, IPB, NT, MANY>), dim3(f.blocks, 1, njobs), dim3(NT), lds, st, one, jobs,
-             a, f.per);
+  LNR_LAUNCH((k_hyp<JOBS, IPB, NT, MODE>), dim3(f.blocks, f.chunks, njobs), dim3(NT), lds, st, one,
+             jobs, a, f.per);
   return hipGetLastError();
 }
 
@@ -831,15 +905,21 @@ hipError_t launch_weed(const WeedJob& one, const WeedJob* jobs, int njobs, int n
   const HypForm f = hyp_form(a.iters, ntiles, words, njobs);
   const bool many = f.per > (f.wide ? 4 : 8);
   hipError_t e =
-      f.wide ? many ? launch_hyp<JOBS, 4, 512, true>(one, jobs, njobs, words, a, f, st)
-                    : launch_hyp<JOBS, 4, 512, false>(one, jobs, njobs, words, a, f, st)
-             : many ? launch_hyp<JOBS, 8, 256, true>(one, jobs, njobs, words, a, f, st)
-                    : launch_hyp<JOBS, 8, 256, false>(one, jobs, njobs, words, a, f, st);
+      f.chunks > 1 ? launch_hyp<JOBS, 4, 512, kSplitHyp>(one, jobs, njobs, words, a, f, st)
+      : f.wide     ? many ? launch_hyp<JOBS, 4, 512, kManyHyp>(one, jobs, njobs, words, a, f, st)
+                          : launch_hyp<JOBS, 4, 512, kUsualHyp>(one, jobs, njobs, words, a, f, st)
+      : many       ? launch_hyp<JOBS, 8, 256, kManyHyp>(one, jobs, njobs, words, a, f, st)
+                   : launch_hyp<JOBS, 8, 256, kUsualHyp>(one, jobs, njobs, words, a, f, st);
   if (e != hipSuccess) return e;
   const int wpb = words <= kFitOne ? kFitOne : kFitWords;
   const int blocks = (words + wpb - 1) / wpb;
-  LNR_LAUNCH(k_fit<JOBS>, dim3(blocks, 1, njobs), dim3(kFitThreads), 0, st, one, jobs, a,
-             f.per, f.blocks, wpb);
+  const int per = f.chunks > 1 ? 1 : f.per, slots = f.chunks > 1 ? a.iters : f.blocks;
+  if (slots <= kWeedBlocks)
+    LNR_LAUNCH((k_fit<JOBS, kWeedBlocks>), dim3(blocks, 1, njobs), dim3(kFitThreads), 0, st, one,
+               jobs, a, per, slots, f.chunks, wpb);
+  else
+    LNR_LAUNCH((k_fit<JOBS, kSplitIters>), dim3(blocks, 1, njobs), dim3(kFitThreads), 0, st, one,
+               jobs, a, per, slots, f.chunks, wpb);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (blocks > 1) {
     LNR_LAUNCH(k_solve<JOBS>, dim3(1, 1, njobs), dim3(64), 0, st, one, jobs, wpb);

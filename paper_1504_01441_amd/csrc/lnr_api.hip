@@ -347,26 +347,35 @@ struct WeedPlan {
 
 size_t weed_words(int ntiles) { return ntiles > 0 ? (size_t)(ntiles + 63) / 64 : 1; }
 
+// blocks of a level's weeding, or hypotheses where those are on their own
+size_t weed_slots(int iters) {
+  return (size_t)(iters <= kSplitIters ? iters : weed_blocks(iters, 4));
+}
+
+size_t weed_key_bytes(int ntiles, int iters) {
+  const size_t chunks = std::min((weed_words(ntiles) + kSplitWords - 1) / kSplitWords,
+                                 (size_t)(iters <= kSplitIters ? kSplitChunks : 1));
+  return round256(sizeof(unsigned long long) * weed_slots(iters) * chunks);
+}
+
 // The keys and partial sums, which live from one weeding kernel to the next
 // only: a registration puts them where its propagation maps will be, so that
 // its workspace does not grow by them.
 size_t weed_passing_bytes(int ntiles, int iters) {
   const size_t fit_blocks = (weed_words(ntiles) + kFitWords - 1) / kFitWords;
-  return round256(sizeof(unsigned long long) * (size_t)weed_blocks(iters, 4)) +
-         sizeof(long long) * 24 * fit_blocks;
+  return weed_key_bytes(ntiles, iters) + sizeof(long long) * 24 * fit_blocks;
 }
 
-// passing: the offset of weed_passing_bytes
-WeedPlan plan_weed(Plan& pl, int ntiles, int iters, size_t passing) {
+WeedPlan plan_weed(Plan& pl, int ntiles, int iters) {
   WeedPlan w;
   const size_t words = weed_words(ntiles);
-  const size_t blocks = (size_t)weed_blocks(iters, 4);
+  const size_t slots = weed_slots(iters);
   w.nmatch = pl.take(sizeof(int32_t));
-  w.G = pl.take(sizeof(double) * 8 * blocks);
-  w.part = pl.take(sizeof(unsigned long long) * words * blocks);
+  w.G = pl.take(sizeof(double) * 8 * slots);
+  w.part = pl.take(sizeof(unsigned long long) * words * slots);
   w.vb = pl.take(sizeof(unsigned long long) * words);
-  w.key = passing;
-  w.psum = passing + round256(sizeof(unsigned long long) * blocks);
+  w.key = pl.off;  // weed_passing_bytes, taken by the caller: the next buffer
+  w.psum = w.key + weed_key_bytes(ntiles, iters);
   return w;
 }
 
@@ -418,8 +427,8 @@ PairPlan plan_pair(int W, int H, const lnr_params* p) {
   q.o_psrc = pl.take(q.g.pyr_bytes);
   q.o_warp = pl.take(N);
   const int nt = q.g.lv[0].ntx * q.g.lv[0].nty;
+  q.wp = plan_weed(pl, nt, p->weed_iters);
   q.o_maps = pl.take(std::max(dt_maps_bytes(W, H), weed_passing_bytes(nt, p->weed_iters)));
-  q.wp = plan_weed(pl, nt, p->weed_iters, q.o_maps);
   q.o_gt = pl.take(dt_guide_t_bytes(W, H));
   q.o_coef = pl.take((size_t)p->dt_iters * 256 * sizeof(double));
   const size_t nt0 = (size_t)q.g.lv[0].ntx * q.g.lv[0].nty;
@@ -1078,8 +1087,8 @@ lnr_status lnr_stage_weed_fit(lnr_ctx* ctx, const int32_t* corner_xy, const int3
     return fail(ctx, LNR_E_ARG, "bad weed/fit arguments");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, LNR_E_HIP, "hipSetDevice");
   Plan pl;
-  const size_t passing = pl.take(weed_passing_bytes(ntiles, p->weed_iters));
-  const WeedPlan wp = plan_weed(pl, ntiles, p->weed_iters, passing);
+  const WeedPlan wp = plan_weed(pl, ntiles, p->weed_iters);
+  pl.take(weed_passing_bytes(ntiles, p->weed_iters));
   if ((s = ensure_ws(ctx, pl.off, (hipStream_t)stream)) != LNR_OK) return s;
   const WeedBufs wb = weed_bufs(static_cast<char*>(ctx->ws), wp);
   LNR_HIP(launch_weed_fit(corner_xy, disp, flags, ntiles, w, h, level, *p, H_prev, H_out, counts,

@@ -203,6 +203,14 @@ inline int weed_blocks(int iters, int per_block) {
   return n < kWeedBlocks ? n : kWeedBlocks;
 }
 constexpr int kFitWords = 16;  // tile words per k_fit block where the level needs several
+// A few iterations over many tiles are tested in up to kSplitChunks chunks of
+// tile words (at least kSplitWords each), every hypothesis on its own ("block"
+// below is then a hypothesis, with a key per chunk that holds the chunk's count).
+constexpr int kSplitIters = 512, kSplitChunks = 32, kSplitWords = 8;
+__host__ __device__ inline int split_words(int words, int chunks) {  // words per chunk
+  const int n = (words + chunks - 1) / chunks;
+  return n < kSplitWords ? kSplitWords : n;
+}
 struct WeedBufs {
   int32_t* nmatch;          // [1] valid matches of the level
   unsigned long long* key;  // [blocks] best (count << 32 | ~iteration), 0: none usable

@@ -394,3 +394,38 @@ def test_pinned_flow_shapes_are_the_ones_that_run(lnr):
     (20, 15, 1025), (20, 15, 2049), (20, 15, 16384), (20, 15, 16389), (70, 61, 16389)])
 def test_weeding_of_many_iterations(lnr, ctx, nx, ny, iters):
     _weeding_parity(lnr, ctx, _weeding_case(nx, ny, 32, 0.8, iters + nx), iters)
+
+
+# few iterations over many tiles, tested in chunks of tiles: the first level
+# that takes chunks and the last that does not, a single iteration, groups left
+# short, the most hypotheses of the narrow and of the wide sums of the chunks'
+# counts and the first past them, chunks of one and of several turns; so few
+# valid matches that no hypothesis is usable
+@pytest.mark.parametrize("nx,ny,iters,keep", [
+    (64, 48, 17, 0.8), (61, 51, 17, 0.8), (61, 51, 1, 0.8), (61, 51, 256, 0.8),
+    (61, 51, 257, 0.8), (129, 65, 300, 0.8), (129, 65, 512, 0.8), (129, 65, 513, 0.8),
+    (250, 186, 5, 0.8), (250, 186, 128, 0.8), (250, 186, 129, 0.5), (70, 61, 40, 0.0005)])
+def test_weeding_of_few_iterations(lnr, ctx, nx, ny, iters, keep):
+    _weeding_parity(lnr, ctx, _weeding_case(nx, ny, 16, keep, iters + nx), iters)
+
+
+# a batch's levels in chunks, with pairs that have one and a few of them
+@pytest.mark.parametrize("iters", [3, 64, 400])
+@pytest.mark.parametrize("n", [1, 3, 5])
+def test_batch_of_few_iterations(lnr, ctx, n, iters):
+    rng = np.random.default_rng(n)
+    p = lnr.Params(tile=16, patch_r=3, quad_r=3, corner_step=1, radius0=2, radius_coarse=2,
+                   weed_iters=iters, dt_iters=1)
+    frames = []
+    for w, h in [(2592, 1944), (17, 16), (700, 500), (320, 200), (1000, 1300)][:n]:
+        y = np.kron(rng.integers(0, 256, (h // 4 + 1, w // 4 + 1)), np.ones((4, 4)))
+        y = y[:h, :w].astype(np.uint8)
+        frames.append((lnr.Frame.from_numpy(y), lnr.Frame.from_numpy(np.roll(y, (1, -1), (0, 1)))))
+    refs, srcs = [f[0] for f in frames], [f[1] for f in frames]
+    for graph in (False, True):
+        outs = lnr.register_batch(ctx, refs, srcs, p, graph=graph)
+        for r, s, got in zip(refs, srcs, outs):
+            want = lnr.register_pair(ctx, r, s, p)
+            torch.cuda.synchronize()
+            for k in ("corner_xy", "disp", "ssd", "flags", "counts", "H", "flow", "image"):
+                assert torch.equal(getattr(got, k), getattr(want, k)), k
