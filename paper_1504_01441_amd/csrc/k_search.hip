@@ -1019,6 +1019,9 @@ int window_stride(int d0, int ncand, int nstrips, int split, int KX, int rows_pe
   return best;
 }
 
+constexpr long long kOneGroupLanes = 262144;  // candidate lanes that fill the chip
+constexpr size_t kLdsGranule = 1280;          // workgroup memory is given out in these
+
 SearchShape make_shape(int R, const SearchCfg& c, int split, long long ntiles, int KX,
                        size_t* lds, int* block) {
   SearchShape sh{};
@@ -1036,7 +1039,7 @@ SearchShape make_shape(int R, const SearchCfg& c, int split, long long ntiles, i
     // when the level has too few candidate threads to fill the chip (coarse
     // levels, small windows), split the patch rows so that a tile keeps about
     // 256 threads busy
-    sh.split = ntiles * base >= 262144 ? 1 : (256 + base / 2) / base;
+    sh.split = ntiles * base >= kOneGroupLanes ? 1 : (256 + base / 2) / base;
   }
   if (sh.split < 1) sh.split = 1;
   if (sh.split > 7) sh.split = 7;
@@ -1172,10 +1175,30 @@ int search_split_candidates(int R, const SearchCfg& c, int* out, int max) {
 // per lane with make_shape's split. Measured on whole frames, us, against
 // the best 8-candidate shape: radius 16 15 (300 tiles, two groups) / 18, 21
 // (1200, one) / 28, 52 (4860) / 76, 102 (11625) / 160; radius 10 27 / 31 at
-// 3072 tiles but 17.7 / 17.4 at 1200; radius 32 28 / 32 at 300.
+// 3072 tiles but 17.7 / 17.4 at 1200; radius 32 28 / 32 at 300. Those are
+// patches of radius 10; the products pad every patch row to 64 bytes, so for
+// small patches it is the lanes, where they need no patch-row groups to fill the
+// chip, if all tiles are resident at once (radius 10, P 3, 4860 tiles: 21 / 24
+// with quadrants of 3, but 27 / 25 of 4, whose memory leaves 18 blocks per CU
+// for 19; not so radius 8 with quadrants of 2, P 4 20.6 / 17.0) and, up to P 3,
+// again from one and a half rounds on (radius 10, P 3, 7500 tiles 32 / 35,
+// 46,750 149 / 184; P 5 188 / 199, but 57 / 56 at 11,625), radius 8 with P 1 at
+// once (8748 tiles 31.8 / 34.3). And where radius 32 leaves most of the fifth
+// block empty on few tiles (100 tiles: P 1 15 / 14, P 3 15.7 / 15.2, P 4 15.9 /
+// 16.3).
 int auto_shape(int R, const SearchCfg& c, long long ntiles) {
   const int nb = (2 * R + 16) / 16;  // blocks of 16 candidates
   if (R < 8 || (R < 11 && ntiles < 2048)) return 0;
+  if (R < 11 && c.P < 6 && ntiles * (2 * R + 1) * ((2 * R + 8) / 8) >= kOneGroupLanes) {
+    size_t lds = 0;
+    int block = 0;
+    (void)make_shape(R, c, 1, ntiles, 8, &lds, &block);
+    const size_t taken = (lds + sizeof(TileShared) + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
+    const long long resident = 256 * (long long)(160 * 1024 / taken);
+    if (ntiles <= resident && (R > 8 || c.r > 2)) return 0;
+    if (c.P <= 3 && c.r <= 8 && ((R == 8 && c.P < 2) || 2 * ntiles >= 3 * resident)) return 0;
+  }
+  if (nb == kMaxNB && c.P <= 3 && ntiles < 256) return 0;
   int split = (int)((2400 + ntiles * nb / 2) / std::max(ntiles * nb, 1ll));
   split = std::min(std::max(split, 1), 3);
   while (split > 1 && !search_shape_fits(R, c, split | kSearchMfma)) --split;

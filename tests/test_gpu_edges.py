@@ -429,3 +429,34 @@ def test_batch_of_few_iterations(lnr, ctx, n, iters):
             torch.cuda.synchronize()
             for k in ("corner_xy", "disp", "ssd", "flags", "counts", "H", "flow", "image"):
                 assert torch.equal(getattr(got, k), getattr(want, k)), k
+
+
+# the automatic search shapes on both sides of every line between them: the
+# matrix cores at radius 11 and below (from 2048 tiles), their patch-row groups
+# by the number of tiles, the patches and quadrants that go to the lanes, and
+# radius 32 on few tiles
+@pytest.mark.parametrize("tile,nx,ny,R,P,r", [
+    (32, 1, 1, 11, 1, 10), (32, 1, 1, 11, 10, 10), (32, 3, 1, 16, 1, 10), (32, 2, 1, 16, 10, 10),
+    (32, 1, 2, 24, 1, 10), (32, 1, 3, 24, 10, 10), (32, 1, 1, 32, 10, 10), (32, 3, 1, 32, 4, 10),
+    (32, 23, 89, 8, 10, 10), (32, 32, 64, 8, 10, 10), (32, 23, 89, 10, 7, 3),
+    (32, 32, 64, 10, 7, 3), (16, 24, 20, 11, 3, 3), (16, 13, 37, 11, 3, 3), (16, 25, 32, 11, 5, 3),
+    (16, 9, 89, 11, 5, 3), (16, 20, 16, 16, 2, 3), (16, 3, 107, 16, 2, 3), (16, 64, 65, 10, 3, 3),
+    (16, 49, 85, 10, 3, 3), (16, 49, 85, 10, 5, 5), (32, 64, 81, 8, 5, 5), (32, 64, 81, 8, 5, 6),
+    (16, 15, 17, 32, 3, 3), (16, 16, 16, 32, 3, 3), (16, 15, 17, 32, 1, 2), (16, 15, 17, 32, 4, 3)])
+def test_automatic_search_shapes(lnr, ctx, tile, nx, ny, R, P, r):
+    rng = np.random.default_rng(nx * 100 + R)
+    w, h = tile * nx, tile * ny
+    base = np.kron(rng.integers(0, 256, (h // 4 + 4, w // 4 + 4)), np.ones((4, 4)))
+    a = np.clip(base[3:3 + h, 5:5 + w] + rng.integers(-3, 4, (h, w)), 0, 255).astype(np.uint8)
+    b = np.clip(base[1:1 + h, 2:2 + w] + rng.integers(-3, 4, (h, w)), 0, 255).astype(np.uint8)
+    kw = dict(tile=tile, patch_r=P, quad_r=r, corner_step=1, min_level_dim=64)
+    p, op = lnr.Params(**kw), oracle.params(**kw)
+    t = lambda v: torch.from_numpy(v).cuda()
+    cxy, disp, ssd, flags = (v.cpu().numpy() for v in lnr.stage_search(ctx, t(a), t(b), R, p))
+    cx, cy, has = oracle.corners(a, op)
+    dx, dy, want, valid = oracle.search(a, b, R, cx, cy, has, op)
+    assert np.array_equal(flags & 1, has) and np.array_equal((flags & 2) > 0, valid > 0)
+    v = valid > 0
+    assert v.any() or nx * ny < 4
+    assert np.array_equal(disp[v, 0], dx[v]) and np.array_equal(disp[v, 1], dy[v])
+    assert np.array_equal(ssd[v].view(np.uint32), want[v])
