@@ -287,12 +287,12 @@ lnr_status lnr_stage_irradiance(lnr_ctx* ctx, int32_t n, int32_t ch, int32_t w, 
 lnr_status lnr_register_batch(lnr_ctx* ctx, const lnr_frame* refs, const lnr_frame* srcs,
                               int32_t n, const lnr_params* p, lnr_registration* outs,
                               int32_t flags, void* stream);
-/* Time every domain-transform kernel shape that covers w x h (Sec. 2.4 pass;
- * results do not depend on the shape), those of lnr_flow_shapes and the ones
- * with the column shape used by default at this height, and use the fastest
- * for that size from then on. shape_out[5] (optional): rows per thread, row
- * block, rows per column segment, columns per block, segments per column.
- * Synchronises. */
+/* Time the domain-transform kernel shapes for w x h (Sec. 2.4 pass; results
+ * do not depend on the shape): every row shape that covers it, with the column
+ * shapes whose segments take the fewest rows that cover the height (as by
+ * default). The fastest is used for that size from then on. shape_out[5]
+ * (optional): rows per thread, row block, rows per column segment, columns per
+ * block, segments per column. Synchronises. */
 lnr_status lnr_autotune_flow(lnr_ctx* ctx, int32_t w, int32_t h, const lnr_params* p,
                              int32_t* shape_out, void* stream);
 /* Use one propagation kernel shape (five values, in the order of

@@ -483,8 +483,9 @@ __global__ __launch_bounds__(NCOL * NSEG, 4) void k_dt_col(Rec* __restrict__ map
     hold(a1[j]);
     hold(a2[j]);
   }
-  // |g[j] - g[j - 1]| of rows j = 0 .. L as a byte offset into the table, 11
-  // bits each; rows past the ends (and the image's) take the 0 behind it
+  // |g[j] - g[j - 1]| of rows j = 0 .. L as a byte offset into the table, in
+  // 16 bits each (12 used); rows past the ends (and the image's) take the 0
+  // behind it
 #define GB(j)                                                              \
   ((j) < 0 ? (int)gup                                                      \
    : (j) >= L ? (int)gdn                                                   \
@@ -652,9 +653,9 @@ hipError_t col_pass(const DtShape& s, bool last, Rec* maps, const uint8_t* gt, i
   // the listed shapes
   COL(8, 8, 128) COL(8, 4, 128) COL(16, 4, 128) COL(8, 2, 256) COL(24, 4, 128)
   COL(16, 2, 256) COL(24, 2, 256)
-  // the other defaults
-  COL(4, 8, 128) COL(12, 4, 128) COL(20, 4, 128) COL(16, 4, 256) COL(20, 4, 256)
-  COL(24, 4, 256)
+  // the others of the fewest rows
+  COL(4, 8, 128) COL(4, 4, 128) COL(12, 4, 128) COL(20, 4, 128)
+  COL(4, 4, 256) COL(8, 4, 256) COL(12, 4, 256) COL(16, 4, 256) COL(20, 4, 256) COL(24, 4, 256)
 #undef COL
   return hipErrorInvalidValue;
 }
@@ -662,42 +663,61 @@ hipError_t col_pass(const DtShape& s, bool last, Rec* maps, const uint8_t* gt, i
 bool same_col(const DtShape& a, const DtShape& b) {
   return a.l == b.l && a.ncol == b.ncol && a.nseg == b.nseg;
 }
+
+bool listed_col(const DtShape& s) {
+  for (const DtShape& c : kColShapes)
+    if (same_col(c, s)) return true;
+  return false;
+}
+
+// The column shapes of a height: the fewest rows per segment (whole guide
+// words) that cover it, which leaves no segment idle (1440 rows would fill 90
+// of 128 segments of 16: of 12, all 120), in blocks of eight columns (up to 8
+// rows) or four by 128 segments, or of four by 256.
+struct ColForm {
+  int ncol, nseg, most;
+};
+constexpr ColForm kColForms[] = {{8, 128, 8}, {4, 128, 24}, {4, 256, 24}};
+
+DtShape fewest_rows(const ColForm& f, int H) {
+  return DtShape{0, 0, ((H + f.nseg - 1) / f.nseg + 3) / 4 * 4, f.ncol, f.nseg};
+}
 }  // namespace
 
-// A listed row shape with a listed column shape or with the height's default.
+// A listed row shape with a listed column shape or with one of the height's.
 bool dt_shape_valid(const DtShape& s, int W, int H) {
-  bool row = false, col = same_col(s, dt_default_shape(W, H));
+  bool row = false, col = listed_col(s);
   for (const DtShape& r : kRowShapes) row |= r.seg == s.seg && r.nt == s.nt;
-  for (const DtShape& c : kColShapes) col |= same_col(c, s);
+  for (const ColForm& f : kColForms) col |= s.l <= f.most && same_col(s, fewest_rows(f, H));
   return row && col && W <= s.seg * s.nt && H <= s.l * s.nseg;
 }
 
-// Every listed (row, column) pair that covers W x H, then (tuner) the row
-// shapes with the height's default column shape where that is not listed.
+// Every listed (row, column) pair that covers W x H; for the tuner, the row
+// shapes with the height's column shapes instead. Of 28 sizes none was faster
+// with a listed column shape of more rows or of two columns, and 4000 x 3000
+// takes 12 rows by 256 segments (a registration 897 us, against 922 with the
+// fastest listed one).
 int dt_shape_candidates(int W, int H, DtShape* out, int max, bool tuner) {
   int n = 0;
   auto add = [&](const DtShape& r, const DtShape& c) {
     const DtShape s{r.seg, r.nt, c.l, c.ncol, c.nseg};
     if (dt_shape_valid(s, W, H) && n < max) out[n++] = s;
   };
-  for (const DtShape& r : kRowShapes)
-    for (const DtShape& c : kColShapes) add(r, c);
-  if (!tuner) return n;
-  const DtShape def = dt_default_shape(W, H);
-  for (const DtShape& c : kColShapes)
-    if (same_col(c, def)) return n;
-  for (const DtShape& r : kRowShapes) add(r, def);
+  for (const DtShape& r : kRowShapes) {
+    if (tuner)
+      for (const ColForm& f : kColForms) add(r, fewest_rows(f, H));
+    else
+      for (const DtShape& c : kColShapes) add(r, c);
+  }
   return n;
 }
 
-// The default: the fewest pixels per thread that cover a row, and segments of
-// the fewest rows (whole guide words) that cover the height, which leaves no
-// segment idle (1440 rows would fill 90 of 128 segments of 16: of 12, all
-// 120). Heights of more than 128 segments of 24 rows take 256 of them in
-// blocks of four columns, not two: runs of 48 bytes per row instead of 24
-// (3000 x 4000: 85 -> 72 us, last 139 -> 103). The column kernels' launch
-// bound holds them to 128 registers, which segments of 24 rows exceed by 24 to
-// 28 bytes of scratch per lane.
+// The default: the fewest pixels per thread that cover a row, and one of the
+// height's column shapes. Heights of more than 128 segments of 24 rows take
+// 256 of them in blocks of four columns, not two: runs of 48 bytes per row
+// instead of 24 (3000 x 4000: 85 -> 72 us, last 139 -> 103). The column
+// kernels' launch bound holds them to 128 registers, which segments of 24 rows
+// exceed by 24 to 28 bytes of scratch per lane.
 DtShape dt_default_shape(int W, int H) {
   DtShape s;
   if (W <= 1024) { s.seg = 4; s.nt = 256; }
@@ -705,10 +725,8 @@ DtShape dt_default_shape(int W, int H) {
   else if (W <= 3072) { s.seg = 12; s.nt = 256; }
   else if (W <= 4096) { s.seg = 8; s.nt = 512; }
   else { s.seg = 12; s.nt = 512; }
-  s.nseg = H <= 3072 ? 128 : 256;
-  s.ncol = H <= 1024 ? 8 : 4;
-  s.l = ((H + s.nseg - 1) / s.nseg + 3) / 4 * 4;
-  return s;
+  const DtShape c = fewest_rows(kColForms[H <= 1024 ? 0 : H <= 3072 ? 1 : 2], H);
+  return DtShape{s.seg, s.nt, c.l, c.ncol, c.nseg};
 }
 
 static DtArgs dt_args(const lnr_params& p) {

@@ -250,7 +250,7 @@ hipError_t launch_weed_fit(const int32_t* corner_xy, const int32_t* disp, uint8_
 // ---- domain-transform propagation (k_dt.hip)
 // Kernel shapes: rows of SEG pixels per thread in NT-thread blocks; columns as
 // NCOL columns x NSEG segments of L rows per block. Only the listed
-// combinations and the default of the size are valid (dt_shape_valid).
+// combinations and the column shapes of the height are valid (dt_shape_valid).
 struct DtShape {
   int seg, nt;         // row kernel
   int l, ncol, nseg;   // column kernel

@@ -355,6 +355,32 @@ def test_flow_default_column_shapes(lnr, ctx, w, h):
     assert (np.abs(nt.cpu().numpy() - n) <= 1e-4 * (np.abs(n) + 1.0)).all()
 
 
+# the column shapes that only the tuner takes, at the first and last heights
+# that have each: 4 rows by 128 segments in blocks of four columns,
+# and 4, 8 and 12 rows by 256 segments
+@pytest.mark.parametrize("w,h,l,nseg", [
+    (37, 32, 4, 128), (40, 511, 4, 128), (33, 512, 4, 128), (36, 130, 4, 256), (35, 1024, 4, 256),
+    (38, 1025, 8, 256), (33, 2048, 8, 256), (40, 2049, 12, 256), (37, 3000, 12, 256),
+    (34, 3072, 12, 256)])
+def test_flow_column_shapes_of_the_tuner(lnr, w, h, l, nseg):
+    c = lnr.Context(0)
+    p, op = lnr.Params(), oracle.params()
+    lnr.set_flow_shape(c, w, h, (4, 256, l, 4, nseg))
+    cx, cy, dx, dy, keep, guide = _flow_case(w, h, w + h)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    flow, nt = lnr.stage_flow(c, t(np.stack([cx, cy], 1)), t(np.stack([dx, dy], 1)),
+                              t(keep * 7), t(guide), p)
+    u, v, n = oracle.sparse_to_dense(cx, cy, dx, dy, keep, guide, op)
+    mask = n > 2e-30
+    for got, want in ((flow[0], u), (flow[1], v)):  # the FP32 stages' bound, 1e-4 relative
+        err = np.abs(got.cpu().numpy().astype(np.float64) - want)
+        assert (err <= 1e-4 * (np.abs(want) + 1.0))[mask].all()
+    assert (np.abs(nt.cpu().numpy() - n) <= 1e-4 * (np.abs(n) + 1.0)).all()
+    with pytest.raises(lnr.LnrError):  # not the fewest rows, and not listed
+        lnr.set_flow_shape(c, w, h, (4, 256, l + 4, 4, 256))
+    c.close()
+
+
 # a pinned shape's rows per segment are the rows that run, whatever the height
 # needs: where a segment ends shows in the last bits of the flow, so that other
 # rows give other bits (within the bound), and the same pin gives the same
