@@ -53,9 +53,8 @@ struct WarpSrc {
 // byte gathers, separate divisions and 64-bit offsets about 330 per pixel, 51
 // us for a 5 MP I420 frame and 64 for NV12. So the two taps of a row are one
 // load, the divisions share a reciprocal, the offsets are 32 bits and the
-// bilinear steps fused: 39 and 37 us. (Held to 64 registers by a launch bound
-// it spills and gains 1.5 us more; the next row's flow loaded ahead gains
-// nothing.)
+// bilinear steps fused: 39 and 37 us, in 62 registers. (The next row's flow
+// loaded ahead gains nothing.)
 template <typename OFF>
 __global__ __launch_bounds__(256) void k_bwarp(WarpSrc s, const double* __restrict__ Hn,
                                                const float* __restrict__ flow, int rows,
