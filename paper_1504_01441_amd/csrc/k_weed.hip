@@ -231,7 +231,6 @@ static_assert(hyp_lds(kMaxWords, 4, 64) <= kHypLdsMax, "the wide form takes ever
 
 // The kernels below take one level of one pair (JOBS false: the job is the
 // kernel argument) or a table of jobs, one per blockIdx.z (batches).
-//
 
 // How k_hyp splits a level's iterations: hypotheses that a block tests
 // together (ipb) and its threads, hypotheses that it solves together (per) and
